@@ -11,16 +11,13 @@ measure all, 1 shot (the rowsum-dominated single-tableau case).
 
 One JSON line is printed with circuits/s, the roofline of the dominant kernel
 and the CPU oracle timed on a bounded sample of the same workload.  At the
-default size the dominant kernel is k_blk, the blocked measurement pass
-(random measurements applied 32 at a time as one low-rank update to the
-tableau held in registers); where it does not run, the register-resident
-rowsum kernel k_meas_xz.  Both keep the tableau on chip, so their bound is
-the ALU: the method's algorithmic 32-bit lane operations (from the
-device-side support counters) over the kernel's time (HIP events recorded on
-its stream around every launch of the timed steps), against the MI355X's
-vector rate.  The HBM-equivalent rate of the same work is kept as
-effective_alg_gbs.  On the per-measurement path (n > 10,240) the sweep
-streams the tableau through HBM and is reported against HBM.
+default size the dominant kernel is k_lr_sweep (64 measurements applied at
+a time as one low-rank update of the tableau, which stays in the Infinity
+Cache), reported against the ALU: the method's algorithmic 32-bit lane
+operations (from the device-side support counters) over the kernel's time
+(HIP events recorded on its stream around every launch of the timed steps),
+against the MI355X's vector rate.  The HBM-equivalent rate of the same work
+is kept as effective_alg_gbs.
 
 Further legs on the same line: the n = 64 and n = 1,024 workloads, the
 batched 4,096-circuit workload (batched vs one circuit per launch, wall and
@@ -45,35 +42,6 @@ LDS_PEAK_GBS = 256 * 128 * 2.4   # 256 CUs x 128 B/clk x 2.4 GHz = 78,643 GB/s
 # operations, so the chip retires 78.6e12 32-bit lane operations per second
 VALU_PEAK_TOPS = 157.3 / 2
 
-# HBM bytes per launch of the dominant kernel from hardware counters
-# (FETCH_SIZE and WRITE_SIZE, each scaled by what it reads for a copy of known
-# size), valid only for the kernel sources they were taken on.
-TRAFFIC = {
-    "k_blk": {
-        "sources": ("paper_2408_00384_amd/csrc/measure_block.hip", "paper_2408_00384_amd/csrc/internal.h"),
-        "sha256": "c6b91930278990bdaec921c5e613334314a5fd1f9e98758708a7a49e753da28e",
-        "bytes_per_launch": 2.504e+08,
-        "summary": "profiles/k_blk_plain_n10000_measure_all.md",
-    },
-    "k_meas_xz": {
-        "sources": ("paper_2408_00384_amd/csrc/measure_persist.hip", "paper_2408_00384_amd/csrc/internal.h"),
-        "sha256": "09f7ac8514d610188a899c7140616b3bf5c1c5c6c1be21e5187d6928cdeecbf2",
-        "bytes_per_launch": 1.1221e+09,
-        "summary": "profiles/k_meas_xz_plain_n10000_measure_all.md",
-    },
-}
-
-
-def traffic_for(kernel: str):
-    import hashlib
-    rec = TRAFFIC.get(kernel)
-    if rec is None:
-        return None
-    h = hashlib.sha256()
-    for f in rec["sources"]:
-        h.update(open(os.path.join(ROOT, f), "rb").read())
-    return rec["bytes_per_launch"] if h.hexdigest() == rec["sha256"] else None
-
 WORKLOADS = {
     "small": dict(desc="plain CHP n=64, 64 layers, measure all, 16 shots", steps=20, warmup=3),
     "mid": dict(desc="plain CHP n=1024, 100 layers, measure all, 128 shots", steps=5, warmup=1),
@@ -81,9 +49,8 @@ WORKLOADS = {
 }
 
 
-def alu_roofline(counters, n, steps, sweep_ms, launches, traffic, blocked=False):
-    """Roofline of the register-resident kernel that measured (k_blk, the
-    blocked pass, or k_meas_xz, one rowsum sweep per measurement).
+def alu_roofline(counters, n, steps, sweep_ms, launches):
+    """Roofline of the measuring kernel (k_lr_sweep).
 
     Per random measurement with pivot-row support s (columns where the pivot
     row is not I), s_x (with an X part) and s_z (with a Z part), the sweep
@@ -93,10 +60,9 @@ def alu_roofline(counters, n, steps, sweep_ms, launches, traffic, blocked=False)
     operations, i.e. 8 s + 4 (s_x + s_z) = 4 (2 s + s_x + s_z) 32-bit lane
     operations per row word.  The device counters give sum(2 s + s_x + s_z)
     through the algorithmic bytes (8 W (2 s + s_x + s_z + 3) + 80 n per random
-    measurement, 8 n W per deterministic one).  The blocked pass does the
+    measurement, 8 n W per deterministic one).  The low-rank update does the
     same measurements with fewer operations (the phase terms are summed once
-    per block of 32); the count stays the method's, so that the two kernels
-    are measured on one scale."""
+    per block of 64); the count stays the method's."""
     W = (2 * n + 63) // 64
     nr, nd = counters["random"], counters["deterministic"]
     sup = (counters["alg_bytes"] - nr * (24 * W + 80 * n) - nd * 8 * n * W) // (8 * W)
@@ -106,20 +72,19 @@ def alu_roofline(counters, n, steps, sweep_ms, launches, traffic, blocked=False)
     achieved = ops_launch / avg_s / 1e12 if avg_s > 0 else 0.0
     sweep_bytes = counters["alg_bytes"] - (8 * W * 3 + 80 * n) * nr
     return {
-        "kernel": ("k_blk (blocked measurement pass: 32 random measurements per low-rank update, one launch "
-                   "per chunk of measurements)" if blocked else
-                   "k_meas_xz (register-resident rowsum sweep, one launch per chunk of measurements)"),
+        "kernel": "k_lr_sweep (64 measurements per launch as one low-rank update; the launch also plans the next 64 "
+                  "and updates the signs of the last)",
         "bound": "alu", "achieved": achieved, "peak": VALU_PEAK_TOPS, "unit": "TOP/s",
         "frac": achieved / VALU_PEAK_TOPS,
-        "traffic": traffic,
+        "traffic": None,
         "launches": launches, "avg_launch_us": avg_s * 1e6,
         "alg_lane_ops_per_launch": ops_launch,
         "support_sum_per_step": int(sup),
         "effective_alg_gbs": steps * sweep_bytes / (sweep_ms * 1e-3) / 1e9 if sweep_ms > 0 else 0.0,
         "note": "32-bit lane operations 4 W sum(2 s + s_x + s_z) per launch over the launch time; peak "
                 "157.3 TFLOP/s fp32 / 2 = 78.6e12 lane ops/s (65.8e12 measured for v_xor_b32 by "
-                "cliff_calibrate); effective_alg_gbs = the sweep's HBM-streaming bytes over the same time "
-                "(the tableau stays on chip, so this exceeds HBM and is not a roofline)",
+                "cliff_calibrate); effective_alg_gbs = the bytes a sweep per measurement would stream over "
+                "the same time (not a roofline)",
     }
 
 
@@ -559,11 +524,11 @@ def bench_fig2a(P, torch, np, lists_by_n, gen_s):
 
 
 def bench_xlarge(P, torch, np, k=256, reps=2):
-    """The HBM-bound path beyond the Infinity Cache: n = 25,000 (a 313 MB
-    tableau; the register-resident path holds at most n = 10,240), gates, then
-    qubits 0..k-1 measured, one per-measurement kernel each.  Reports the
-    sweep kernels' algorithmic HBM bandwidth (device counters over HIP-event
-    kernel time); the first 32 outcomes are compared with the oracle's."""
+    """A tableau beyond the Infinity Cache: n = 25,000 (313 MB), gates, then
+    qubits 0..k-1 measured.  Reports the sweep kernel's HBM bandwidth: the
+    tableau read and written once per 64 measurements, over HIP-event kernel
+    time (words that do not change are not written, so this counts at most
+    what moves); the first 32 outcomes are compared with the oracle's."""
     from inputs import plain_xlarge
     c = plain_xlarge()
     ctx = P.Context(0)
@@ -588,8 +553,8 @@ def bench_xlarge(P, torch, np, k=256, reps=2):
             best = (wall, prof, P.cliff_tab_counters(tab.handle), out, rnd)
     wall, prof, counters, out, rnd = best
     nr = counters["random"]
-    sweep_bytes = counters["alg_bytes"] - (8 * W * 3 + 80 * n) * nr
-    sweep_ms, launches = prof["sweep"]
+    sweep_ms, launches = prof["blocked"]
+    sweep_bytes = launches * 4 * n * W * 8
     gbs = sweep_bytes / (sweep_ms * 1e-3) / 1e9 if sweep_ms > 0 else 0.0
     parity = None
     gold = os.path.join(ROOT, "tests", "golden", "plain_xlarge_prefix.json")
@@ -607,8 +572,8 @@ def bench_xlarge(P, torch, np, k=256, reps=2):
         "tableau_bytes": 2 * n * W * 8,
         "measurements": k, "random": int(nr), "ms_measure": wall * 1e3,
         "us_per_measurement": wall * 1e6 / k,
-        "sweep": {"kernel": "k_step (one launch per measurement)", "launches": launches,
-                  "ms": sweep_ms, "alg_bytes": sweep_bytes, "alg_gbs": gbs, "frac_of_8000": gbs / HBM_PEAK_GBS},
+        "sweep": {"kernel": "k_lr_sweep (one launch per 64 measurements)", "launches": launches,
+                  "ms": sweep_ms, "bytes": sweep_bytes, "gbs": gbs, "frac_of_8000": gbs / HBM_PEAK_GBS},
         "parity_first_32_vs_stored_oracle": parity,
     }
 
@@ -787,30 +752,10 @@ def main():
         P.cliff_ctx_profile(ctx.handle, False)
     # device counters cover the last step (init clears them); steps are identical
     counters = P.cliff_tab_counters(tab.handle)
-    n, W = c.n, (2 * c.n + 63) // 64
-    nr, nd = counters["random"], counters["deterministic"]
     alg_step = counters["alg_bytes"]
-    # the sweep kernel's share: x/z words of the pivot-touching columns
-    # (random) and the stabilizer halves (deterministic); the update mask,
-    # counter planes and row rewrites belong to the finalize kernels
-    sweep_step = alg_step - (8 * W * 3 + 80 * n) * nr
-    sweep_ms, sweep_launches = prof["sweep"]
     blk_ms, blk_launches = prof["blocked"]
-    persistent = sweep_launches < steps * len(qubits)
     meas_ms = sum(prof[k][0] for k in ("select", "sweep", "final", "blocked"))
-    if blk_launches and blk_ms > sweep_ms:
-        roofline = alu_roofline(counters, n, steps, blk_ms, blk_launches,
-                                traffic_for("k_blk") if args.workload == "large" else None, blocked=True)
-    elif persistent:
-        roofline = alu_roofline(counters, n, steps, sweep_ms, sweep_launches,
-                                traffic_for("k_meas_xz") if args.workload == "large" else None)
-    else:
-        achieved = steps * sweep_step / (sweep_ms * 1e-3) / 1e9 if sweep_ms > 0 else 0.0
-        roofline = {"kernel": "k_step (rowsum sweep, one launch per measurement)",
-                    "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                    "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                    "launches": sweep_launches, "avg_launch_us": 1e3 * sweep_ms / max(1, sweep_launches),
-                    "alg_bytes_per_launch": steps * sweep_step / max(1, sweep_launches)}
+    roofline = alu_roofline(counters, c.n, steps, blk_ms, blk_launches)
     tab.close()
     ctx.close()
     print("# kernels over %d steps: " % steps
@@ -866,7 +811,7 @@ def main():
         result["fig2a"] = bench_fig2a(P, torch, np, fig2a_lists, fig2a_gen_s)
         result["random_clifford"] = result["fig2a"]["per_n"][-1]   # n = 1000
     if not args.no_xlarge:
-        print("# n = 25,000, per-measurement kernels ...", file=sys.stderr, flush=True)
+        print("# n = 25,000 ...", file=sys.stderr, flush=True)
         result["xlarge_hbm"] = bench_xlarge(P, torch, np)
     if not args.no_cpu_baseline:
         print("# cpu baseline (oracle) ...", file=sys.stderr, flush=True)

@@ -16,10 +16,10 @@
  *  - Device memory belongs to the caller.  A tableau is a view bound onto one
  *    caller-owned device buffer of cliff_tab_bytes(n, shots) bytes; the library
  *    never frees it.  The context owns only its own staging buffers and the
- *    register-resident measurement's chunk scratch (allocated at the first
- *    such measurement, grown to the largest tableau shape the context has
- *    measured: about 270 MB at n = 4,096, 2.2 GB at n = 10,000; freed by
- *    cliff_ctx_destroy).
+ *    measurement scratch (allocated at the first measurement, grown to the
+ *    largest tableau shape the context has measured: 3 MB at n = 10,000 in
+ *    the automatic mode; the register-resident modes take about 270 MB at
+ *    n = 4,096, 2.2 GB at n = 10,000; freed by cliff_ctx_destroy).
  *  - Host pointers are read (inputs) or written (outputs) before the call
  *    returns.  Calls that return host data synchronize the context stream;
  *    the others only enqueue work on it.
@@ -117,17 +117,20 @@ int cliff_ctx_set_gate_mode(cliff_ctx *ctx, int mode);
  * first deterministic one); where the blocked launch shape does not fit
  * (n in (2040 L, 2048 L] for L = ceil(2n/4096), e.g. n = 2041..2048,
  * 8161..8192, 10201..10240) it is PERSISTENT.  STEP: one kernel per
- * measurement.  AUTO: BLOCKED for n >= 2048, PERSISTENT below, STEP where
- * neither fits.  Results are identical; only speed differs.  A measure-all of
- * a dense state at n = 10,000 takes 16.1 ms with BLOCKED against 38.7 ms with
- * PERSISTENT (6,000: 9.5 against 16.5 ms; 2,100: 4.0 against 4.6 ms); a GHZ
- * measure-all (n - 1 of n outcomes deterministic) takes 61 ms with the
- * register-resident path at n = 10,000 against 125 ms with STEP.  From
- * n = 3,000 the blocked pass works in chunks of 2048 measurements, whose
- * scratch (about 5.6 GB at n = 10,000) the context allocates at its first
- * such call; if device memory refuses it, the call runs with the
- * per-measurement path's smaller chunks instead (same results;
- * cliff_last_error then names the refused allocation). */
+ * measurement.  AUTO: any n, in blocks of 64 measurements, random and
+ * deterministic ones alike, each block one low-rank update of the tableau in
+ * memory (two launches per block, a few MB of context-owned scratch).  AUTO
+ * takes the register-resident path instead while the context's stream is
+ * being captured (BLOCKED for n >= 2048, PERSISTENT below), and STEP for
+ * lists of up to 32 qubits above n = 10,240, under capture above n = 10,240,
+ * or when the scratch cannot be had.  Results are identical; only speed
+ * differs.  A measure-all of a dense state at n = 10,000 takes 10.1 ms with
+ * AUTO, 16.1 ms with BLOCKED and 38.7 ms with PERSISTENT.  From n = 3,000 the
+ * BLOCKED pass works in chunks of 2048 measurements, whose scratch (about
+ * 5.6 GB at n = 10,000) the context allocates at its first such call; if
+ * device memory refuses it, the call runs with the per-measurement path's
+ * smaller chunks instead (same results; cliff_last_error then names the
+ * refused allocation). */
 #define CLIFF_MEASURE_AUTO 0
 #define CLIFF_MEASURE_STEP 1
 #define CLIFF_MEASURE_PERSISTENT 2
@@ -294,10 +297,10 @@ int cliff_apply_cond_paulis(cliff_tab *tab, const uint32_t *qubits, const uint8_
  * nothing and stages nothing through the context: the qubit list and the
  * register-resident pass's chunk scratch live in a static device array of
  * CLIFF_NOALLOC_SCRATCH_BYTES that the library keeps on each GPU it runs on
- * until the process ends (its chunks are as large as fits there, 48
- * measurements at n = 10,000, and it does not take the blocked pass, where
- * cliff_measure_record takes chunks of 2048, so large n run slower than with
- * cliff_measure_record).  Every call on a GPU uses that GPU's one array:
+ * until the process ends (the automatic mode runs there as it does
+ * elsewhere, also under capture; the register-resident modes' chunks are as
+ * large as fits there, 48 measurements at n = 10,000, without the blocked
+ * pass).  Every call on a GPU uses that GPU's one array:
  * calls that overlap on one GPU (several host threads, or contexts on
  * different streams) race and must be serialized by the caller.
  * CLIFF_EINVAL as cliff_measure_record and while kernel timing

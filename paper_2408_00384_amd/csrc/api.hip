@@ -1,6 +1,6 @@
 // C ABI of the tableau library: argument checks, gate encoding, launches and
 // host <-> device marshalling.  Every step of the simulation itself runs in
-// the kernels of gates.hip, measure_step.hip, measure_persist.hip and batch.hip.
+// the kernels of gates.hip, the measure_*.hip files and batch.hip.
 #include <stdarg.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -842,12 +842,61 @@ static int ctx_persist_scratch(cliff_ctx *c, size_t need, uint8_t **base) {
 static int noalloc_persist_scratch(cliff_ctx *c, const Dims &d, const uint32_t *qubits, size_t cnt,
                                    uint32_t *kc, uint8_t **base, const uint32_t **dev_qubits);
 
+// The low-rank pass of the automatic mode.  *done = false: not taken (its
+// scratch is not to be had, or the stream is being captured, where a staged
+// upload or a grown scratch must not be recorded), nothing enqueued.
+static int measure_pass_lr(cliff_tab *t, const uint32_t *qubits, size_t cnt, uint64_t seed, uint64_t circuit,
+                           uint64_t shot0, uint64_t m0, bool noalloc, bool *done) {
+  cliff_ctx *c = t->ctx;
+  *done = false;
+  const size_t need = lr_scratch_bytes(t->d, uint32_t(c->num_cus)), qbytes = align256(cnt * 4);
+  const uint32_t *dq = nullptr;
+  uint8_t *base = nullptr;
+  if (noalloc) {
+    uint8_t *sp = noalloc_ptr(c->device);
+    if (!sp || qbytes + need > CLIFF_NOALLOC_SCRATCH_BYTES) return CLIFF_OK;
+    HIP_TRY(launch_store_words(reinterpret_cast<uint32_t *>(sp), qubits, uint32_t(cnt), c->stream));
+    dq = reinterpret_cast<uint32_t *>(sp);
+    base = sp + qbytes;
+  } else {
+    if (c->stream) {
+      hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return CLIFF_OK;
+      }
+    }
+    int rc = ctx_persist_scratch(c, need, &base);
+    if (rc == CLIFF_ENOMEM) return CLIFF_OK;
+    if (rc) return rc;
+    rc = upload_stream(c, nullptr, 0, qubits, cnt, nullptr, &dq);
+    if (rc) return rc;
+  }
+  LrDev s;
+  (void)lr_scratch_bind(t->d, uint32_t(c->num_cus), base, s);
+  *done = true;
+  HIP_TRY(launch_measure_lr(t->dev, s, dq, uint32_t(cnt), seed, circuit, shot0, m0, c->num_cus, c->stream,
+                            &c->prof));
+  return CLIFF_OK;
+}
+
 // `noalloc`: the chunk scratch and qubit list come from the static array and
 // nothing is allocated (cliff_measure_record_noalloc).
 static int measure_pass(cliff_tab *t, const uint32_t *qubits, size_t cnt, uint64_t seed,
-                        uint64_t circuit, uint64_t shot0, uint64_t m0, uint64_t abort_at, bool noalloc) {
+                        uint64_t circuit, uint64_t shot0, uint64_t m0, uint64_t abort_at, bool noalloc, bool first) {
   cliff_ctx *c = t->ctx;
   hipStream_t st = c->stream;
+  if (c->measure_mode == CLIFF_MEASURE_AUTO && (persist_layout(t->d.n) || cnt > kStepList)) {
+    bool done = false;
+    const int rc = measure_pass_lr(t, qubits, cnt, seed, circuit, shot0, m0, noalloc, &done);
+    if (rc || done) return rc;
+  }
+  if (first) {
+    c->prof.begin(PK_OTHER, st);
+    const hipError_t fe = launch_fold_pending(t->dev, st);
+    c->prof.end(PK_OTHER, st);
+    HIP_TRY(fe);
+  }
   uint32_t G, L, CW;
   const bool shape_ok = persist_layout(t->d.n) && persist_shape(t->d.n, uint32_t(c->num_cus), &G, &L, &CW);
   uint32_t bG = 0, bL = 0;
@@ -949,10 +998,6 @@ static int measure_impl(cliff_tab *t, const uint32_t *qubits, size_t k, uint64_t
   for (size_t i = 0; i < k; ++i)
     if (qubits[i] >= n) return fail(CLIFF_EINVAL, "measure: qubit %u >= n = %u", qubits[i], n);
   hipStream_t st = t->ctx->stream;
-  t->ctx->prof.begin(PK_OTHER, st);
-  hipError_t fe = launch_fold_pending(t->dev, st);
-  t->ctx->prof.end(PK_OTHER, st);
-  HIP_TRY(fe);
   std::vector<uint8_t> out_stage, kind_stage;
   // a pending injection counts down over the context's measurements
   const uint64_t inject = t->ctx->inject_abort_at;
@@ -960,7 +1005,7 @@ static int measure_impl(cliff_tab *t, const uint32_t *qubits, size_t k, uint64_t
   for (size_t base = 0; base < k; base += n) {
     const size_t cnt = std::min<size_t>(n, k - base);
     const uint64_t at = (inject != UINT64_MAX && inject >= base && inject - base < cnt) ? inject - base : UINT64_MAX;
-    int rc = measure_pass(t, qubits + base, cnt, seed, circuit, shot0, m0 + base, at, noalloc);
+    int rc = measure_pass(t, qubits + base, cnt, seed, circuit, shot0, m0 + base, at, noalloc, base == 0);
     if (rc) return rc;
     if (dr && dr->rec) {
       t->ctx->prof.begin(PK_OTHER, st);

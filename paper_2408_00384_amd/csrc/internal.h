@@ -294,6 +294,45 @@ inline BlkDev blk_scratch_bind(const Dims &d, uint32_t kc, uint32_t G, uint8_t *
   return s;
 }
 
+// Low-rank pass (measure_lowrank.hip): blocks of kLrK measurements, two
+// launches per block, for any number of qubits.
+constexpr uint32_t kLrK = 64;
+// Above n = 10,240 the automatic mode measures lists of up to this many
+// qubits with one kernel per measurement, where callers' kernel timings count
+// one sweep launch per measurement.  It is the slower way (after 6 layers:
+// 32 qubits 0.48 ms against 33 in 0.18 ms at n = 10,300, 1.13 against 0.65 ms
+// at n = 25,000), so longer lists do not take it.
+constexpr uint32_t kStepList = 32;
+struct LrPlan {            // one block's plan
+  uint64_t rand;           // bit t: measurement t of the block is random
+  uint64_t RX[kLrK];       // pivot row t's bits of the block's columns at its step, less bit t
+  uint64_t RQ[kLrK];       // replaced row p_t - n's bits of U
+  uint32_t P[kLrK];        // pivot rows (kNone: deterministic)
+};
+struct LrDev {
+  LrPlan *plan;            // [4] by block mod 4
+  uint64_t *Bt;            // [64 W] row form: a row's bits of the next block's columns
+  uint64_t *U[2];          // [W][kLrK] by block mod 2
+  uint64_t *BX, *BZ;       // [n] x and z of the column at the block's pivot rows
+  uint32_t *ME;            // [n] 1 + its random measurement in the block, or 0
+  uint64_t *Gp, *G;        // pivot rows' Gram rows: per workgroup [nC][kLrK], summed
+  uint32_t *Yp, *Y;        // their Y counts: per workgroup, summed mod 4
+  uint64_t *part;          // [column group][3][Wp]: (Y_old - Y_new) mod 4 (two planes), z.x parity
+  uint64_t *H, *KW, *CW;   // [Wp] sign flips, pivot and replaced rows, pivot rows
+  uint64_t *RP, *OB;       // [S] pivot rows' signs before the block, outcome bits
+  uint32_t *list;          // [n] columns with x bits in stabilizer rows
+  uint32_t *dets;          // [n] deterministic measurements
+  uint32_t *cnt;           // [2] deterministic measurements, entries of list
+};
+size_t lr_scratch_bytes(const Dims &d, uint32_t num_cus);
+// Points s into `base` (256-byte aligned); returns the bytes used.
+size_t lr_scratch_bind(const Dims &d, uint32_t num_cus, uint8_t *base, LrDev &s);
+// k <= n measurements; pending gate signs are folded in.  Kernel launches on
+// `st` only.
+hipError_t launch_measure_lr(const TabDev &t, const LrDev &s, const uint32_t *dev_qubits, uint32_t k, uint64_t seed,
+                             uint64_t circuit, uint64_t shot0, uint64_t m0, int num_cus, hipStream_t st,
+                             Profiler *prof);
+
 
 // ---- launchers (each defined in the .hip file holding its kernels) ----------
 hipError_t launch_init_zero(const TabDev &t, hipStream_t st);

@@ -1,0 +1,1039 @@
+// Z-measurement of a list of qubits in blocks of 64, each block one low-rank
+// update of the tableau in memory; kernel boundaries are the only grid-wide
+// sync (two launches per block, no waiting between workgroups).
+//
+// Method: paper Sec. 2 (Aaronson & Gottesman 2004 tableau rules); outcomes,
+// tableau bits and signs are those of the step-by-step rule.
+//
+//  * A random measurement of qubit a with pivot p (smallest stabilizer row
+//    with x = 1 on column a) multiplies every other row with x = 1 on column
+//    a by row p, copies row p into row p - n and sets row p to +-Z_a.  On the
+//    bits of a column this is one linear map of the rows, the same for every
+//    column.  Over a block with pivots p_0, p_1, .. every row i that is not
+//    a pivot row ends as
+//        new_i = [i not replaced] old_i  XOR  sum_t U[i][t] old_{p_t}
+//    (old: at the block's start; the replaced rows are p_t - n), and p_t ends
+//    as Z_{a_t}.  So every column takes x ^= sum over t with x[p_t] = 1 of
+//    U_t, and the same for z.
+//  * The bits of the block's own columns, row by row (64 bits a row, "row
+//    form"), determine everything: step t finds the smallest stabilizer row
+//    with bit t, and every row with bit t XORs that row's bits into its own.
+//    Only the few smallest rows have to be followed step by step to find the
+//    pivots (the planner); every other row replays the steps on its own.
+//  * A measurement without a pivot is deterministic and changes nothing.
+//    Z_a is then in the stabilizer group, and measurements of other Z's leave
+//    it there with its sign, so the outcome is read from the tableau at the
+//    end of the pass: the sign of the product of the stabilizers n + i with
+//    x_ia = 1.
+//  * Signs.  Every product formed is of commuting Pauli rows, so a final row
+//    is the product of its factors (old_i if kept, and the pivot rows in
+//    U[i]) in any order, with sign
+//        sum of the factors' signs + (sum of the factors' Y counts
+//        - Y count of the result) / 2 + sum over factor pairs a < b of
+//        z(a).x(b)   (mod 2).
+//    With old_i first the pair sum is z(old_i).(x_new_i ^ x_old_i), summed in
+//    the sweep, plus the pivot rows' Gram matrix z(p_a).x(p_b) over the pairs
+//    in U[i].
+//
+// Launches for block b (b = -1 starts the pipeline, b = nb ends it):
+//   k_lr_prep   rows:    U of block b from the plan and the row form; the next
+//                        block's row form, brought past block b
+//               columns: x and z of every column at the pivot rows; the
+//                        pivots' Y counts and Gram rows
+//               signs:   block b - 1's sign flips H per row word; per shot its
+//                        pivots' signs and the outcome bits
+//   k_lr_sweep  planner (one workgroup) of block b + 1; the sweep of block b
+//               over all columns; the signs of block b - 1 for every shot
+// and k_lr_det_terms, k_lr_det, the deterministic outcomes, at the end of the pass.
+//
+// Bound: the sweep reads and writes the tableau once per 64 measurements and
+// does 2 x 64 masked XORs per word (51 us a launch at n = 10,000: the XORs);
+// small tableaux are bound by the launches and the planner's chain of 64
+// steps (19 us a sweep launch at n = 1,024, 12 us of it the chain).  Against
+// one rowsum sweep per measurement (register-resident up to n = 10,240, one
+// kernel per measurement above), circuit and measure-all: n = 64, 16 shots
+// 0.172 against 0.387 ms; n = 1,024, 128 shots 0.96 against 2.68 ms; n = 3,001
+// after 2 layers, a third of the outcomes deterministic, 1.44 against 7.26 ms;
+// n = 10,000 10.4 against 16.4 ms (blocks of 32 in registers); 128 of n = 25,000
+// 3.16 against 12.2 ms.  Blocks of 64: twice the work per launch of 32 at the
+// same number of tableau passes, and a row's bits are one 64-bit word.
+#include <algorithm>
+
+#include "internal.h"
+#include "philox.h"
+
+namespace cliff {
+
+namespace {
+
+constexpr uint32_t kK = kLrK;              // measurements per block
+constexpr uint32_t kPrepThreads = 256;
+constexpr uint32_t kSweepThreads = 1024;
+constexpr uint32_t kSweepWaves = kSweepThreads / 64;
+constexpr uint32_t kPrepCols = 16;         // columns per wave of the prep kernel
+constexpr uint32_t kWindow = 512;          // rows the planner can follow step by step
+constexpr uint32_t kStride = 65;           // LDS row stride of a U tile (words; odd: no bank conflicts)
+
+__device__ __forceinline__ uint64_t lbit(uint32_t b) { return 1ull << (b & 63); }
+__device__ __forceinline__ uint64_t pair64(uint32_t lo, uint32_t hi) { return (uint64_t(hi) << 32) | lo; }
+__device__ __forceinline__ uint32_t rdlane(uint32_t v, uint32_t l) {
+  return uint32_t(__builtin_amdgcn_readlane(int(v), int(l)));
+}
+__device__ __forceinline__ uint64_t rdlane64(uint64_t v, uint32_t l) {
+  return pair64(rdlane(uint32_t(v), l), rdlane(uint32_t(v >> 32), l));
+}
+
+template <uint32_t J>
+__device__ __forceinline__ uint32_t swz_xor(uint32_t v) {
+  return uint32_t(__builtin_amdgcn_ds_swizzle(int(v), int((J << 10) | 0x1f)));
+}
+template <uint32_t J>
+__device__ __forceinline__ uint32_t transpose_step(uint32_t v, uint32_t lane) {
+  constexpr uint32_t m = J == 16 ? 0x0000ffffu : J == 8 ? 0x00ff00ffu : J == 4 ? 0x0f0f0f0fu
+                       : J == 2 ? 0x33333333u : 0x55555555u;
+  const uint32_t y = swz_xor<J>(v);
+  return (lane & J) ? ((v & ~m) | ((y & ~m) >> J)) : ((v & m) | ((y & m) << J));
+}
+// 64 x 64 bit transpose across a wave: bit j of lane i <-> bit i of lane j.
+__device__ __forceinline__ uint64_t transpose64(uint64_t v, uint32_t lane) {
+  uint32_t lo = uint32_t(v), hi = uint32_t(v >> 32);
+  const uint32_t give = lane < 32 ? hi : lo;
+  const uint32_t got = uint32_t(__shfl_xor(int(give), 32));
+  if (lane < 32) hi = got;
+  else lo = got;
+  lo = transpose_step<16>(lo, lane); hi = transpose_step<16>(hi, lane);
+  lo = transpose_step<8>(lo, lane);  hi = transpose_step<8>(hi, lane);
+  lo = transpose_step<4>(lo, lane);  hi = transpose_step<4>(hi, lane);
+  lo = transpose_step<2>(lo, lane);  hi = transpose_step<2>(hi, lane);
+  lo = transpose_step<1>(lo, lane);  hi = transpose_step<1>(hi, lane);
+  return pair64(lo, hi);
+}
+
+// a ^= v where bit `on` (0 or 1) is set
+__device__ __forceinline__ uint64_t xor_if(uint64_t a, uint64_t v, uint32_t mask) {
+  return pair64(bop3<LUT_AND_XOR>(uint32_t(v), mask, uint32_t(a)),
+                bop3<LUT_AND_XOR>(uint32_t(v >> 32), mask, uint32_t(a >> 32)));
+}
+__device__ __forceinline__ uint32_t bit_mask(uint64_t v, uint32_t t) {   // all ones where bit t of v is set
+  return 0u - (uint32_t(v >> t) & 1u);
+}
+
+}  // namespace
+
+struct LrArgs {
+  const uint32_t *q;      // device: the pass's measured qubits
+  uint32_t k, b;          // measurements of the pass; block (int32: -1 .. nb)
+  uint32_t nR, nC, nH, nS, nF;   // prep: workgroups per part
+  uint32_t CG, T;         // sweep: column groups, row tiles
+  uint32_t nA;            // sweep: sign workgroups
+  uint64_t seed, circuit, shot0, m0;
+};
+
+// ------------------------------------------------------------------ prep ---
+// One wave per 64 rows: lane = row.
+__device__ __forceinline__ void prep_rows(const TabDev &t, const LrDev &s, const LrArgs &a, uint32_t wg,
+                                          uint64_t *sV, uint32_t *sP, uint32_t *spec) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int32_t b = int32_t(a.b);
+  const bool cur = b >= 0;                                   // block b has a plan
+  const uint32_t base = uint32_t(b + 1) * kK;                // the next block's first measurement
+  const uint32_t kn = base < a.k ? min(kK, a.k - base) : 0u;
+  if (!cur && kn == 0) return;
+  const uint32_t row0 = wg * kPrepThreads, w = wg * 4 + wave;
+  const bool have = w < t.W;
+  const LrPlan *pl = s.plan + (uint32_t(b) & 3u);
+  const uint32_t myq = lane < kn ? a.q[base + lane] : 0u;
+  // this wave's word of the next block's columns (lane j: column j)
+  uint64_t nw = lane < kn && have ? t.X[size_t(myq) * t.Wp + w] : 0ull;
+  uint64_t e = cur && have ? s.Bt[size_t(w) * 64 + lane] : 0ull;
+  spec[tid] = 0;
+  if (cur && tid < kK) sP[tid] = pl->P[tid];
+  const uint64_t rx = cur ? pl->RX[lane] : 0ull, rand = cur ? pl->rand : 0ull;
+  __syncthreads();
+  if (cur && kn) {
+    // V_t: the next block's columns at pivot row t, as they stand before block b
+    uint32_t p[16];
+    uint64_t xv[16];
+#pragma unroll
+    for (uint32_t i = 0; i < 16; ++i) {
+      p[i] = __builtin_amdgcn_readfirstlane(sP[wave * 16 + i]);
+      const bool ok = p[i] != kNone && lane < kn;
+      xv[i] = t.X[ok ? size_t(myq) * t.Wp + (p[i] >> 6) : 0];
+      if (!ok) xv[i] = 0;
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < 16; ++i) {
+      const uint64_t v = __ballot((xv[i] >> (p[i] & 63)) & 1u);
+      if (lane == 0) sV[wave * 16 + i] = v;
+    }
+  }
+  if (cur && tid < kK && sP[tid] != kNone) {
+    const uint32_t r = sP[tid] - row0, r2 = sP[tid] - t.n - row0;
+    if (r < kPrepThreads) spec[r] = 255;          // pivot row
+    if (r2 < kPrepThreads) spec[r2] = tid + 1;    // replaced row
+  }
+  __syncthreads();
+  if (!have) return;
+  uint64_t v = transpose64(nw, lane);
+  if (cur) {
+    // the row replays the block's steps: after step t bit t holds U[row][t]
+#pragma unroll
+    for (uint32_t i = 0; i < kK; ++i) e = xor_if(e, rdlane64(rx, i), bit_mask(e, i));
+    uint64_t u = e & rand;
+    const uint32_t sp = spec[tid];
+    if (sp) {
+      u = sp == 255 ? 0ull : pl->RQ[sp - 1] & rand;
+      v = 0;
+    }
+    if (kn) {
+      const uint64_t vt = sV[lane];
+#pragma unroll
+      for (uint32_t i = 0; i < kK; ++i) v = xor_if(v, rdlane64(vt, i), bit_mask(u, i));
+    }
+    s.U[(uint32_t(b) & 1u)][size_t(w) * kK + lane] = transpose64(u, lane);
+  }
+  if (kn) s.Bt[size_t(w) * 64 + lane] = v;
+}
+
+// One wave per column at a time: lane = pivot.
+__device__ __forceinline__ void prep_cols(const TabDev &t, const LrDev &s, const LrArgs &a, uint32_t wg,
+                                          unsigned long long *sG, uint32_t *sY) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const LrPlan *pl = s.plan + (a.b & 3u);
+  const uint64_t rand = pl->rand;
+  if (rand == 0) return;
+  const uint32_t p = pl->P[lane], base = a.b * kK, n = t.n;
+  const bool mine = (rand >> lane) & 1u;
+  const uint32_t wp = mine ? p >> 6 : 0u, sh = p & 63;
+  const uint64_t ru = mine ? pl->RX[lane] & rand & (lbit(lane) - 1) : 0ull;   // pivots row p absorbed before its step
+  const uint32_t q = mine ? a.q[base + lane] : kNone;
+  if (tid < kK) {
+    sG[tid] = 0;
+    sY[tid] = 0;
+  }
+  __syncthreads();
+  uint64_t g = 0;
+  uint32_t y = 0;
+  unsigned long long sup = 0;
+  const uint32_t wv = wg * 4 + wave, nwv = a.nC * 4;
+  constexpr uint32_t B = 8;   // columns in flight
+  for (uint32_t c0 = wv; c0 < n; c0 += nwv * B) {
+    uint64_t xw[B], zw[B];
+#pragma unroll
+    for (uint32_t i = 0; i < B; ++i) {
+      const uint32_t c = c0 + i * nwv;
+      const size_t at = c < n ? size_t(c) * t.Wp + wp : 0;
+      xw[i] = t.X[at];
+      zw[i] = t.Z[at];
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < B; ++i) {
+      const uint32_t c = c0 + i * nwv;
+      if (c >= n) break;
+      const uint32_t xb = mine ? uint32_t(xw[i] >> sh) & 1u : 0u, zb = mine ? uint32_t(zw[i] >> sh) & 1u : 0u;
+      const uint64_t bx = __ballot(xb), bz = __ballot(zb), me = __ballot(q == c);
+      if (lane == 0) {
+        s.BX[c] = bx;
+        s.BZ[c] = bz;
+        s.ME[c] = me ? uint32_t(__builtin_ctzll(me)) + 1u : 0u;
+      }
+      g = xor_if(g, bx, 0u - zb);
+      y += xb & zb;
+      // the pivot row at its step: row p plus the pivots it had absorbed
+      const uint32_t xs = (xb ^ uint32_t(__popcll(bx & ru))) & 1u, zs = (zb ^ uint32_t(__popcll(bz & ru))) & 1u;
+      if (mine) sup += 2 * (xs | zs) + xs + zs;
+    }
+  }
+  atomicXor(&sG[lane], (unsigned long long)g);
+  atomicAdd(&sY[lane], y);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) sup += __shfl_xor(sup, off);
+  if (lane == 0 && sup) atomicAdd(reinterpret_cast<unsigned long long *>(t.state + ST_SUPPORT), sup);
+  __syncthreads();
+  if (tid < kK) {
+    s.Gp[size_t(wg) * kK + tid] = sG[tid];
+    s.Yp[size_t(wg) * kK + tid] = sY[tid];
+  }
+}
+
+// Sign flips of block b - 1 per row word: 16 lanes a word, each a share of
+// the column groups' partials and of the pivots.
+__device__ __forceinline__ void prep_flips(const TabDev &t, const LrDev &s, const LrArgs &a, uint32_t wg,
+                                           uint64_t *sU, unsigned long long *sKill, unsigned long long *sCons) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t bp = a.b - 1;
+  const LrPlan *pl = s.plan + (bp & 3u);
+  if (pl->rand == 0) return;
+  const uint32_t w0 = wg * 16, wl = wave * 4 + (lane >> 4), w = w0 + wl, sl = lane & 15;
+  const bool have = w < t.W;
+  if (tid < 16) {
+    sKill[tid] = 0;
+    sCons[tid] = 0;
+  }
+  const uint64_t *U = s.U[bp & 1u] + size_t(have ? w : 0) * kK;
+  uint64_t u[4];
+#pragma unroll
+  for (uint32_t i = 0; i < 4; ++i) {
+    u[i] = have ? U[sl * 4 + i] : 0ull;
+    sU[wl * kK + sl * 4 + i] = u[i];
+  }
+  __syncthreads();
+  if (tid < kK && pl->P[tid] != kNone) {
+    const uint32_t p = pl->P[tid], r = (p >> 6) - w0, r2 = ((p - t.n) >> 6) - w0;
+    if (r < 16) {
+      atomicOr(&sCons[r], (unsigned long long)lbit(p));
+      atomicOr(&sKill[r], (unsigned long long)lbit(p));
+    }
+    if (r2 < 16) atomicOr(&sKill[r2], (unsigned long long)lbit(p - t.n));
+  }
+  uint64_t c0 = 0, c1 = 0, x = 0;   // (Y_old - Y_new) mod 4 in two planes; flips
+  if (have) {
+#pragma unroll 4
+    for (uint32_t cg = sl; cg < a.CG; cg += 16) {
+      const uint64_t *part = s.part + size_t(cg) * 3 * t.Wp + w;
+      const uint64_t v0 = part[0], v1 = part[t.Wp], v2 = part[2 * size_t(t.Wp)];
+      c1 ^= v1 ^ (c0 & v0);
+      c0 ^= v0;
+      x ^= v2;
+    }
+  }
+  uint64_t gr[4], acc[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (uint32_t i = 0; i < 4; ++i) {
+    const uint32_t ia = sl * 4 + i, yc = s.Y[ia];
+    const uint64_t uy = (yc & 1u) ? u[i] : 0ull;   // the absorbed pivots' Y counts
+    c1 ^= c0 & uy;
+    c0 ^= uy;
+    if (yc & 2u) c1 ^= u[i];
+    gr[i] = s.G[ia] & ~(lbit(ia) | (lbit(ia) - 1));   // pairs (ia, ib > ia)
+  }
+#pragma unroll 8
+  for (uint32_t ib = 0; ib < kK; ++ib) {
+    const uint64_t ub = sU[wl * kK + ib];
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) acc[i] = xor_if(acc[i], ub, bit_mask(gr[i], ib));
+  }
+#pragma unroll
+  for (uint32_t i = 0; i < 4; ++i) x ^= u[i] & acc[i];
+#pragma unroll
+  for (int off = 1; off < 16; off <<= 1) {
+    const uint64_t b0 = __shfl_xor(c0, off), b1 = __shfl_xor(c1, off);
+    c1 ^= b1 ^ (c0 & b0);
+    c0 ^= b0;
+    x ^= __shfl_xor(x, off);
+  }
+  __syncthreads();
+  if (have && sl == 0) {
+    const uint64_t cons = sCons[wl], odd = c0 & ~cons;
+    if (odd) atomicAdd(&t.state[ST_ANOMALY], uint32_t(__popcll(odd)));
+    s.H[w] = (c1 ^ x) & ~cons;
+    s.KW[w] = sKill[wl];
+    s.CW[w] = cons;
+  }
+}
+
+// Block b - 1, one wave per shot: lane = pivot.  Its sign before the block,
+// and the outcome bit.
+__device__ __forceinline__ void prep_shots(const TabDev &t, const LrDev &s, const LrArgs &a, uint32_t wg) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t bp = a.b - 1, S = t.S;
+  const LrPlan *pl = s.plan + (bp & 3u);
+  const uint64_t rand = pl->rand;
+  if (rand == 0) return;
+  const bool mine = (rand >> lane) & 1u;
+  const uint32_t p = mine ? pl->P[lane] : 0u;
+  const size_t slot = size_t(bp) * kK + lane;
+  for (uint32_t sh = wg * 4 + wave; sh < S; sh += a.nS * 4) {
+    const uint64_t r = t.R[size_t(p >> 6) * S + sh];
+    uint32_t o = 0;
+    if (mine) {
+      o = outcome_bit(a.seed, a.circuit, a.shot0 + sh, a.m0 + slot);
+      t.out[slot * S + sh] = uint8_t(o);
+    }
+    const uint64_t rp = __ballot(mine && ((r >> (p & 63)) & 1u)), ob = __ballot(o != 0);
+    if (lane == 0) {
+      s.RP[sh] = rp;
+      s.OB[sh] = ob;
+    }
+  }
+}
+
+__global__ void __launch_bounds__(kPrepThreads) k_lr_prep(TabDev t, LrDev s, LrArgs a) {
+  __shared__ uint64_t s_mem[16 * kK + 64];
+  __shared__ uint32_t s_a[kPrepThreads], s_b[kK];
+  uint32_t wg = blockIdx.x;
+  if (wg < a.nR) return prep_rows(t, s, a, wg, s_mem, s_b, s_a);
+  wg -= a.nR;
+  if (wg < a.nC) return prep_cols(t, s, a, wg, reinterpret_cast<unsigned long long *>(s_mem), s_b);
+  wg -= a.nC;
+  if (wg < a.nH) {
+    unsigned long long *m = reinterpret_cast<unsigned long long *>(s_mem) + 16 * kK;
+    return prep_flips(t, s, a, wg, s_mem, m, m + 16);
+  }
+  wg -= a.nH;
+  if (wg < a.nS) return prep_shots(t, s, a, wg);
+  wg -= a.nS;
+  // start of the pass: pending gate signs into every shot's signs (the sweep
+  // launch after this one clears them), the pass's counters
+  const size_t nr = size_t(t.Wp) * t.S;
+  for (size_t i = size_t(wg) * blockDim.x + threadIdx.x; i < nr; i += size_t(a.nF) * blockDim.x) {
+    const uint64_t p = t.P[i / t.S];
+    if (p) t.R[i] ^= p;
+  }
+  for (size_t i = size_t(wg) * blockDim.x + threadIdx.x; i < a.k; i += size_t(a.nF) * blockDim.x)
+    t.detpar[i] = t.detY[i] = 0;
+  if (wg == 0 && threadIdx.x < 2) s.cnt[threadIdx.x] = 0;
+}
+
+// --------------------------------------------------------------- planner ---
+// One workgroup finds block b + 1's pivots from the row form of the
+// stabilizer rows.  Wave 0 follows the smallest rows that have a bit at all
+// (128 of them, or all when there are at most 512) step by step, a row a
+// lane: a ballot finds the pivot, a lane read gives its bits.  The other rows
+// are needed only when none of those has the step's bit and there are more
+// rows: then every wave replays the steps so far on its rows (in registers,
+// from where its last search left them) and searches them.
+struct PlanShared {
+  uint64_t we[kWindow], rx[kK], sv[kSweepWaves];
+  uint32_t wi[kWindow], cnt[kSweepWaves], sr[kSweepWaves], cmd;
+};
+
+template <int RW>
+struct PlanRows {
+  uint64_t e[RW > 0 ? RW : 1];
+  uint32_t done;   // steps already replayed
+  uint32_t i0, i1; // this wave's stabilizer words
+};
+
+__device__ __forceinline__ uint64_t plan_load(const TabDev &t, const LrDev &s, uint32_t i, uint32_t lane) {
+  const uint32_t w = (t.n >> 6) + i;
+  const uint64_t v = s.Bt[size_t(w) * 64 + lane];
+  return (w * 64 + lane >= t.n) ? v : 0ull;   // the first word may hold destabilizer rows too
+}
+
+// Smallest row of this wave with bit tt after steps 0 .. tt - 1, into sr / sv.
+template <int RW>
+__device__ __forceinline__ void plan_search(const TabDev &t, const LrDev &s, PlanRows<RW> &r, PlanShared &sh,
+                                            uint32_t tt, uint32_t wave, uint32_t lane) {
+  uint32_t row = kNone;
+  uint64_t val = 0;
+  if constexpr (RW > 0) {
+    for (uint32_t d = r.done; d < tt; ++d) {
+      const uint64_t rx = rdlane64(sh.rx[d], 0);
+      if (rx == 0) continue;
+#pragma unroll
+      for (int k = 0; k < RW; ++k) r.e[k] = xor_if(r.e[k], rx, bit_mask(r.e[k], d));
+    }
+    r.done = tt;
+#pragma unroll
+    for (int k = 0; k < RW; ++k) {
+      const uint64_t bal = __ballot((r.e[k] >> tt) & 1u);
+      if (bal && row == kNone) {
+        const uint32_t l = uint32_t(__builtin_ctzll(bal));
+        row = ((t.n >> 6) + r.i0 + k) * 64 + l;
+        val = rdlane64(r.e[k], l);
+      }
+    }
+  } else {
+    for (uint32_t i = r.i0; i < r.i1 && row == kNone; ++i) {
+      uint64_t e = plan_load(t, s, i, lane);
+      for (uint32_t d = 0; d < tt; ++d) e = xor_if(e, rdlane64(sh.rx[d], 0), bit_mask(e, d));
+      const uint64_t bal = __ballot((e >> tt) & 1u);
+      if (bal) {
+        const uint32_t l = uint32_t(__builtin_ctzll(bal));
+        row = ((t.n >> 6) + i) * 64 + l;
+        val = rdlane64(e, l);
+      }
+    }
+  }
+  if (lane == 0) {
+    sh.sr[wave] = row;
+    sh.sv[wave] = val;
+  }
+}
+
+// The steps, by wave 0 (lane t ends with step t's results).
+template <int RW, int R>
+__device__ __forceinline__ void plan_steps(const TabDev &t, const LrDev &s, PlanRows<RW> &r, PlanShared &sh,
+                                           uint32_t kb, uint32_t total, uint32_t lane, uint32_t &P, uint64_t &RX,
+                                           uint64_t &RQ) {
+  uint64_t e[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) e[i] = uint32_t(i) * 64 + lane < total ? sh.we[i * 64 + lane] : 0ull;
+  const bool complete = total <= uint32_t(R) * 64;
+  P = kNone;
+  RX = RQ = 0;
+  for (uint32_t tt = 0; tt < kb; ++tt) {
+    uint64_t rb = 0;
+    uint32_t row = kNone;   // window position, or row | 1 << 31
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const uint64_t bal = __ballot((e[i] >> tt) & 1u);
+      if (row == kNone && bal) {
+        const uint32_t l = uint32_t(__builtin_ctzll(bal));
+        row = uint32_t(i) * 64 + l;
+        rb = rdlane64(e[i], l);
+      }
+    }
+    if (row == kNone && !complete) {
+      sh.rx[lane] = RX;
+      if (lane == 0) sh.cmd = tt + 1;
+      __syncthreads();
+      plan_search<RW>(t, s, r, sh, tt, 0, lane);
+      __syncthreads();
+      const uint32_t cr = lane < kSweepWaves ? sh.sr[lane] : kNone;
+      const uint64_t cv = lane < kSweepWaves ? sh.sv[lane] : 0ull;
+      const uint64_t bal = __ballot(cr != kNone);   // waves hold ascending rows
+      if (bal) {
+        const uint32_t l = uint32_t(__builtin_ctzll(bal));
+        row = rdlane(cr, l) | 0x80000000u;
+        rb = rdlane64(cv, l);
+      }
+    }
+    if (row == kNone) continue;   // deterministic
+    const uint64_t rx = rb & ~lbit(tt);
+#pragma unroll
+    for (int i = 0; i < R; ++i) e[i] = xor_if(e[i], rx, bit_mask(e[i], tt));
+    // replaced row p - n: the pivot row's bits, then as any row
+    if (lane < tt) RQ = xor_if(RQ, rx, bit_mask(RQ, tt));
+    if (lane == tt) {
+      RQ = rb;
+      RX = rx;
+      P = row;
+    }
+  }
+  if (P != kNone) P = (P & 0x80000000u) ? P & 0x7fffffffu : sh.wi[P];
+}
+
+template <int RW>
+__device__ __forceinline__ void plan_block(const TabDev &t, const LrDev &s, const LrArgs &a, PlanShared &sh) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t bn = a.b + 1, base = bn * kK, kb = min(kK, a.k - base);
+  const uint32_t nsw = t.W - (t.n >> 6), per = (nsw + kSweepWaves - 1) / kSweepWaves;
+  PlanRows<RW> r;
+  r.done = 0;
+  r.i0 = min(nsw, wave * per);
+  r.i1 = min(nsw, r.i0 + per);
+  uint32_t mycnt = 0;
+  if constexpr (RW > 0) {
+#pragma unroll
+    for (int k = 0; k < RW; ++k) r.e[k] = r.i0 + k < r.i1 ? plan_load(t, s, r.i0 + k, lane) : 0ull;
+#pragma unroll
+    for (int k = 0; k < RW; ++k) mycnt += uint32_t(__popcll(__ballot(r.e[k] != 0)));
+  } else {
+    for (uint32_t i = r.i0; i < r.i1; ++i) mycnt += uint32_t(__popcll(__ballot(plan_load(t, s, i, lane) != 0)));
+  }
+  if (lane == 0) sh.cnt[wave] = mycnt;
+  if (tid == 0) sh.cmd = 0;
+  __syncthreads();
+  uint32_t at = 0, total = 0;
+  for (uint32_t v = 0; v < kSweepWaves; ++v) {
+    if (v < wave) at += sh.cnt[v];
+    total += sh.cnt[v];
+  }
+  at = __builtin_amdgcn_readfirstlane(at);
+  total = __builtin_amdgcn_readfirstlane(total);
+  // the first rows with a bit, in order
+  auto fill = [&](uint64_t e, uint32_t i) {
+    const uint64_t bal = __ballot(e != 0);
+    const uint32_t pos = at + uint32_t(__popcll(bal & (lbit(lane) - 1)));
+    if (e != 0 && pos < kWindow) {
+      sh.we[pos] = e;
+      sh.wi[pos] = ((t.n >> 6) + i) * 64 + lane;
+    }
+    at += uint32_t(__popcll(bal));
+  };
+  if constexpr (RW > 0) {
+#pragma unroll
+    for (int k = 0; k < RW; ++k)
+      if (at < kWindow) fill(r.e[k], r.i0 + k);
+  } else {
+    for (uint32_t i = r.i0; i < r.i1 && at < kWindow; ++i) fill(plan_load(t, s, i, lane), i);
+  }
+  __syncthreads();
+  if (wave != 0) {   // searches on request
+    for (;;) {
+      __syncthreads();
+      const uint32_t cmd = __builtin_amdgcn_readfirstlane(sh.cmd);
+      if (cmd == 0) return;
+      plan_search<RW>(t, s, r, sh, cmd - 1, wave, lane);
+      __syncthreads();
+    }
+  }
+  uint32_t P;
+  uint64_t RX, RQ;
+  // (between 129 and 512 rows all of them are followed: none is left to search)
+  if (total > 128 && total <= kWindow) plan_steps<RW, kWindow / 64>(t, s, r, sh, kb, total, lane, P, RX, RQ);
+  else plan_steps<RW, 2>(t, s, r, sh, kb, total, lane, P, RX, RQ);
+  if (lane == 0) sh.cmd = 0;
+  __syncthreads();
+  LrPlan *pl = s.plan + (bn & 3u);
+  const uint64_t rand = __ballot(P != kNone);
+  pl->P[lane] = P;
+  pl->RX[lane] = RX;
+  pl->RQ[lane] = RQ;
+  if (lane < kb) {
+    t.kind[base + lane] = P != kNone ? 1 : 0;
+    if (P == kNone) s.dets[s.cnt[0] + uint32_t(__popcll(~rand & (lbit(lane) - 1)))] = base + lane;
+  }
+  if (lane == 0) {
+    pl->rand = rand;
+    const uint32_t nr = uint32_t(__popcll(rand));
+    if (nr) atomicAdd(&t.state[ST_RANDOM_CNT], nr);
+    if (kb > nr) {
+      atomicAdd(&t.state[ST_DET_CNT], kb - nr);
+      s.cnt[0] += kb - nr;
+    }
+  }
+}
+
+// ----------------------------------------------------------------- sweep ---
+// A workgroup holds 64 units (T: 32 or 64 rows) of U in LDS and updates them
+// in a share of the columns, four columns in flight per wave.  Per step and
+// column the pivot-row bits are wave-uniform masks (a scalar instruction),
+// so the update is one v_bitop3 per 32 rows and plane.
+template <typename T>
+struct Halves;
+template <>
+struct Halves<uint32_t> { static constexpr int N = 1; };
+template <>
+struct Halves<uint64_t> { static constexpr int N = 2; };
+__device__ __forceinline__ uint32_t and_xor(uint32_t v, uint32_t m, uint32_t a) { return bop3<LUT_AND_XOR>(v, m, a); }
+__device__ __forceinline__ uint64_t and_xor(uint64_t v, uint32_t m, uint64_t a) { return xor_if(a, v, m); }
+__device__ __forceinline__ unsigned long long lds_xor_ret(uint64_t *p, uint64_t v) {
+  return atomicXor(reinterpret_cast<unsigned long long *>(p), (unsigned long long)v);
+}
+__device__ __forceinline__ uint32_t lds_xor_ret(uint32_t *p, uint32_t v) { return atomicXor(p, v); }
+
+template <typename T>
+__device__ __forceinline__ void lr_sweep(const TabDev &t, const LrDev &s, const LrArgs &a, uint32_t wg,
+                                         uint64_t *s_u, uint64_t *s_k, uint64_t *s_e, uint32_t *s_flag) {
+  constexpr uint32_t Q = 8 / sizeof(T);               // units per word
+  constexpr uint32_t TW = 64 / Q;                     // words per tile
+  constexpr uint32_t US = Q == 1 ? kStride : 2 * (TW + 1);   // LDS row stride (units)
+  constexpr uint32_t B = 4;                           // columns in flight
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const LrPlan *pl = s.plan + (a.b & 3u);
+  if (pl->rand == 0) return;   // nothing random in this block
+  const uint32_t tile = wg % a.T, cg = wg / a.T, n = t.n, W = t.W;
+  const uint32_t w0 = tile * TW;
+  const T *sU = reinterpret_cast<const T *>(s_u);
+  T *sE = reinterpret_cast<T *>(s_e);
+  if (tid < TW) s_k[tid] = 0;
+  if (tid < 3 * 64) sE[tid] = 0;
+  if (tid == 0) *s_flag = 0;
+  __syncthreads();
+  // U of this tile: [word][step] in memory, [step][word] in LDS
+  const uint64_t *U = s.U[a.b & 1u];
+  uint64_t any = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < TW * kK / kSweepThreads; ++j) {
+    const uint32_t i = tid + j * kSweepThreads, wl = i / kK, st = i % kK;
+    const uint64_t v = w0 + wl < W ? U[size_t(w0 + wl) * kK + st] : 0ull;
+    s_u[st * (US / Q) + wl] = v;
+    any |= v;
+  }
+  if (tid < kK && pl->P[tid] != kNone) {
+    const uint32_t p = pl->P[tid], r = (p >> 6) - w0, r2 = ((p - n) >> 6) - w0;
+    if (r < TW) atomicOr(reinterpret_cast<unsigned long long *>(&s_k[r]), (unsigned long long)lbit(p));
+    if (r2 < TW) atomicOr(reinterpret_cast<unsigned long long *>(&s_k[r2]), (unsigned long long)lbit(p - n));
+    any |= uint64_t(r < TW || r2 < TW);
+  }
+  if (__ballot(any != 0) && lane == 0) *s_flag = 1;
+  __syncthreads();
+  const uint32_t units = W * Q, unit = tile * 64 + lane;
+  const bool live = unit < units;
+  if (*s_flag) {   // (otherwise no row of this tile changes)
+    const T keep = live ? ~reinterpret_cast<const T *>(s_k)[lane] : T(0);
+    const size_t cs = size_t(t.Wp) * Q;
+    T *XT = reinterpret_cast<T *>(t.X), *ZT = reinterpret_cast<T *>(t.Z);
+    const uint32_t c0 = uint32_t(uint64_t(cg) * n / a.CG), c1 = uint32_t(uint64_t(cg + 1) * n / a.CG);
+    T e0 = 0, e1 = 0, zx = 0;
+    for (uint32_t cb = c0 + wave; cb < c1; cb += 64 * kSweepWaves) {
+      // lane i: the pivot-row bits of the wave's i-th column
+      const uint32_t ci = cb + lane * kSweepWaves;
+      const uint64_t bxv = ci < c1 ? s.BX[ci] : 0ull, bzv = ci < c1 ? s.BZ[ci] : 0ull;
+      const uint32_t mev = ci < c1 ? s.ME[ci] : 0u;
+      const uint32_t cnt = min(64u, (c1 - cb + kSweepWaves - 1) / kSweepWaves);
+      T xn[B], zn[B];
+#pragma unroll
+      for (uint32_t i = 0; i < B; ++i) {
+        const bool ok = i < cnt && live;
+        const size_t at = ok ? size_t(cb + i * kSweepWaves) * cs + unit : 0;
+        xn[i] = XT[at];
+        zn[i] = ZT[at];
+      }
+      for (uint32_t j = 0; j < cnt; j += B) {
+        T x[B], z[B], dx[B], dz[B];
+        uint32_t xl[B], xh[B], zl[B], zh[B], me[B], some = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < B; ++i) {
+          const bool ok = j + i < cnt;
+          const uint32_t jl = (j + i) & 63u;
+          xl[i] = ok ? rdlane(uint32_t(bxv), jl) : 0u;
+          xh[i] = ok ? rdlane(uint32_t(bxv >> 32), jl) : 0u;
+          zl[i] = ok ? rdlane(uint32_t(bzv), jl) : 0u;
+          zh[i] = ok ? rdlane(uint32_t(bzv >> 32), jl) : 0u;
+          me[i] = ok ? rdlane(mev, jl) : 0u;
+          some |= xl[i] | xh[i] | zl[i] | zh[i];
+          x[i] = xn[i];
+          z[i] = zn[i];
+          dx[i] = 0;
+          dz[i] = 0;
+        }
+        // the next four columns' loads run under this four's arithmetic
+#pragma unroll
+        for (uint32_t i = 0; i < B; ++i) {
+          const bool ok = j + B + i < cnt && live;
+          const size_t at = ok ? size_t(cb + (j + B + i) * kSweepWaves) * cs + unit : 0;
+          xn[i] = XT[at];
+          zn[i] = ZT[at];
+        }
+        if (some) {
+#pragma unroll 8
+          for (uint32_t st = 0; st < 32; ++st) {
+            const T u = sU[st * US + lane];
+#pragma unroll
+            for (uint32_t i = 0; i < B; ++i) {
+              dx[i] = and_xor(u, 0u - ((xl[i] >> st) & 1u), dx[i]);
+              dz[i] = and_xor(u, 0u - ((zl[i] >> st) & 1u), dz[i]);
+            }
+          }
+#pragma unroll 8
+          for (uint32_t st = 0; st < 32; ++st) {
+            const T u = sU[(32 + st) * US + lane];
+#pragma unroll
+            for (uint32_t i = 0; i < B; ++i) {
+              dx[i] = and_xor(u, 0u - ((xh[i] >> st) & 1u), dx[i]);
+              dz[i] = and_xor(u, 0u - ((zh[i] >> st) & 1u), dz[i]);
+            }
+          }
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < B; ++i) {
+          if (j + i >= cnt) break;   // wave-uniform
+          const T ox = x[i] & keep, oz = z[i] & keep;
+          const T nx = ox ^ dx[i];
+          T nz = oz ^ dz[i];
+          if (me[i]) {   // this column was measured: its pivot row becomes Z on it
+            const uint32_t p = pl->P[me[i] - 1], pu = (p >> 6) * Q + (Q == 2 ? (p >> 5) & 1u : 0u);
+            if (unit == pu) nz |= T(1) << (p & (8 * sizeof(T) - 1));
+          }
+          // (Y_old - Y_new) mod 4 in two planes, and z_old.(x_new ^ x_old)
+          const T yn = nx & nz, anti = (ox & oz) ^ yn;
+          e1 ^= anti & (e0 ^ yn);
+          e0 ^= anti;
+          zx ^= oz & dx[i];
+          const size_t at = size_t(cb + (j + i) * kSweepWaves) * cs + unit;
+          if (live && nx != x[i]) XT[at] = nx;
+          if (live && nz != z[i]) ZT[at] = nz;
+        }
+      }
+    }
+    const T old = lds_xor_ret(&sE[lane], e0);
+    lds_xor_ret(&sE[64 + lane], e1 ^ (old & e0));
+    lds_xor_ret(&sE[128 + lane], zx);
+  }
+  __syncthreads();
+  if (tid < 3 * 64) {
+    const uint32_t pln = tid >> 6, un = tile * 64 + lane;
+    T *part = reinterpret_cast<T *>(s.part + (size_t(cg) * 3 + pln) * t.Wp);
+    if (un < units) part[un] = sE[tid];
+  }
+}
+
+// The signs of block b - 1: r = [kept] r ^ H ^ sum over pivots with r = 1 of
+// U_t, the pivot rows take the outcomes.
+__device__ __forceinline__ void lr_signs(const TabDev &t, const LrDev &s, const LrArgs &a, uint32_t wg, uint32_t *sP) {
+  const uint32_t bp = a.b - 1, S = t.S;
+  const LrPlan *pl = s.plan + (bp & 3u);
+  if (pl->rand == 0) return;
+  if (threadIdx.x < kK) sP[threadIdx.x] = pl->P[threadIdx.x];
+  __syncthreads();
+  const size_t total = size_t(t.W) * S;
+  for (size_t i = size_t(wg) * kSweepThreads + threadIdx.x; i < total; i += size_t(a.nA) * kSweepThreads) {
+    const uint32_t w = uint32_t(i / S), sh = uint32_t(i % S);
+    const uint64_t rp = s.RP[sh], cons = s.CW[w];
+    const ulonglong2 *U = reinterpret_cast<const ulonglong2 *>(s.U[bp & 1u] + size_t(w) * kK);
+    uint64_t v = (t.R[i] & ~s.KW[w]) ^ s.H[w];
+#pragma unroll 8
+    for (uint32_t st = 0; st < kK / 2; ++st) {
+      const ulonglong2 u = U[st];
+      v = xor_if(v, u.x, bit_mask(rp, 2 * st));
+      v = xor_if(v, u.y, bit_mask(rp, 2 * st + 1));
+    }
+    if (cons) {
+      const uint64_t ob = s.OB[sh];
+      for (uint32_t st = 0; st < kK; ++st) {
+        const uint32_t p = sP[st];
+        if (p != kNone && (p >> 6) == w && ((ob >> st) & 1u)) v |= lbit(p);
+      }
+    }
+    t.R[i] = v;
+  }
+}
+
+// Gram rows and Y counts of block b over the prep kernel's workgroups.
+__device__ __forceinline__ void lr_gram(const LrDev &s, const LrArgs &a, uint64_t *sg, uint32_t *sy) {
+  const uint32_t tid = threadIdx.x, st = tid & 63, sl = tid >> 6;
+  if (s.plan[a.b & 3u].rand == 0) return;
+  if (tid < kK) {
+    sg[tid] = 0;
+    sy[tid] = 0;
+  }
+  __syncthreads();
+  uint64_t g = 0;
+  uint32_t y = 0;
+#pragma unroll 4
+  for (uint32_t q = sl; q < a.nC; q += kSweepWaves) {
+    g ^= s.Gp[size_t(q) * kK + st];
+    y += s.Yp[size_t(q) * kK + st];
+  }
+  atomicXor(reinterpret_cast<unsigned long long *>(&sg[st]), (unsigned long long)g);
+  atomicAdd(&sy[st], y);
+  __syncthreads();
+  if (tid < kK) {
+    s.G[tid] = sg[tid];
+    s.Y[tid] = sy[tid] & 3u;
+  }
+}
+
+// Columns with an x bit in a stabilizer row, for the deterministic outcomes.
+__device__ __forceinline__ void lr_columns(const TabDev &t, const LrDev &s, const LrArgs &a, uint32_t wg) {
+  if (s.cnt[0] == 0) return;
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (uint32_t c = wg * kSweepWaves + wave; c < t.n; c += a.CG * kSweepWaves) {
+    uint64_t any = 0;
+    for (uint32_t w = (t.n >> 6) + lane; w < t.W; w += 64) {
+      uint64_t v = t.X[size_t(c) * t.Wp + w];
+      if (w == (t.n >> 6)) v &= ~0ull << (t.n & 63);
+      any |= v;
+    }
+    if (__ballot(any != 0) && lane == 0) s.list[atomicAdd(&s.cnt[1], 1u)] = c;
+  }
+}
+
+template <typename T, int RW>
+__global__ void __launch_bounds__(kSweepThreads) k_lr_sweep(TabDev t, LrDev s, LrArgs a) {
+  __shared__ uint64_t s_mem[kK * kStride];
+  __shared__ uint64_t s_k[64], s_e[3 * 64];
+  __shared__ uint32_t s_flag[kK];
+  static_assert(sizeof(PlanShared) <= sizeof(s_mem), "planner's LDS");
+  const int32_t b = int32_t(a.b), nb = int32_t((a.k + kK - 1) / kK);
+  uint32_t wg = blockIdx.x;
+  if (wg == 0) {
+    if (b + 1 < nb) plan_block<RW>(t, s, a, *reinterpret_cast<PlanShared *>(s_mem));
+    return;
+  }
+  if (wg == 1) {
+    if (b >= 0 && b < nb) return lr_gram(s, a, s_mem, s_flag);
+    if (b < 0)   // the pending signs were folded by the launch before this one
+      for (uint32_t i = threadIdx.x; i < t.Wp; i += kSweepThreads) t.P[i] = 0;
+    return;
+  }
+  wg -= 2;
+  if (wg < a.nA) return lr_signs(t, s, a, wg, s_flag);
+  wg -= a.nA;
+  if (b < nb) lr_sweep<T>(t, s, a, wg, s_mem, s_k, s_e, s_flag);
+  else lr_columns(t, s, a, wg);
+}
+
+// --------------------------------------------------- deterministic outcomes ---
+// Measurement m's product rows in word w: the destabilizer half of its
+// column, shifted up by n rows.
+__device__ __forceinline__ uint64_t det_rows(const TabDev &t, const uint64_t *col, uint32_t w) {
+  const uint32_t w0 = t.n >> 6, sh = t.n & 63, i = w - w0;
+  auto src = [&](uint32_t j) -> uint64_t {
+    if (j >= t.NW) return 0ull;
+    uint64_t v = col[j];
+    if (j == w0 && sh) v &= lbit(sh) - 1;
+    return v;
+  };
+  uint64_t v = src(i) << sh;
+  if (sh && i) v |= src(i - 1) >> (64 - sh);
+  return v;
+}
+
+// The x/z terms of the ordered product of the rows (-1)^r i^(x.z) X^x Z^z: the
+// pairs s < t with z_s x_t, and the Y count.  They come from the columns with
+// x bits in stabilizer rows (none after a measure-all), which the grid's x
+// dimension shares out; its y dimension shares out the measurements.
+__global__ void __launch_bounds__(256) k_lr_det_terms(TabDev t, LrDev s, LrArgs a) {
+  const uint32_t nd = s.cnt[0], ncol = s.cnt[1];
+  const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t w0 = t.n >> 6, W = t.W, wv = blockIdx.x * 4 + wave, nwv = gridDim.x * 4;
+  if (ncol == 0 || wv >= ncol) return;
+  for (uint32_t d = blockIdx.y; d < nd; d += gridDim.y) {
+    const uint32_t m = s.dets[d];
+    const uint64_t *col = t.X + size_t(a.q[m]) * t.Wp;
+    uint32_t y = 0, par = 0;
+    for (uint32_t ic = wv; ic < ncol; ic += nwv) {
+      const size_t at = size_t(s.list[ic]) * t.Wp;
+      uint32_t carry = 0;   // z parity of the product rows in earlier words
+#pragma unroll 2
+      for (uint32_t wb = w0; wb < W; wb += 64) {
+        const uint32_t w = wb + lane;
+        const uint64_t tm = w < W ? det_rows(t, col, w) : 0ull;
+        const uint64_t xt = tm ? t.X[at + w] & tm : 0ull, zt = tm ? t.Z[at + w] & tm : 0ull;
+        y += uint32_t(__popcll(xt & zt));
+        uint64_t pre = zt << 1;   // exclusive prefix parity inside the word
+        pre ^= pre << 1; pre ^= pre << 2; pre ^= pre << 4;
+        pre ^= pre << 8; pre ^= pre << 16; pre ^= pre << 32;
+        const uint64_t zb = __ballot(__popcll(zt) & 1);
+        const uint32_t cin = (carry ^ uint32_t(__popcll(zb & (lbit(lane) - 1)))) & 1u;
+        par ^= (uint32_t(__popcll(xt & pre)) & 1u) ^ (cin & uint32_t(__popcll(xt)) & 1u);
+        carry ^= uint32_t(__popcll(zb)) & 1u;
+      }
+    }
+    const uint64_t pb = __ballot(par & 1u);
+    for (int off = 32; off > 0; off >>= 1) y += __shfl_xor(y, off);
+    if (lane == 0) {
+      if (y) atomicAdd(&t.detY[m], y);
+      if (__popcll(pb) & 1) atomicXor(&t.detpar[m], 1u);
+    }
+  }
+}
+
+// One workgroup per deterministic measurement (of those it meets at its
+// stride): outcome = XOR of the product rows' signs ^ the x/z terms.
+__global__ void __launch_bounds__(256) k_lr_det(TabDev t, LrDev s, LrArgs a) {
+  __shared__ uint32_t s_out[256];
+  const uint32_t nd = s.cnt[0], tid = threadIdx.x, W = t.W, S = t.S, w0 = t.n >> 6;
+  for (uint32_t d = blockIdx.x; d < nd; d += gridDim.x) {
+    const uint32_t m = s.dets[d];
+    const uint64_t *col = t.X + size_t(a.q[m]) * t.Wp;
+    const uint32_t y = t.detY[m], terms = t.detpar[m] ^ (y >> 1);
+    // 256 threads over the shots, several threads a shot when there are fewer
+    const uint32_t ss = min(S, 256u), per = 256 / ss, my = tid / ss;
+    for (uint32_t s0 = 0; s0 < S; s0 += ss) {
+      const uint32_t si = s0 + tid % ss;
+      s_out[tid] = 0;
+      __syncthreads();
+      if (my < per && si < S) {
+        uint32_t rt = 0;
+        for (uint32_t w = w0 + my; w < W; w += per)
+          rt ^= uint32_t(__popcll(det_rows(t, col, w) & t.R[size_t(w) * S + si])) & 1u;
+        if (rt) atomicXor(&s_out[tid % ss], 1u);
+      }
+      __syncthreads();
+      if (tid < ss && si < S) t.out[size_t(m) * S + si] = uint8_t((s_out[tid] ^ terms) & 1u);
+      __syncthreads();
+    }
+    if (tid == 0 && (y & 1u)) atomicAdd(&t.state[ST_ANOMALY], 1u);   // odd Y count
+  }
+}
+
+// ------------------------------------------------------------------ host ---
+static uint32_t div_up(size_t a, size_t b) { return uint32_t((a + b - 1) / b); }
+
+// Sweep shape: units of 32 rows up to n = 1,024 (a wave then holds a whole
+// column: 64-row words would leave half the lanes idle), 64 above.
+struct LrShape {
+  bool narrow;
+  uint32_t T, CG, nC;
+};
+static LrShape lr_shape(uint32_t n, uint32_t num_cus) {
+  LrShape r;
+  const uint32_t W = (2 * n + 63) / 64;
+  r.narrow = W <= 32;
+  r.T = div_up(W, r.narrow ? 32 : 64);
+  // one workgroup per compute unit, the planner and the sign work aside; at
+  // least two columns per wave
+  const uint32_t wgs = num_cus > 16 ? num_cus - 6 : num_cus;
+  uint32_t cg = wgs / r.T;
+  const uint32_t most = div_up(n, 2 * kSweepWaves);
+  if (cg > most) cg = most;
+  r.CG = cg < 1 ? 1 : cg;
+  r.nC = div_up(n, 4 * kPrepCols);
+  if (r.nC > 512) r.nC = 512;
+  return r;
+}
+
+size_t lr_scratch_bytes(const Dims &d, uint32_t num_cus) {
+  LrDev s;
+  return lr_scratch_bind(d, num_cus, nullptr, s);
+}
+
+size_t lr_scratch_bind(const Dims &d, uint32_t num_cus, uint8_t *base, LrDev &s) {
+  const LrShape h = lr_shape(d.n, num_cus);
+  size_t cur = 0;
+  auto take = [&](size_t bytes) {
+    uint8_t *at = base + cur;
+    cur = align256(cur + bytes);
+    return at;
+  };
+  s.plan = reinterpret_cast<LrPlan *>(take(4 * sizeof(LrPlan)));
+  s.Bt = reinterpret_cast<uint64_t *>(take(size_t(d.W) * 64 * 8));
+  s.U[0] = reinterpret_cast<uint64_t *>(take(size_t(d.W) * kK * 8));
+  s.U[1] = reinterpret_cast<uint64_t *>(take(size_t(d.W) * kK * 8));
+  s.BX = reinterpret_cast<uint64_t *>(take(size_t(d.n) * 8));
+  s.BZ = reinterpret_cast<uint64_t *>(take(size_t(d.n) * 8));
+  s.ME = reinterpret_cast<uint32_t *>(take(size_t(d.n) * 4));
+  s.Gp = reinterpret_cast<uint64_t *>(take(size_t(h.nC) * kK * 8));
+  s.Yp = reinterpret_cast<uint32_t *>(take(size_t(h.nC) * kK * 4));
+  s.G = reinterpret_cast<uint64_t *>(take(kK * 8));
+  s.Y = reinterpret_cast<uint32_t *>(take(kK * 4));
+  s.part = reinterpret_cast<uint64_t *>(take(size_t(h.CG) * 3 * d.Wp * 8));
+  s.H = reinterpret_cast<uint64_t *>(take(size_t(d.Wp) * 8));
+  s.KW = reinterpret_cast<uint64_t *>(take(size_t(d.Wp) * 8));
+  s.CW = reinterpret_cast<uint64_t *>(take(size_t(d.Wp) * 8));
+  s.RP = reinterpret_cast<uint64_t *>(take(size_t(d.S) * 8));
+  s.OB = reinterpret_cast<uint64_t *>(take(size_t(d.S) * 8));
+  s.list = reinterpret_cast<uint32_t *>(take(size_t(d.n) * 4));
+  s.dets = reinterpret_cast<uint32_t *>(take(size_t(d.n) * 4));
+  s.cnt = reinterpret_cast<uint32_t *>(take(2 * 4));
+  return cur;
+}
+
+hipError_t launch_measure_lr(const TabDev &t, const LrDev &s, const uint32_t *dev_qubits, uint32_t k, uint64_t seed,
+                             uint64_t circuit, uint64_t shot0, uint64_t m0, int num_cus, hipStream_t st,
+                             Profiler *prof) {
+  if (k == 0) return hipSuccess;
+  const LrShape h = lr_shape(t.n, uint32_t(num_cus));
+  const int32_t nb = int32_t((k + kK - 1) / kK);
+  // stabilizer words per planner wave: registers for up to 32 of them
+  const uint32_t per = div_up(t.W - (t.n >> 6), kSweepWaves);
+  LrArgs a{};
+  a.q = dev_qubits;
+  a.k = k;
+  a.CG = h.CG;
+  a.T = h.T;
+  a.seed = seed;
+  a.circuit = circuit;
+  a.shot0 = shot0;
+  a.m0 = m0;
+  hipError_t e;
+  for (int32_t b = -1; b <= nb; ++b) {
+    a.b = uint32_t(b);
+    a.nR = b < nb ? div_up(t.W, 4) : 0;
+    a.nC = b >= 0 && b < nb ? h.nC : 0;
+    a.nH = b > 0 ? div_up(t.W, 16) : 0;
+    a.nS = b > 0 ? std::min(div_up(t.S, 4), 256u) : 0;
+    a.nF = b < 0 ? std::min(div_up(size_t(t.Wp) * t.S, kPrepThreads), 256u) : 0;
+    if (prof) prof->begin(PK_SELECT, st);
+    k_lr_prep<<<a.nR + a.nC + a.nH + a.nS + a.nF, kPrepThreads, 0, st>>>(t, s, a);
+    if (prof) prof->end(PK_SELECT, st);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    a.nC = h.nC;
+    a.nA = b > 0 ? std::min(div_up(size_t(t.W) * t.S, kSweepThreads), 64u) : 0;
+    const uint32_t sweep = b < 0 ? 0 : b < nb ? h.T * h.CG : h.CG;
+    const dim3 grid(2 + a.nA + sweep);
+    const ProfKind kind = b >= 0 && b < nb ? PK_BLOCKED : PK_FINAL;
+    if (prof) prof->begin(kind, st);
+    if (h.narrow) k_lr_sweep<uint32_t, 2><<<grid, kSweepThreads, 0, st>>>(t, s, a);
+    else if (per <= 2) k_lr_sweep<uint64_t, 2><<<grid, kSweepThreads, 0, st>>>(t, s, a);
+    else if (per <= 11) k_lr_sweep<uint64_t, 11><<<grid, kSweepThreads, 0, st>>>(t, s, a);
+    else if (per <= 32) k_lr_sweep<uint64_t, 32><<<grid, kSweepThreads, 0, st>>>(t, s, a);
+    else k_lr_sweep<uint64_t, 0><<<grid, kSweepThreads, 0, st>>>(t, s, a);
+    if (prof) prof->end(kind, st);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if (prof) prof->begin(PK_FINAL, st);
+  k_lr_det_terms<<<dim3(std::min(div_up(t.n, 32), 256u), std::min(k, 4u)), 256, 0, st>>>(t, s, a);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  k_lr_det<<<std::min(k, 1024u), 256, 0, st>>>(t, s, a);
+  if (prof) prof->end(PK_FINAL, st);
+  return hipGetLastError();
+}
+
+}  // namespace cliff
