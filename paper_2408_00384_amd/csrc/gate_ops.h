@@ -102,6 +102,7 @@ __device__ __forceinline__ U128 bop3(U128 a, U128 b, U128 c) {
   return {bop3<LUT>(a.lo, b.lo, c.lo), bop3<LUT>(a.hi, b.hi, c.hi)};
 }
 constexpr uint32_t LUT_AND3 = 0x80;        // a & b & c
+constexpr uint32_t LUT_XOR3 = 0x96;        // a ^ b ^ c
 constexpr uint32_t LUT_AND_XOR = 0x6A;     // (a & b) ^ c
 constexpr uint32_t LUT_ANDN_XOR = 0x9A;    // (a & ~b) ^ c
 constexpr uint32_t LUT_AND_ANDN = 0x40;    // a & b & ~c

@@ -47,16 +47,17 @@
 // and k_lr_det_terms, k_lr_det, the deterministic outcomes, at the end of the pass.
 //
 // Bound: the sweep reads and writes the tableau once per 64 measurements and
-// does 2 x 64 masked XORs per word (51 us a launch at n = 10,000: the XORs);
+// takes 32 table reads per word of x and z (21 us a launch at n = 10,000: LDS
+// reads and memory about even; 71 us at n = 25,000, half written back: memory);
 // small tableaux are bound by the launches and the planner's chain of 64
-// steps (19 us a sweep launch at n = 1,024, 12 us of it the chain).  Against
-// one rowsum sweep per measurement (register-resident up to n = 10,240, one
-// kernel per measurement above), circuit and measure-all: n = 64, 16 shots
-// 0.172 against 0.387 ms; n = 1,024, 128 shots 0.96 against 2.68 ms; n = 3,001
-// after 2 layers, a third of the outcomes deterministic, 1.44 against 7.26 ms;
-// n = 10,000 10.4 against 16.4 ms (blocks of 32 in registers); 128 of n = 25,000
-// 3.16 against 12.2 ms.  Blocks of 64: twice the work per launch of 32 at the
-// same number of tableau passes, and a row's bits are one 64-bit word.
+// steps (19 us a sweep launch at n = 1,024).  Against one rowsum sweep per
+// measurement (register-resident up to n = 10,240, one kernel per measurement
+// above), circuit and measure-all: n = 64, 16 shots 0.172 against 0.387 ms;
+// n = 1,024, 128 shots 0.96 against 2.68 ms; n = 3,001 after 2 layers, a third
+// of the outcomes deterministic, 1.30 against 7.26 ms; n = 10,000 5.99 against
+// 16.4 ms (blocks of 32 in registers); 128 of n = 25,000 2.87 against 12.2 ms.
+// Blocks of 64: twice the work per launch of 32 at the same number of tableau
+// passes, and a row's bits are one 64-bit word.
 #include <algorithm>
 
 #include "internal.h"
@@ -72,7 +73,6 @@ constexpr uint32_t kSweepThreads = 1024;
 constexpr uint32_t kSweepWaves = kSweepThreads / 64;
 constexpr uint32_t kPrepCols = 16;         // columns per wave of the prep kernel
 constexpr uint32_t kWindow = 512;          // rows the planner can follow step by step
-constexpr uint32_t kStride = 65;           // LDS row stride of a U tile (words; odd: no bank conflicts)
 
 __device__ __forceinline__ uint64_t lbit(uint32_t b) { return 1ull << (b & 63); }
 __device__ __forceinline__ uint64_t pair64(uint32_t lo, uint32_t hi) { return (uint64_t(hi) << 32) | lo; }
@@ -124,7 +124,7 @@ struct LrArgs {
   const uint32_t *q;      // device: the pass's measured qubits
   uint32_t k, b;          // measurements of the pass; block (int32: -1 .. nb)
   uint32_t nR, nC, nH, nS, nF;   // prep: workgroups per part
-  uint32_t CG, T;         // sweep: column groups, row tiles
+  uint32_t CG, T, lp;     // sweep: column groups, row tiles, log2 of the lanes per column
   uint32_t nA;            // sweep: sign workgroups
   uint64_t seed, circuit, shot0, m0;
 };
@@ -588,157 +588,158 @@ __device__ __forceinline__ void plan_block(const TabDev &t, const LrDev &s, cons
 }
 
 // ----------------------------------------------------------------- sweep ---
-// A workgroup holds 64 units (T: 32 or 64 rows) of U in LDS and updates them
-// in a share of the columns, four columns in flight per wave.  Per step and
-// column the pivot-row bits are wave-uniform masks (a scalar instruction),
-// so the update is one v_bitop3 per 32 rows and plane.
-template <typename T>
-struct Halves;
-template <>
-struct Halves<uint32_t> { static constexpr int N = 1; };
-template <>
-struct Halves<uint64_t> { static constexpr int N = 2; };
-__device__ __forceinline__ uint32_t and_xor(uint32_t v, uint32_t m, uint32_t a) { return bop3<LUT_AND_XOR>(v, m, a); }
-__device__ __forceinline__ uint64_t and_xor(uint64_t v, uint32_t m, uint64_t a) { return xor_if(a, v, m); }
-__device__ __forceinline__ unsigned long long lds_xor_ret(uint64_t *p, uint64_t v) {
-  return atomicXor(reinterpret_cast<unsigned long long *>(p), (unsigned long long)v);
-}
-__device__ __forceinline__ uint32_t lds_xor_ret(uint32_t *p, uint32_t v) { return atomicXor(p, v); }
+// A workgroup updates a tile of up to 64 row words in a share of the columns.
+// Its 64 U columns are laid out as tables in LDS, all 16 sums of each group
+// of 4, so that a column takes one 16-byte read per group, plane and two
+// words instead of four masked XORs a word.  A column is held by LP lanes (two
+// words each; LP = 32, so two columns a wave, from 64 words on), each with
+// that column's pivot-row bits, so there is no scalar work per column.  (The
+// masked form, bits as scalar masks, spent two scalar instructions per mask,
+// one scalar unit for the four SIMDs: 51 us a launch at n = 10,000, now 21.)
+struct SweepShared {
+  uint64_t tab[16][16][64];                  // [group][sum][word]
+  uint64_t kill[64];                         // rows p_t and p_t - n
+  unsigned long long e0[64], e1[64], zx[64];
+  uint32_t P[kK], any;
+};
 
-template <typename T>
-__device__ __forceinline__ void lr_sweep(const TabDev &t, const LrDev &s, const LrArgs &a, uint32_t wg,
-                                         uint64_t *s_u, uint64_t *s_k, uint64_t *s_e, uint32_t *s_flag) {
-  constexpr uint32_t Q = 8 / sizeof(T);               // units per word
-  constexpr uint32_t TW = 64 / Q;                     // words per tile
-  constexpr uint32_t US = Q == 1 ? kStride : 2 * (TW + 1);   // LDS row stride (units)
-  constexpr uint32_t B = 4;                           // columns in flight
+__device__ __forceinline__ void xor3(uint4 &a, const uint4 b, const uint4 c) {
+  a.x = bop3<LUT_XOR3>(a.x, b.x, c.x);
+  a.y = bop3<LUT_XOR3>(a.y, b.y, c.y);
+  a.z = bop3<LUT_XOR3>(a.z, b.z, c.z);
+  a.w = bop3<LUT_XOR3>(a.w, b.w, c.w);
+}
+__device__ __forceinline__ uint4 as4(uint64_t a, uint64_t b) {
+  return make_uint4(uint32_t(a), uint32_t(a >> 32), uint32_t(b), uint32_t(b >> 32));
+}
+
+__device__ __forceinline__ void lr_sweep(const TabDev &t, const LrDev &s, const LrArgs &a, uint32_t wg, SweepShared &sh) {
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const LrPlan *pl = s.plan + (a.b & 3u);
   if (pl->rand == 0) return;   // nothing random in this block
-  const uint32_t tile = wg % a.T, cg = wg / a.T, n = t.n, W = t.W;
-  const uint32_t w0 = tile * TW;
-  const T *sU = reinterpret_cast<const T *>(s_u);
-  T *sE = reinterpret_cast<T *>(s_e);
-  if (tid < TW) s_k[tid] = 0;
-  if (tid < 3 * 64) sE[tid] = 0;
-  if (tid == 0) *s_flag = 0;
+  const uint32_t tile = wg % a.T, cg = wg / a.T, n = t.n, W = t.W, w0 = tile * 64;
+  if (tid < 64) {
+    sh.kill[tid] = 0;
+    sh.e0[tid] = sh.e1[tid] = sh.zx[tid] = 0;
+    sh.P[tid] = pl->P[tid];
+  }
+  if (tid == 0) sh.any = 0;
   __syncthreads();
-  // U of this tile: [word][step] in memory, [step][word] in LDS
-  const uint64_t *U = s.U[a.b & 1u];
-  uint64_t any = 0;
+  {
+    // thread (word, group): the 16 sums of its four U words
+    const uint32_t wl = lane, g = wave;
+    uint64_t c[16];
+    c[0] = 0;
 #pragma unroll
-  for (uint32_t j = 0; j < TW * kK / kSweepThreads; ++j) {
-    const uint32_t i = tid + j * kSweepThreads, wl = i / kK, st = i % kK;
-    const uint64_t v = w0 + wl < W ? U[size_t(w0 + wl) * kK + st] : 0ull;
-    s_u[st * (US / Q) + wl] = v;
-    any |= v;
+    for (uint32_t i = 0; i < 4; ++i)
+      c[1u << i] = w0 + wl < W ? s.U[a.b & 1u][size_t(w0 + wl) * kK + 4 * g + i] : 0ull;
+    uint64_t any = c[1] | c[2] | c[4] | c[8];
+#pragma unroll
+    for (uint32_t v = 1; v < 16; ++v) c[v] = c[v & (v - 1)] ^ c[v & (0u - v)];
+#pragma unroll
+    for (uint32_t v = 0; v < 16; ++v) sh.tab[g][v][wl] = c[v];
+    if (tid < kK && sh.P[tid] != kNone) {
+      const uint32_t p = sh.P[tid], r = (p >> 6) - w0, r2 = ((p - n) >> 6) - w0;
+      if (r < 64) atomicOr(reinterpret_cast<unsigned long long *>(&sh.kill[r]), (unsigned long long)lbit(p));
+      if (r2 < 64) atomicOr(reinterpret_cast<unsigned long long *>(&sh.kill[r2]), (unsigned long long)lbit(p - n));
+      any |= uint64_t(r < 64 || r2 < 64);
+    }
+    if (__ballot(any != 0) && lane == 0) sh.any = 1;
   }
-  if (tid < kK && pl->P[tid] != kNone) {
-    const uint32_t p = pl->P[tid], r = (p >> 6) - w0, r2 = ((p - n) >> 6) - w0;
-    if (r < TW) atomicOr(reinterpret_cast<unsigned long long *>(&s_k[r]), (unsigned long long)lbit(p));
-    if (r2 < TW) atomicOr(reinterpret_cast<unsigned long long *>(&s_k[r2]), (unsigned long long)lbit(p - n));
-    any |= uint64_t(r < TW || r2 < TW);
-  }
-  if (__ballot(any != 0) && lane == 0) *s_flag = 1;
   __syncthreads();
-  const uint32_t units = W * Q, unit = tile * 64 + lane;
-  const bool live = unit < units;
-  if (*s_flag) {   // (otherwise no row of this tile changes)
-    const T keep = live ? ~reinterpret_cast<const T *>(s_k)[lane] : T(0);
-    const size_t cs = size_t(t.Wp) * Q;
-    T *XT = reinterpret_cast<T *>(t.X), *ZT = reinterpret_cast<T *>(t.Z);
+  if (sh.any) {   // (otherwise no row of this tile changes)
+    const uint32_t wl = 2 * (lane & ((1u << a.lp) - 1u)), cl = lane >> a.lp;   // this lane's words wl, wl + 1; column slot
+    const bool live = w0 + wl < W;   // (an odd W's second word is padding: zero, and stays so)
+    const uint32_t step = kSweepWaves << (6 - a.lp);   // columns the workgroup takes at a time
     const uint32_t c0 = uint32_t(uint64_t(cg) * n / a.CG), c1 = uint32_t(uint64_t(cg + 1) * n / a.CG);
-    T e0 = 0, e1 = 0, zx = 0;
-    for (uint32_t cb = c0 + wave; cb < c1; cb += 64 * kSweepWaves) {
-      // lane i: the pivot-row bits of the wave's i-th column
-      const uint32_t ci = cb + lane * kSweepWaves;
-      const uint64_t bxv = ci < c1 ? s.BX[ci] : 0ull, bzv = ci < c1 ? s.BZ[ci] : 0ull;
-      const uint32_t mev = ci < c1 ? s.ME[ci] : 0u;
-      const uint32_t cnt = min(64u, (c1 - cb + kSweepWaves - 1) / kSweepWaves);
-      T xn[B], zn[B];
+    const uint4 kl = as4(sh.kill[wl], sh.kill[wl + 1]);
+    const unsigned char *tb = reinterpret_cast<const unsigned char *>(&sh.tab[0][0][wl]);
+    constexpr uint32_t B = 2;   // columns in flight ahead of the one at hand
+    struct Col {
+      uint4 x, z;
+      uint64_t bx, bz;
+      uint32_t me;
+    } nx[B];
+    auto fetch = [&](Col &d, uint32_t c) {
+      const bool ok = c < c1 && live;
+      const size_t at = ok ? size_t(c) * t.Wp + w0 + wl : 0, ac = ok ? c : 0;
+      d.x = *reinterpret_cast<const uint4 *>(t.X + at);
+      d.z = *reinterpret_cast<const uint4 *>(t.Z + at);
+      d.bx = s.BX[ac];
+      d.bz = s.BZ[ac];
+      d.me = s.ME[ac];
+      if (!ok) d.bx = d.bz = 0;
+    };
+    uint4 e0 = make_uint4(0, 0, 0, 0), e1 = e0, zx = e0;
+    const uint32_t cw = c0 + (wave << (6 - a.lp)) + cl;
+#pragma unroll
+    for (uint32_t i = 0; i < B; ++i) fetch(nx[i], cw + i * step);
+    for (uint32_t cb = c0; cb < c1; cb += B * step) {
 #pragma unroll
       for (uint32_t i = 0; i < B; ++i) {
-        const bool ok = i < cnt && live;
-        const size_t at = ok ? size_t(cb + i * kSweepWaves) * cs + unit : 0;
-        xn[i] = XT[at];
-        zn[i] = ZT[at];
-      }
-      for (uint32_t j = 0; j < cnt; j += B) {
-        T x[B], z[B], dx[B], dz[B];
-        uint32_t xl[B], xh[B], zl[B], zh[B], me[B], some = 0;
+        const uint32_t c = cw + (cb - c0) + i * step;
+        const Col d = nx[i];
+        fetch(nx[i], c + B * step);
+        uint4 dx = make_uint4(0, 0, 0, 0), dz = dx;
+        if (__ballot((d.bx | d.bz) != 0)) {
 #pragma unroll
-        for (uint32_t i = 0; i < B; ++i) {
-          const bool ok = j + i < cnt;
-          const uint32_t jl = (j + i) & 63u;
-          xl[i] = ok ? rdlane(uint32_t(bxv), jl) : 0u;
-          xh[i] = ok ? rdlane(uint32_t(bxv >> 32), jl) : 0u;
-          zl[i] = ok ? rdlane(uint32_t(bzv), jl) : 0u;
-          zh[i] = ok ? rdlane(uint32_t(bzv >> 32), jl) : 0u;
-          me[i] = ok ? rdlane(mev, jl) : 0u;
-          some |= xl[i] | xh[i] | zl[i] | zh[i];
-          x[i] = xn[i];
-          z[i] = zn[i];
-          dx[i] = 0;
-          dz[i] = 0;
-        }
-        // the next four columns' loads run under this four's arithmetic
-#pragma unroll
-        for (uint32_t i = 0; i < B; ++i) {
-          const bool ok = j + B + i < cnt && live;
-          const size_t at = ok ? size_t(cb + (j + B + i) * kSweepWaves) * cs + unit : 0;
-          xn[i] = XT[at];
-          zn[i] = ZT[at];
-        }
-        if (some) {
-#pragma unroll 8
-          for (uint32_t st = 0; st < 32; ++st) {
-            const T u = sU[st * US + lane];
-#pragma unroll
-            for (uint32_t i = 0; i < B; ++i) {
-              dx[i] = and_xor(u, 0u - ((xl[i] >> st) & 1u), dx[i]);
-              dz[i] = and_xor(u, 0u - ((zl[i] >> st) & 1u), dz[i]);
-            }
-          }
-#pragma unroll 8
-          for (uint32_t st = 0; st < 32; ++st) {
-            const T u = sU[(32 + st) * US + lane];
-#pragma unroll
-            for (uint32_t i = 0; i < B; ++i) {
-              dx[i] = and_xor(u, 0u - ((xh[i] >> st) & 1u), dx[i]);
-              dz[i] = and_xor(u, 0u - ((zh[i] >> st) & 1u), dz[i]);
-            }
+          for (uint32_t g = 0; g < 16; g += 2) {
+            const uint32_t xs = uint32_t(d.bx >> (4 * g)), zs = uint32_t(d.bz >> (4 * g));
+            auto get = [&](uint32_t gg, uint32_t nib) {
+              return *reinterpret_cast<const uint4 *>(tb + gg * (16 * 64 * 8) + nib * (64 * 8));
+            };
+            xor3(dx, get(g, xs & 15u), get(g + 1, (xs >> 4) & 15u));
+            xor3(dz, get(g, zs & 15u), get(g + 1, (zs >> 4) & 15u));
           }
         }
+        if (c < c1 && live) {
+          uint32_t ox[4] = {d.x.x, d.x.y, d.x.z, d.x.w}, oz[4] = {d.z.x, d.z.y, d.z.z, d.z.w};
+          uint32_t px[4] = {dx.x, dx.y, dx.z, dx.w}, pz[4] = {dz.x, dz.y, dz.z, dz.w};
+          uint32_t *f0 = &e0.x, *f1 = &e1.x, *fz = &zx.x;
+          const uint32_t kw[4] = {kl.x, kl.y, kl.z, kl.w};
+          uint32_t chx = 0, chz = 0, pz_bit[4] = {0, 0, 0, 0};
+          if (d.me) {   // this column was measured: its pivot row becomes Z on it
+            const uint32_t p = sh.P[d.me - 1], h = (p >> 5) - 2 * (w0 + wl);
 #pragma unroll
-        for (uint32_t i = 0; i < B; ++i) {
-          if (j + i >= cnt) break;   // wave-uniform
-          const T ox = x[i] & keep, oz = z[i] & keep;
-          const T nx = ox ^ dx[i];
-          T nz = oz ^ dz[i];
-          if (me[i]) {   // this column was measured: its pivot row becomes Z on it
-            const uint32_t p = pl->P[me[i] - 1], pu = (p >> 6) * Q + (Q == 2 ? (p >> 5) & 1u : 0u);
-            if (unit == pu) nz |= T(1) << (p & (8 * sizeof(T) - 1));
+            for (uint32_t q = 0; q < 4; ++q)
+              if (h == q) pz_bit[q] = 1u << (p & 31);
           }
-          // (Y_old - Y_new) mod 4 in two planes, and z_old.(x_new ^ x_old)
-          const T yn = nx & nz, anti = (ox & oz) ^ yn;
-          e1 ^= anti & (e0 ^ yn);
-          e0 ^= anti;
-          zx ^= oz & dx[i];
-          const size_t at = size_t(cb + (j + i) * kSweepWaves) * cs + unit;
-          if (live && nx != x[i]) XT[at] = nx;
-          if (live && nz != z[i]) ZT[at] = nz;
+#pragma unroll
+          for (uint32_t q = 0; q < 4; ++q) {
+            const uint32_t kx = ox[q] & ~kw[q], kz = oz[q] & ~kw[q];
+            px[q] = (kx ^ px[q]);
+            const uint32_t dq = px[q] ^ kx;
+            pz[q] = (kz ^ pz[q]) | pz_bit[q];
+            // (Y_old - Y_new) mod 4 in two planes, and z_old.(x_new ^ x_old)
+            const uint32_t yn = px[q] & pz[q], anti = (kx & kz) ^ yn;
+            f1[q] = bop3<LUT_AND_XOR>(anti, f0[q] ^ yn, f1[q]);
+            f0[q] ^= anti;
+            fz[q] = bop3<LUT_AND_XOR>(kz, dq, fz[q]);
+            chx |= px[q] ^ ox[q];
+            chz |= pz[q] ^ oz[q];
+          }
+          const size_t at = size_t(c) * t.Wp + w0 + wl;
+          if (chx) *reinterpret_cast<uint4 *>(t.X + at) = make_uint4(px[0], px[1], px[2], px[3]);
+          if (chz) *reinterpret_cast<uint4 *>(t.Z + at) = make_uint4(pz[0], pz[1], pz[2], pz[3]);
         }
       }
     }
-    const T old = lds_xor_ret(&sE[lane], e0);
-    lds_xor_ret(&sE[64 + lane], e1 ^ (old & e0));
-    lds_xor_ret(&sE[128 + lane], zx);
+    // the lanes' counters summed in LDS: mod-4 addition with the low plane's
+    // carry taken from the atomic XOR's old value
+    auto add = [&](uint32_t w, uint64_t v0, uint64_t v1, uint64_t vz) {
+      const unsigned long long old = atomicXor(&sh.e0[w], (unsigned long long)v0);
+      atomicXor(&sh.e1[w], (unsigned long long)(v1 ^ (old & v0)));
+      atomicXor(&sh.zx[w], (unsigned long long)vz);
+    };
+    add(wl, pair64(e0.x, e0.y), pair64(e1.x, e1.y), pair64(zx.x, zx.y));
+    add(wl + 1, pair64(e0.z, e0.w), pair64(e1.z, e1.w), pair64(zx.z, zx.w));
   }
   __syncthreads();
-  if (tid < 3 * 64) {
-    const uint32_t pln = tid >> 6, un = tile * 64 + lane;
-    T *part = reinterpret_cast<T *>(s.part + (size_t(cg) * 3 + pln) * t.Wp);
-    if (un < units) part[un] = sE[tid];
+  if (tid < 64 && w0 + tid < W) {
+    uint64_t *part = s.part + size_t(cg) * 3 * t.Wp + w0 + tid;
+    part[0] = sh.e0[tid];
+    part[t.Wp] = sh.e1[tid];
+    part[2 * size_t(t.Wp)] = sh.zx[tid];
   }
 }
 
@@ -813,28 +814,33 @@ __device__ __forceinline__ void lr_columns(const TabDev &t, const LrDev &s, cons
   }
 }
 
-template <typename T, int RW>
+template <int RW>
 __global__ void __launch_bounds__(kSweepThreads) k_lr_sweep(TabDev t, LrDev s, LrArgs a) {
-  __shared__ uint64_t s_mem[kK * kStride];
-  __shared__ uint64_t s_k[64], s_e[3 * 64];
-  __shared__ uint32_t s_flag[kK];
-  static_assert(sizeof(PlanShared) <= sizeof(s_mem), "planner's LDS");
+  __shared__ union {
+    SweepShared sweep;
+    PlanShared plan;
+    struct {
+      uint64_t g[kK];
+      uint32_t y[kK];
+    } gram;
+    uint32_t P[kK];
+  } sh;
   const int32_t b = int32_t(a.b), nb = int32_t((a.k + kK - 1) / kK);
   uint32_t wg = blockIdx.x;
   if (wg == 0) {
-    if (b + 1 < nb) plan_block<RW>(t, s, a, *reinterpret_cast<PlanShared *>(s_mem));
+    if (b + 1 < nb) plan_block<RW>(t, s, a, sh.plan);
     return;
   }
   if (wg == 1) {
-    if (b >= 0 && b < nb) return lr_gram(s, a, s_mem, s_flag);
+    if (b >= 0 && b < nb) return lr_gram(s, a, sh.gram.g, sh.gram.y);
     if (b < 0)   // the pending signs were folded by the launch before this one
       for (uint32_t i = threadIdx.x; i < t.Wp; i += kSweepThreads) t.P[i] = 0;
     return;
   }
   wg -= 2;
-  if (wg < a.nA) return lr_signs(t, s, a, wg, s_flag);
+  if (wg < a.nA) return lr_signs(t, s, a, wg, sh.P);
   wg -= a.nA;
-  if (b < nb) lr_sweep<T>(t, s, a, wg, s_mem, s_k, s_e, s_flag);
+  if (b < nb) lr_sweep(t, s, a, wg, sh.sweep);
   else lr_columns(t, s, a, wg);
 }
 
@@ -926,26 +932,23 @@ __global__ void __launch_bounds__(256) k_lr_det(TabDev t, LrDev s, LrArgs a) {
 // ------------------------------------------------------------------ host ---
 static uint32_t div_up(size_t a, size_t b) { return uint32_t((a + b - 1) / b); }
 
-// Sweep shape: units of 32 rows up to n = 1,024 (a wave then holds a whole
-// column: 64-row words would leave half the lanes idle), 64 above.
+// Sweep shape: row tiles of 64 words, or the whole column by fewer lanes, and
+// one workgroup per compute unit (the tables take most of its LDS), the
+// planner and the sign work aside; at least two rounds of columns each.
 struct LrShape {
-  bool narrow;
-  uint32_t T, CG, nC;
+  uint32_t T, lp, CG, nC, nA;
 };
-static LrShape lr_shape(uint32_t n, uint32_t num_cus) {
+static LrShape lr_shape(uint32_t n, uint32_t S, uint32_t num_cus) {
   LrShape r;
   const uint32_t W = (2 * n + 63) / 64;
-  r.narrow = W <= 32;
-  r.T = div_up(W, r.narrow ? 32 : 64);
-  // one workgroup per compute unit, the planner and the sign work aside; at
-  // least two columns per wave
-  const uint32_t wgs = num_cus > 16 ? num_cus - 6 : num_cus;
-  uint32_t cg = wgs / r.T;
-  const uint32_t most = div_up(n, 2 * kSweepWaves);
-  if (cg > most) cg = most;
-  r.CG = cg < 1 ? 1 : cg;
-  r.nC = div_up(n, 4 * kPrepCols);
-  if (r.nC > 512) r.nC = 512;
+  r.T = div_up(W, 64);
+  r.lp = 0;
+  while (r.lp < 5 && (2u << r.lp) < W) ++r.lp;
+  r.nA = std::min(div_up(size_t(W) * S, kSweepThreads), std::max(1u, num_cus / 8));
+  const uint32_t wgs = num_cus > 2 + r.nA ? num_cus - 2 - r.nA : 1;
+  const uint32_t most = div_up(n, 2 * (kSweepWaves << (6 - r.lp)));
+  r.CG = std::max(1u, std::min(wgs / r.T, most));
+  r.nC = std::min(div_up(n, 4 * kPrepCols), 512u);
   return r;
 }
 
@@ -955,7 +958,7 @@ size_t lr_scratch_bytes(const Dims &d, uint32_t num_cus) {
 }
 
 size_t lr_scratch_bind(const Dims &d, uint32_t num_cus, uint8_t *base, LrDev &s) {
-  const LrShape h = lr_shape(d.n, num_cus);
+  const LrShape h = lr_shape(d.n, d.S, num_cus);
   size_t cur = 0;
   auto take = [&](size_t bytes) {
     uint8_t *at = base + cur;
@@ -989,7 +992,7 @@ hipError_t launch_measure_lr(const TabDev &t, const LrDev &s, const uint32_t *de
                              uint64_t circuit, uint64_t shot0, uint64_t m0, int num_cus, hipStream_t st,
                              Profiler *prof) {
   if (k == 0) return hipSuccess;
-  const LrShape h = lr_shape(t.n, uint32_t(num_cus));
+  const LrShape h = lr_shape(t.n, t.S, uint32_t(num_cus));
   const int32_t nb = int32_t((k + kK - 1) / kK);
   // stabilizer words per planner wave: registers for up to 32 of them
   const uint32_t per = div_up(t.W - (t.n >> 6), kSweepWaves);
@@ -998,6 +1001,7 @@ hipError_t launch_measure_lr(const TabDev &t, const LrDev &s, const uint32_t *de
   a.k = k;
   a.CG = h.CG;
   a.T = h.T;
+  a.lp = h.lp;
   a.seed = seed;
   a.circuit = circuit;
   a.shot0 = shot0;
@@ -1015,16 +1019,15 @@ hipError_t launch_measure_lr(const TabDev &t, const LrDev &s, const uint32_t *de
     if (prof) prof->end(PK_SELECT, st);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     a.nC = h.nC;
-    a.nA = b > 0 ? std::min(div_up(size_t(t.W) * t.S, kSweepThreads), 64u) : 0;
+    a.nA = b > 0 ? h.nA : 0;
     const uint32_t sweep = b < 0 ? 0 : b < nb ? h.T * h.CG : h.CG;
     const dim3 grid(2 + a.nA + sweep);
     const ProfKind kind = b >= 0 && b < nb ? PK_BLOCKED : PK_FINAL;
     if (prof) prof->begin(kind, st);
-    if (h.narrow) k_lr_sweep<uint32_t, 2><<<grid, kSweepThreads, 0, st>>>(t, s, a);
-    else if (per <= 2) k_lr_sweep<uint64_t, 2><<<grid, kSweepThreads, 0, st>>>(t, s, a);
-    else if (per <= 11) k_lr_sweep<uint64_t, 11><<<grid, kSweepThreads, 0, st>>>(t, s, a);
-    else if (per <= 32) k_lr_sweep<uint64_t, 32><<<grid, kSweepThreads, 0, st>>>(t, s, a);
-    else k_lr_sweep<uint64_t, 0><<<grid, kSweepThreads, 0, st>>>(t, s, a);
+    if (per <= 2) k_lr_sweep<2><<<grid, kSweepThreads, 0, st>>>(t, s, a);
+    else if (per <= 11) k_lr_sweep<11><<<grid, kSweepThreads, 0, st>>>(t, s, a);
+    else if (per <= 32) k_lr_sweep<32><<<grid, kSweepThreads, 0, st>>>(t, s, a);
+    else k_lr_sweep<0><<<grid, kSweepThreads, 0, st>>>(t, s, a);
     if (prof) prof->end(kind, st);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
