@@ -306,7 +306,6 @@ constexpr uint32_t kStepList = 32;
 struct LrPlan {            // one block's plan
   uint64_t rand;           // bit t: measurement t of the block is random
   uint64_t RX[kLrK];       // pivot row t's bits of the block's columns at its step, less bit t
-  uint64_t RQ[kLrK];       // replaced row p_t - n's bits of U
   uint32_t P[kLrK];        // pivot rows (kNone: deterministic)
 };
 struct LrDev {
@@ -316,6 +315,7 @@ struct LrDev {
   uint64_t *BX, *BZ;       // [n] x and z of the column at the block's pivot rows
   uint32_t *ME;            // [n] 1 + its random measurement in the block, or 0
   uint64_t *Gp, *G;        // pivot rows' Gram rows: per workgroup [nC][kLrK], summed
+  unsigned long long *Sp;  // [nC] their support
   uint32_t *Yp, *Y;        // their Y counts: per workgroup, summed mod 4
   uint64_t *part;          // [column group][3][Wp]: (Y_old - Y_new) mod 4 (two planes), z.x parity
   uint64_t *H, *KW, *CW;   // [Wp] sign flips, pivot and replaced rows, pivot rows

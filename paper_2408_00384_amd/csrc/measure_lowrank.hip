@@ -49,13 +49,14 @@
 // Bound: the sweep reads and writes the tableau once per 64 measurements and
 // takes 32 table reads per word of x and z (21 us a launch at n = 10,000: LDS
 // reads and memory about even; 71 us at n = 25,000, half written back: memory);
-// small tableaux are bound by the launches and the planner's chain of 64
-// steps (19 us a sweep launch at n = 1,024).  Against one rowsum sweep per
-// measurement (register-resident up to n = 10,240, one kernel per measurement
-// above), circuit and measure-all: n = 64, 16 shots 0.172 against 0.387 ms;
-// n = 1,024, 128 shots 0.96 against 2.68 ms; n = 3,001 after 2 layers, a third
-// of the outcomes deterministic, 1.30 against 7.26 ms; n = 10,000 5.99 against
-// 16.4 ms (blocks of 32 in registers); 128 of n = 25,000 2.87 against 12.2 ms.
+// below n = 6,000 the planner's chain of 64 dependent steps (0.11 us each;
+// 11 us a sweep launch at n = 1,024) and the prep launch's chain of loads (7
+// to 8 us).  Against one rowsum sweep per measurement (register-resident up to
+// n = 10,240, one kernel per measurement above), circuit and measure-all:
+// n = 64, 16 shots 0.164 against 0.391 ms; n = 1,024, 128 shots 0.81 against
+// 2.67 ms; n = 3,001 after 2 layers, a third of the outcomes deterministic,
+// 1.27 against 7.29 ms; n = 5,003 1.94 against 8.16 ms; n = 10,000 5.11 against
+// 16.3 ms (blocks of 32 in registers); 128 of n = 25,000 2.86 against 12.2 ms.
 // Blocks of 64: twice the work per launch of 32 at the same number of tableau
 // passes, and a row's bits are one 64-bit word.
 #include <algorithm>
@@ -71,7 +72,7 @@ constexpr uint32_t kK = kLrK;              // measurements per block
 constexpr uint32_t kPrepThreads = 256;
 constexpr uint32_t kSweepThreads = 1024;
 constexpr uint32_t kSweepWaves = kSweepThreads / 64;
-constexpr uint32_t kPrepCols = 16;         // columns per wave of the prep kernel
+constexpr uint32_t kPrepCols = 8;          // columns per wave of the prep kernel, all in flight
 constexpr uint32_t kWindow = 512;          // rows the planner can follow step by step
 
 __device__ __forceinline__ uint64_t lbit(uint32_t b) { return 1ull << (b & 63); }
@@ -150,21 +151,15 @@ __device__ __forceinline__ void prep_rows(const TabDev &t, const LrDev &s, const
   if (cur && tid < kK) sP[tid] = pl->P[tid];
   const uint64_t rx = cur ? pl->RX[lane] : 0ull, rand = cur ? pl->rand : 0ull;
   __syncthreads();
+  // V_t: the next block's columns at pivot row t, as they stand before block
+  // b; loaded under the rows' replay
+  uint32_t p[16];
+  uint64_t xv[16];
   if (cur && kn) {
-    // V_t: the next block's columns at pivot row t, as they stand before block b
-    uint32_t p[16];
-    uint64_t xv[16];
 #pragma unroll
     for (uint32_t i = 0; i < 16; ++i) {
       p[i] = __builtin_amdgcn_readfirstlane(sP[wave * 16 + i]);
-      const bool ok = p[i] != kNone && lane < kn;
-      xv[i] = t.X[ok ? size_t(myq) * t.Wp + (p[i] >> 6) : 0];
-      if (!ok) xv[i] = 0;
-    }
-#pragma unroll
-    for (uint32_t i = 0; i < 16; ++i) {
-      const uint64_t v = __ballot((xv[i] >> (p[i] & 63)) & 1u);
-      if (lane == 0) sV[wave * 16 + i] = v;
+      xv[i] = t.X[size_t(myq) * t.Wp + (p[i] != kNone ? p[i] >> 6 : 0)];
     }
   }
   if (cur && tid < kK && sP[tid] != kNone) {
@@ -172,19 +167,38 @@ __device__ __forceinline__ void prep_rows(const TabDev &t, const LrDev &s, const
     if (r < kPrepThreads) spec[r] = 255;          // pivot row
     if (r2 < kPrepThreads) spec[r2] = tid + 1;    // replaced row
   }
-  __syncthreads();
-  if (!have) return;
   uint64_t v = transpose64(nw, lane);
+  __syncthreads();
+  uint64_t u = 0;
   if (cur) {
-    // the row replays the block's steps: after step t bit t holds U[row][t]
-#pragma unroll
-    for (uint32_t i = 0; i < kK; ++i) e = xor_if(e, rdlane64(rx, i), bit_mask(e, i));
-    uint64_t u = e & rand;
+    // the row replays the block's steps: after step t bit t holds U[row][t].
+    // Replaced row p_s - n takes row p_s's bits at step s and goes on from
+    // there: the steps after s act on its later bits alone, and what they
+    // add below is added to the bits it took.
     const uint32_t sp = spec[tid];
+    uint64_t low = 0;
     if (sp) {
-      u = sp == 255 ? 0ull : pl->RQ[sp - 1] & rand;
+      const uint32_t st = sp - 1;
+      e = sp == 255 ? 0ull : pl->RX[st] | lbit(st);
+      const uint64_t upto = sp == 255 ? 0ull : lbit(st) | (lbit(st) - 1);
+      low = e & upto;
+      e &= ~upto;
       v = 0;
     }
+#pragma unroll
+    for (uint32_t i = 0; i < kK; ++i) e = xor_if(e, rdlane64(rx, i), bit_mask(e, i));
+    u = (e ^ low) & rand;
+    if (kn) {
+#pragma unroll
+      for (uint32_t i = 0; i < 16; ++i) {
+        const uint64_t bits = __ballot(lane < kn && p[i] != kNone && ((xv[i] >> (p[i] & 63)) & 1u));
+        if (lane == 0) sV[wave * 16 + i] = bits;
+      }
+    }
+  }
+  __syncthreads();
+  if (!have) return;
+  if (cur) {
     if (kn) {
       const uint64_t vt = sV[lane];
 #pragma unroll
@@ -207,16 +221,14 @@ __device__ __forceinline__ void prep_cols(const TabDev &t, const LrDev &s, const
   const uint32_t wp = mine ? p >> 6 : 0u, sh = p & 63;
   const uint64_t ru = mine ? pl->RX[lane] & rand & (lbit(lane) - 1) : 0ull;   // pivots row p absorbed before its step
   const uint32_t q = mine ? a.q[base + lane] : kNone;
-  if (tid < kK) {
-    sG[tid] = 0;
-    sY[tid] = 0;
-  }
+  if (tid <= kK) sG[tid] = 0;   // [kK]: the pivot rows' support
+  if (tid < kK) sY[tid] = 0;
   __syncthreads();
   uint64_t g = 0;
   uint32_t y = 0;
   unsigned long long sup = 0;
   const uint32_t wv = wg * 4 + wave, nwv = a.nC * 4;
-  constexpr uint32_t B = 8;   // columns in flight
+  constexpr uint32_t B = kPrepCols;
   for (uint32_t c0 = wv; c0 < n; c0 += nwv * B) {
     uint64_t xw[B], zw[B];
 #pragma unroll
@@ -248,86 +260,65 @@ __device__ __forceinline__ void prep_cols(const TabDev &t, const LrDev &s, const
   atomicAdd(&sY[lane], y);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) sup += __shfl_xor(sup, off);
-  if (lane == 0 && sup) atomicAdd(reinterpret_cast<unsigned long long *>(t.state + ST_SUPPORT), sup);
+  if (lane == 0) atomicAdd(&sG[kK], sup);
   __syncthreads();
+  if (tid == 0) s.Sp[wg] = sG[kK];
   if (tid < kK) {
     s.Gp[size_t(wg) * kK + tid] = sG[tid];
     s.Yp[size_t(wg) * kK + tid] = sY[tid];
   }
 }
 
-// Sign flips of block b - 1 per row word: 16 lanes a word, each a share of
-// the column groups' partials and of the pivots.
-__device__ __forceinline__ void prep_flips(const TabDev &t, const LrDev &s, const LrArgs &a, uint32_t wg,
-                                           uint64_t *sU, unsigned long long *sKill, unsigned long long *sCons) {
-  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint32_t bp = a.b - 1;
+// Sign flips of block b - 1, one wave per row word: lane = pivot (and a
+// share of the column groups' partials).
+__device__ __forceinline__ void prep_flips(const TabDev &t, const LrDev &s, const LrArgs &a, uint32_t wg) {
+  const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t bp = a.b - 1, w = wg * 4 + wave;
   const LrPlan *pl = s.plan + (bp & 3u);
-  if (pl->rand == 0) return;
-  const uint32_t w0 = wg * 16, wl = wave * 4 + (lane >> 4), w = w0 + wl, sl = lane & 15;
-  const bool have = w < t.W;
-  if (tid < 16) {
-    sKill[tid] = 0;
-    sCons[tid] = 0;
-  }
-  const uint64_t *U = s.U[bp & 1u] + size_t(have ? w : 0) * kK;
-  uint64_t u[4];
-#pragma unroll
-  for (uint32_t i = 0; i < 4; ++i) {
-    u[i] = have ? U[sl * 4 + i] : 0ull;
-    sU[wl * kK + sl * 4 + i] = u[i];
-  }
-  __syncthreads();
-  if (tid < kK && pl->P[tid] != kNone) {
-    const uint32_t p = pl->P[tid], r = (p >> 6) - w0, r2 = ((p - t.n) >> 6) - w0;
-    if (r < 16) {
-      atomicOr(&sCons[r], (unsigned long long)lbit(p));
-      atomicOr(&sKill[r], (unsigned long long)lbit(p));
-    }
-    if (r2 < 16) atomicOr(&sKill[r2], (unsigned long long)lbit(p - t.n));
-  }
+  if (w >= t.W || pl->rand == 0) return;
+  const uint64_t u = s.U[bp & 1u][size_t(w) * kK + lane];
+  const uint64_t gr = s.G[lane] & ~(lbit(lane) | (lbit(lane) - 1));   // pairs (lane, b > lane)
+  const uint32_t yc = s.Y[lane], p = pl->P[lane];
   uint64_t c0 = 0, c1 = 0, x = 0;   // (Y_old - Y_new) mod 4 in two planes; flips
-  if (have) {
-#pragma unroll 4
-    for (uint32_t cg = sl; cg < a.CG; cg += 16) {
-      const uint64_t *part = s.part + size_t(cg) * 3 * t.Wp + w;
-      const uint64_t v0 = part[0], v1 = part[t.Wp], v2 = part[2 * size_t(t.Wp)];
-      c1 ^= v1 ^ (c0 & v0);
-      c0 ^= v0;
-      x ^= v2;
-    }
+#pragma unroll 2
+  for (uint32_t cg = lane; cg < a.CG; cg += 64) {
+    const uint64_t *part = s.part + size_t(cg) * 3 * t.Wp + w;
+    const uint64_t v0 = part[0], v1 = part[t.Wp], v2 = part[2 * size_t(t.Wp)];
+    c1 ^= v1 ^ (c0 & v0);
+    c0 ^= v0;
+    x ^= v2;
   }
-  uint64_t gr[4], acc[4] = {0, 0, 0, 0};
+  // this word's rows among the pivot and the replaced rows
+  const bool isp = p != kNone && (p >> 6) == w, isq = p != kNone && ((p - t.n) >> 6) == w;
+  uint64_t cons = isp ? lbit(p) : 0ull, kill = cons | (isq ? lbit(p - t.n) : 0ull);
+  // the absorbed pivots' Y counts, and their Gram pairs
+  const uint64_t uy = (yc & 1u) ? u : 0ull;
+  c1 ^= c0 & uy;
+  c0 ^= uy;
+  if (yc & 2u) c1 ^= u;
+  uint64_t acc = 0;
 #pragma unroll
-  for (uint32_t i = 0; i < 4; ++i) {
-    const uint32_t ia = sl * 4 + i, yc = s.Y[ia];
-    const uint64_t uy = (yc & 1u) ? u[i] : 0ull;   // the absorbed pivots' Y counts
-    c1 ^= c0 & uy;
-    c0 ^= uy;
-    if (yc & 2u) c1 ^= u[i];
-    gr[i] = s.G[ia] & ~(lbit(ia) | (lbit(ia) - 1));   // pairs (ia, ib > ia)
-  }
-#pragma unroll 8
-  for (uint32_t ib = 0; ib < kK; ++ib) {
-    const uint64_t ub = sU[wl * kK + ib];
+  for (uint32_t i = 1; i < kK; ++i) acc = xor_if(acc, rdlane64(u, i), bit_mask(gr, i));
+  x ^= u & acc;
 #pragma unroll
-    for (uint32_t i = 0; i < 4; ++i) acc[i] = xor_if(acc[i], ub, bit_mask(gr[i], ib));
-  }
-#pragma unroll
-  for (uint32_t i = 0; i < 4; ++i) x ^= u[i] & acc[i];
-#pragma unroll
-  for (int off = 1; off < 16; off <<= 1) {
+  for (int off = 1; off < 64; off <<= 1) {
     const uint64_t b0 = __shfl_xor(c0, off), b1 = __shfl_xor(c1, off);
     c1 ^= b1 ^ (c0 & b0);
     c0 ^= b0;
     x ^= __shfl_xor(x, off);
   }
-  __syncthreads();
-  if (have && sl == 0) {
-    const uint64_t cons = sCons[wl], odd = c0 & ~cons;
+  if (__ballot(isp || isq)) {
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      cons |= __shfl_xor(cons, off);
+      kill |= __shfl_xor(kill, off);
+    }
+  }
+  if (lane == 0) {
+    const uint64_t odd = c0 & ~cons;
     if (odd) atomicAdd(&t.state[ST_ANOMALY], uint32_t(__popcll(odd)));
     s.H[w] = (c1 ^ x) & ~cons;
-    s.KW[w] = sKill[wl];
+    s.KW[w] = kill;
     s.CW[w] = cons;
   }
 }
@@ -359,17 +350,14 @@ __device__ __forceinline__ void prep_shots(const TabDev &t, const LrDev &s, cons
 }
 
 __global__ void __launch_bounds__(kPrepThreads) k_lr_prep(TabDev t, LrDev s, LrArgs a) {
-  __shared__ uint64_t s_mem[16 * kK + 64];
+  __shared__ uint64_t s_mem[kK + 1];
   __shared__ uint32_t s_a[kPrepThreads], s_b[kK];
   uint32_t wg = blockIdx.x;
   if (wg < a.nR) return prep_rows(t, s, a, wg, s_mem, s_b, s_a);
   wg -= a.nR;
   if (wg < a.nC) return prep_cols(t, s, a, wg, reinterpret_cast<unsigned long long *>(s_mem), s_b);
   wg -= a.nC;
-  if (wg < a.nH) {
-    unsigned long long *m = reinterpret_cast<unsigned long long *>(s_mem) + 16 * kK;
-    return prep_flips(t, s, a, wg, s_mem, m, m + 16);
-  }
+  if (wg < a.nH) return prep_flips(t, s, a, wg);
   wg -= a.nH;
   if (wg < a.nS) return prep_shots(t, s, a, wg);
   wg -= a.nS;
@@ -452,31 +440,115 @@ __device__ __forceinline__ void plan_search(const TabDev &t, const LrDev &s, Pla
   }
 }
 
-// The steps, by wave 0 (lane t ends with step t's results).
-template <int RW, int R>
-__device__ __forceinline__ void plan_steps(const TabDev &t, const LrDev &s, PlanRows<RW> &r, PlanShared &sh,
-                                           uint32_t kb, uint32_t total, uint32_t lane, uint32_t &P, uint64_t &RX,
-                                           uint64_t &RQ) {
-  uint64_t e[R];
-#pragma unroll
-  for (int i = 0; i < R; ++i) e[i] = uint32_t(i) * 64 + lane < total ? sh.we[i * 64 + lane] : 0ull;
-  const bool complete = total <= uint32_t(R) * 64;
-  P = kNone;
-  RX = RQ = 0;
-  for (uint32_t tt = 0; tt < kb; ++tt) {
-    uint64_t rb = 0;
-    uint32_t row = kNone;   // window position, or row | 1 << 31
+// Wave 0's state: the followed rows' bits in halves, and per lane t step t's
+// results (pos: window position of the pivot, or its row | 1 << 31).
+template <int R>
+struct PlanWindow {
+  uint32_t el[R], eh[R];
+};
+struct PlanSteps {
+  uint32_t pos, rxl, rxh;
+};
+
+__device__ __forceinline__ uint32_t sbit(uint32_t v, uint32_t t) {   // all ones where bit t (< 32) is set
+  return uint32_t(__builtin_amdgcn_sbfe(int(v), t, 1));
+}
+
+// Steps t0 .. of half H (bits 32 H ..) while a window row has the step's bit;
+// returns the first step without one, or t1.  A step is one chain of
+// dependent instructions: bit test, ballot, first lane, its bits by lane
+// read, XOR.
+template <int R, int H>
+__device__ __forceinline__ uint32_t plan_run(PlanWindow<R> &w, PlanSteps &st, uint32_t t0, uint32_t t1,
+                                             uint32_t lane) {
+  uint32_t t = t0;
+  auto apply = [&](uint32_t tb, uint32_t rl, uint32_t rh, uint32_t pos) {
+    const uint32_t xl = H ? rl : rl & ~(1u << tb), xh = H ? rh & ~(1u << tb) : rh;
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      const uint64_t bal = __ballot((e[i] >> tt) & 1u);
-      if (row == kNone && bal) {
-        const uint32_t l = uint32_t(__builtin_ctzll(bal));
-        row = uint32_t(i) * 64 + l;
-        rb = rdlane64(e[i], l);
-      }
+      const uint32_t m = sbit(H ? w.eh[i] : w.el[i], tb);
+      w.el[i] = bop3<LUT_AND_XOR>(xl, m, w.el[i]);
+      w.eh[i] = bop3<LUT_AND_XOR>(xh, m, w.eh[i]);
     }
-    if (row == kNone && !complete) {
-      sh.rx[lane] = RX;
+    const bool me = lane == t;
+    st.rxl = me ? xl : st.rxl;
+    st.rxh = me ? xh : st.rxh;
+    st.pos = me ? pos : st.pos;
+  };
+  for (;;) {
+    // the usual case alone in a loop of its own (taken branches are dear here)
+    uint64_t bal;
+    while ((bal = __ballot(sbit(H ? w.eh[0] : w.el[0], t & 31) != 0)) != 0) {
+      const uint32_t l = uint32_t(__builtin_ctzll(bal));
+      apply(t & 31, rdlane(w.el[0], l), rdlane(w.eh[0], l), l);
+      if (++t >= t1) return t;
+    }
+    uint32_t l = 0, pos = 0, rl = 0, rh = 0;
+#pragma unroll
+    for (int i = 1; i < R; ++i) {
+      if (bal) break;   // wave-uniform
+      bal = __ballot(sbit(H ? w.eh[i] : w.el[i], t & 31) != 0);
+      l = uint32_t(__builtin_ctzll(bal | (1ull << 63)));
+      rl = rdlane(w.el[i], l);
+      rh = rdlane(w.eh[i], l);
+      pos = uint32_t(i) * 64 + l;
+    }
+    if (bal == 0) return t;
+    apply(t & 31, rl, rh, pos);
+    if (++t >= t1) return t;
+  }
+}
+
+// A pivot found outside the window: the same updates.
+template <int R>
+__device__ __forceinline__ void plan_apply(PlanWindow<R> &w, PlanSteps &st, uint32_t t, uint32_t row, uint64_t rb,
+                                           uint32_t lane) {
+  const uint64_t rx = rb & ~lbit(t);
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const uint64_t v = xor_if(pair64(w.el[i], w.eh[i]), rx, bit_mask(pair64(w.el[i], w.eh[i]), t));
+    w.el[i] = uint32_t(v);
+    w.eh[i] = uint32_t(v >> 32);
+  }
+  if (lane == t) {
+    st.rxl = uint32_t(rx);
+    st.rxh = uint32_t(rx >> 32);
+    st.pos = row | 0x80000000u;
+  }
+}
+
+// Steps t0 .. kb - 1 following the first 64 R rows (replaying the steps before
+// t0).  Returns kb, or the step at which a larger window of `total` rows
+// would do without a search.
+template <int RW, int R>
+__device__ __forceinline__ uint32_t plan_steps(const TabDev &t, const LrDev &s, PlanRows<RW> &r, PlanShared &sh,
+                                               uint32_t t0, uint32_t kb, uint32_t total, uint32_t lane,
+                                               PlanSteps &st) {
+  PlanWindow<R> w;
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const uint64_t e = uint32_t(i) * 64 + lane < total ? sh.we[i * 64 + lane] : 0ull;
+    w.el[i] = uint32_t(e);
+    w.eh[i] = uint32_t(e >> 32);
+  }
+  for (uint32_t d = 0; d < t0; ++d) {
+    const uint64_t rx = pair64(rdlane(st.rxl, d), rdlane(st.rxh, d));
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const uint64_t e = pair64(w.el[i], w.eh[i]), v = xor_if(e, rx, bit_mask(e, d));
+      w.el[i] = uint32_t(v);
+      w.eh[i] = uint32_t(v >> 32);
+    }
+  }
+  uint32_t tt = t0;
+  while (tt < kb) {
+    if (tt < 32) tt = plan_run<R, 0>(w, st, tt, min(kb, 32u), lane);
+    if (tt >= 32 && tt < kb) tt = plan_run<R, 1>(w, st, tt, kb, lane);
+    if (tt == kb) break;
+    // no window row has the bit
+    if (total > uint32_t(R) * 64) {
+      if (total <= kWindow) return tt;
+      sh.rx[lane] = pair64(st.rxl, st.rxh);
       if (lane == 0) sh.cmd = tt + 1;
       __syncthreads();
       plan_search<RW>(t, s, r, sh, tt, 0, lane);
@@ -486,23 +558,12 @@ __device__ __forceinline__ void plan_steps(const TabDev &t, const LrDev &s, Plan
       const uint64_t bal = __ballot(cr != kNone);   // waves hold ascending rows
       if (bal) {
         const uint32_t l = uint32_t(__builtin_ctzll(bal));
-        row = rdlane(cr, l) | 0x80000000u;
-        rb = rdlane64(cv, l);
+        plan_apply<R>(w, st, tt, rdlane(cr, l), rdlane64(cv, l), lane);
       }
     }
-    if (row == kNone) continue;   // deterministic
-    const uint64_t rx = rb & ~lbit(tt);
-#pragma unroll
-    for (int i = 0; i < R; ++i) e[i] = xor_if(e[i], rx, bit_mask(e[i], tt));
-    // replaced row p - n: the pivot row's bits, then as any row
-    if (lane < tt) RQ = xor_if(RQ, rx, bit_mask(RQ, tt));
-    if (lane == tt) {
-      RQ = rb;
-      RX = rx;
-      P = row;
-    }
+    ++tt;   // without a pivot: deterministic
   }
-  if (P != kNone) P = (P & 0x80000000u) ? P & 0x7fffffffu : sh.wi[P];
+  return kb;
 }
 
 template <int RW>
@@ -560,18 +621,19 @@ __device__ __forceinline__ void plan_block(const TabDev &t, const LrDev &s, cons
       __syncthreads();
     }
   }
-  uint32_t P;
-  uint64_t RX, RQ;
-  // (between 129 and 512 rows all of them are followed: none is left to search)
-  if (total > 128 && total <= kWindow) plan_steps<RW, kWindow / 64>(t, s, r, sh, kb, total, lane, P, RX, RQ);
-  else plan_steps<RW, 2>(t, s, r, sh, kb, total, lane, P, RX, RQ);
+  PlanSteps st{kNone, 0, 0};
+  // 128 rows do in a dense tableau (64 random bits each); where they fall
+  // short and there are at most 512, all of them are followed
+  const uint32_t tt = plan_steps<RW, 2>(t, s, r, sh, 0, kb, total, lane, st);
+  if (tt < kb) plan_steps<RW, kWindow / 64>(t, s, r, sh, tt, kb, total, lane, st);
+  const uint32_t P = st.pos == kNone ? kNone : (st.pos & 0x80000000u) ? st.pos & 0x7fffffffu : sh.wi[st.pos];
+  const uint64_t RX = pair64(st.rxl, st.rxh);
   if (lane == 0) sh.cmd = 0;
   __syncthreads();
   LrPlan *pl = s.plan + (bn & 3u);
   const uint64_t rand = __ballot(P != kNone);
   pl->P[lane] = P;
   pl->RX[lane] = RX;
-  pl->RQ[lane] = RQ;
   if (lane < kb) {
     t.kind[base + lane] = P != kNone ? 1 : 0;
     if (P == kNone) s.dets[s.cnt[0] + uint32_t(__popcll(~rand & (lbit(lane) - 1)))] = base + lane;
@@ -775,7 +837,7 @@ __device__ __forceinline__ void lr_signs(const TabDev &t, const LrDev &s, const 
 }
 
 // Gram rows and Y counts of block b over the prep kernel's workgroups.
-__device__ __forceinline__ void lr_gram(const LrDev &s, const LrArgs &a, uint64_t *sg, uint32_t *sy) {
+__device__ __forceinline__ void lr_gram(const TabDev &t, const LrDev &s, const LrArgs &a, uint64_t *sg, uint32_t *sy) {
   const uint32_t tid = threadIdx.x, st = tid & 63, sl = tid >> 6;
   if (s.plan[a.b & 3u].rand == 0) return;
   if (tid < kK) {
@@ -792,6 +854,13 @@ __device__ __forceinline__ void lr_gram(const LrDev &s, const LrArgs &a, uint64_
   }
   atomicXor(reinterpret_cast<unsigned long long *>(&sg[st]), (unsigned long long)g);
   atomicAdd(&sy[st], y);
+  if (sl == 0) {   // the pivot rows' support
+    unsigned long long sup = 0;
+    for (uint32_t q = st; q < a.nC; q += 64) sup += s.Sp[q];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sup += __shfl_xor(sup, off);
+    if (st == 0) atomicAdd(reinterpret_cast<unsigned long long *>(t.state + ST_SUPPORT), sup);
+  }
   __syncthreads();
   if (tid < kK) {
     s.G[tid] = sg[tid];
@@ -832,7 +901,7 @@ __global__ void __launch_bounds__(kSweepThreads) k_lr_sweep(TabDev t, LrDev s, L
     return;
   }
   if (wg == 1) {
-    if (b >= 0 && b < nb) return lr_gram(s, a, sh.gram.g, sh.gram.y);
+    if (b >= 0 && b < nb) return lr_gram(t, s, a, sh.gram.g, sh.gram.y);
     if (b < 0)   // the pending signs were folded by the launch before this one
       for (uint32_t i = threadIdx.x; i < t.Wp; i += kSweepThreads) t.P[i] = 0;
     return;
@@ -973,6 +1042,7 @@ size_t lr_scratch_bind(const Dims &d, uint32_t num_cus, uint8_t *base, LrDev &s)
   s.BZ = reinterpret_cast<uint64_t *>(take(size_t(d.n) * 8));
   s.ME = reinterpret_cast<uint32_t *>(take(size_t(d.n) * 4));
   s.Gp = reinterpret_cast<uint64_t *>(take(size_t(h.nC) * kK * 8));
+  s.Sp = reinterpret_cast<unsigned long long *>(take(size_t(h.nC) * 8));
   s.Yp = reinterpret_cast<uint32_t *>(take(size_t(h.nC) * kK * 4));
   s.G = reinterpret_cast<uint64_t *>(take(kK * 8));
   s.Y = reinterpret_cast<uint32_t *>(take(kK * 4));
@@ -1011,7 +1081,7 @@ hipError_t launch_measure_lr(const TabDev &t, const LrDev &s, const uint32_t *de
     a.b = uint32_t(b);
     a.nR = b < nb ? div_up(t.W, 4) : 0;
     a.nC = b >= 0 && b < nb ? h.nC : 0;
-    a.nH = b > 0 ? div_up(t.W, 16) : 0;
+    a.nH = b > 0 ? div_up(t.W, 4) : 0;
     a.nS = b > 0 ? std::min(div_up(t.S, 4), 256u) : 0;
     a.nF = b < 0 ? std::min(div_up(size_t(t.Wp) * t.S, kPrepThreads), 256u) : 0;
     if (prof) prof->begin(PK_SELECT, st);
