@@ -130,6 +130,8 @@ struct cliff_ctx {
   hipEvent_t persist_ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   uint8_t *pscratch = nullptr;
   size_t pscratch_bytes = 0;
+  uint2 *gscratch = nullptr;     // decoded gate streams (at most kDecodeSteps steps)
+  size_t gscratch_steps = 0;
   int gate_mode = CLIFF_GATES_AUTO;
   int measure_mode = CLIFF_MEASURE_AUTO;
   uint64_t inject_abort_at = UINT64_MAX;   // test aid: see cliff_ctx_inject_abort
@@ -236,6 +238,7 @@ int cliff_ctx_destroy(cliff_ctx *c) {
   if (c->aux) (void)hipStreamSynchronize(c->aux);
   if (c->dev_ops) (void)hipFree(c->dev_ops);
   if (c->pscratch) (void)hipFree(c->pscratch);
+  if (c->gscratch) (void)hipFree(c->gscratch);
   if (c->pinned) (void)hipHostFree(c->pinned);
   if (c->upload_done) (void)hipEventDestroy(c->upload_done);
   if (c->aux) {
@@ -494,31 +497,147 @@ static int upload_commit(cliff_ctx *c, size_t words) {
   return CLIFF_OK;
 }
 
-// Upload [ops | layer offsets]; returns device pointers to both parts.
-static int upload_stream(cliff_ctx *c, const uint64_t *ops, size_t nops, const uint32_t *offs,
-                         size_t noffs, const uint64_t **dev_ops, const uint32_t **dev_offs) {
-  const size_t offs_words = (noffs + 1) / 2;
-  const size_t words = nops + offs_words;
+// Upload host arrays side by side, each from an 8-byte boundary; dev[i]
+// receives part i's device address.
+struct UploadPart {
+  const void *host;
+  size_t bytes;
+  const void **dev;
+};
+static int upload_parts(cliff_ctx *c, const UploadPart *parts, size_t count) {
+  size_t words = 0;
+  for (size_t i = 0; i < count; ++i) words += (parts[i].bytes + 7) / 8;
   if (words == 0) return CLIFF_OK;
   uint64_t *host = nullptr, *dev = nullptr;
   int rc = upload_reserve(c, words, &host, &dev);
   if (rc) return rc;
-  if (nops) memcpy(host, ops, nops * 8);
-  if (noffs) {
-    host[nops + offs_words - 1] = 0;
-    memcpy(host + nops, offs, noffs * 4);
+  size_t at = 0;
+  for (size_t i = 0; i < count; ++i) {
+    const size_t w = (parts[i].bytes + 7) / 8;
+    if (w) {
+      host[at + w - 1] = 0;
+      memcpy(host + at, parts[i].host, parts[i].bytes);
+    }
+    if (parts[i].dev) *parts[i].dev = dev + at;
+    at += w;
   }
-  rc = upload_commit(c, words);
+  return upload_commit(c, words);
+}
+
+// Upload [ops | layer offsets]; returns device pointers to both parts.
+static int upload_stream(cliff_ctx *c, const uint64_t *ops, size_t nops, const uint32_t *offs,
+                         size_t noffs, const uint64_t **dev_ops, const uint32_t **dev_offs) {
+  const void *po = nullptr, *pf = nullptr;
+  const UploadPart parts[2] = {{ops, nops * 8, &po}, {offs, noffs * 4, &pf}};
+  const int rc = upload_parts(c, parts, 2);
   if (rc) return rc;
-  if (dev_ops) *dev_ops = dev;
-  if (dev_offs) *dev_offs = reinterpret_cast<const uint32_t *>(dev + nops);
+  if (dev_ops && po) *dev_ops = static_cast<const uint64_t *>(po);
+  if (dev_offs && pf) *dev_offs = static_cast<const uint32_t *>(pf);
+  return CLIFF_OK;
+}
+
+// True while the context's stream is being captured (or cannot be asked): a
+// staged upload would be read again at replay, and context scratch may be
+// reallocated between capture and replay.
+static bool capturing(const cliff_ctx *c) {
+  if (!c->stream) return false;   // the default stream cannot be captured
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) return false;
+  (void)hipGetLastError();
+  return true;
+}
+
+// Decoded gate streams: layers in steps of 64 ops, each rounded up, at most
+// kDecodeSteps (256 MB) at a time.
+constexpr size_t kDecodeSteps = size_t(1) << 19;
+struct DecodePlan {
+  std::vector<uint32_t> at;      // layer l: steps at[l] .. at[l + 1]
+  uint32_t most = 0;             // of one layer
+  std::vector<uint64_t> sched;   // rounds (see launch_gates_decoded), steps counted from their segment's first
+  struct Segment {
+    uint32_t l0, l1;             // layers
+    size_t r0, r1;               // their rounds
+  };
+  std::vector<Segment> segs;     // as many layers each as the scratch holds
+  size_t total() const { return at.back(); }
+};
+// Steps of the largest layer (raised in *most) and of all; false where a
+// layer's or the total do not fit.
+static bool count_steps(const uint32_t *offs, uint32_t depth, uint32_t *most, size_t *total) {
+  size_t sum = 0;
+  uint32_t m = 0;
+  for (uint32_t l = 0; l < depth; ++l) {
+    const uint32_t s = uint32_t((uint64_t(offs[l + 1] - offs[l]) + 63) / 64);
+    m = std::max(m, s);
+    sum += s;
+  }
+  *most = std::max(*most, m);
+  *total = sum;
+  return m != 0 && sum <= kDecodeSteps;
+}
+// Layer starts; false when the stream is too short to pay for decoding it
+// (kDecodeMinDepth), or a layer or the count does not fit.
+static bool plan_steps(const uint32_t *offs, uint32_t depth, DecodePlan *p) {
+  if (depth < kDecodeMinDepth) return false;
+  p->at.resize(size_t(depth) + 1);
+  size_t at = 0;
+  p->most = 0;
+  for (uint32_t l = 0; l < depth; ++l) {
+    if (offs[l + 1] < offs[l]) return false;   // refused by the caller's own check
+    const uint32_t cnt = offs[l + 1] - offs[l], s = cnt / 64 + (cnt % 64 != 0);
+    p->at[l] = uint32_t(at);
+    p->most = std::max(p->most, s);
+    at += s;
+    if (at > 0xFFFFFFF0ull) return false;
+  }
+  p->at[depth] = uint32_t(at);
+  return p->most != 0 && p->most <= kDecodeSteps;
+}
+static void plan_rounds(DecodePlan *p, uint32_t waves) {
+  const uint32_t depth = uint32_t(p->at.size() - 1);
+  p->sched.clear();
+  p->segs.clear();
+  DecodePlan::Segment seg{0, 0, 0, 0};
+  for (uint32_t l = 0; l < depth; ++l) {
+    if (p->at[l + 1] - p->at[seg.l0] > kDecodeSteps) {
+      seg.l1 = l;
+      seg.r1 = p->sched.size();
+      p->segs.push_back(seg);
+      seg.l0 = l;
+      seg.r0 = seg.r1;
+    }
+    const uint32_t s0 = p->at[l] - p->at[seg.l0], s1 = p->at[l + 1] - p->at[seg.l0];
+    for (uint32_t s = s0; s < s1; s += waves) {
+      const uint32_t cnt = std::min(waves, s1 - s);
+      p->sched.push_back(uint64_t(s) | uint64_t(cnt | (s + cnt == s1 ? 256u : 0u)) << 32);
+    }
+  }
+  seg.l1 = depth;
+  seg.r1 = p->sched.size();
+  p->segs.push_back(seg);
+}
+static int ctx_gate_scratch(cliff_ctx *c, size_t steps, uint2 **base) {
+  if (c->gscratch_steps < steps) {
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    if (c->gscratch) HIP_TRY(hipFree(c->gscratch));
+    c->gscratch = nullptr;
+    c->gscratch_steps = 0;
+    const hipError_t e = hipMalloc(reinterpret_cast<void **>(&c->gscratch), steps * 512);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(CLIFF_ENOMEM, "decoded gate stream of %zu bytes: %s", steps * 512, hipGetErrorString(e));
+    }
+    c->gscratch_steps = steps;
+  }
+  *base = c->gscratch;
   return CLIFF_OK;
 }
 
 // Run an encoded gate stream: all layers in one launch when the 32-row LDS
 // slice of every column fits, otherwise one launch per layer.
 static int run_encoded(cliff_tab *t, const uint64_t *dev_ops, const uint32_t *host_offs,
-                       const uint32_t *dev_offs, uint32_t depth) {
+                       const uint32_t *dev_offs, uint32_t depth, const DecodePlan *plan = nullptr,
+                       uint32_t waves = 0, const uint32_t *dev_poffs = nullptr, const uint2 *dev_sched = nullptr) {
   for (uint32_t l = 0; l < depth; ++l)
     if (host_offs[l + 1] < host_offs[l])
       return fail(CLIFF_EINVAL, "layer offsets decrease at layer %u", l);
@@ -526,6 +645,21 @@ static int run_encoded(cliff_tab *t, const uint64_t *dev_ops, const uint32_t *ho
   const int mode = t->ctx->gate_mode;
   if (mode == CLIFF_GATES_FUSED && !(dev_offs && fused_gates_fit(t->d.n)))
     return fail(CLIFF_EINVAL, "fused gates need 8n <= %zu bytes of LDS (n = %u)", kFusedGateLds, t->d.n);
+  if (mode != CLIFF_GATES_PER_LAYER && dev_offs && plan && fused_gates_fit(t->d.n)) {
+    uint2 *dec = nullptr;
+    int rc = ctx_gate_scratch(t->ctx, std::min(plan->total(), kDecodeSteps) + kDecodeMaxWaves, &dec);
+    if (rc && rc != CLIFF_ENOMEM) return rc;
+    if (!rc) {
+      for (const DecodePlan::Segment &g : plan->segs) {
+        t->ctx->prof.begin(PK_GATE, st);
+        hipError_t e = launch_gates_decoded(t->dev, dev_ops, dev_offs + g.l0, dev_poffs + g.l0, dev_sched + g.r0, g.l1 - g.l0,
+                                            uint32_t(g.r1 - g.r0), plan->most, waves, dec - size_t(plan->at[g.l0]) * 64, dec, st);
+        t->ctx->prof.end(PK_GATE, st);
+        HIP_TRY(e);
+      }
+      return CLIFF_OK;
+    }
+  }
   if (mode != CLIFF_GATES_PER_LAYER && dev_offs && fused_gates_fit(t->d.n)) {
     t->ctx->prof.begin(PK_GATE, st);
     hipError_t e = launch_gates_fused(t->dev, dev_ops, dev_offs, depth, st);
@@ -543,6 +677,34 @@ static int run_encoded(cliff_tab *t, const uint64_t *dev_ops, const uint32_t *ho
   return CLIFF_OK;
 }
 
+// Upload a host stream (or, with host_ops NULL, the boundaries of one at
+// dev_ops) and run it.
+static int upload_and_run(cliff_tab *t, const uint64_t *host_ops, size_t nops, const uint64_t *dev_ops,
+                          const uint32_t *offs, uint32_t depth) {
+  cliff_ctx *c = t->ctx;
+  DecodePlan plan;
+  uint32_t waves = 0;
+  const bool fused = fused_gates_fit(t->d.n) && c->gate_mode != CLIFF_GATES_PER_LAYER;
+  const bool decode = fused && !capturing(c) && plan_steps(offs, depth, &plan);
+  if (decode) {
+    waves = std::min(plan.most, kDecodeMaxWaves);
+    plan_rounds(&plan, waves);
+  }
+  const void *dops = dev_ops, *doffs = nullptr, *dpoffs = nullptr, *dsched = nullptr;
+  if (host_ops || fused) {
+    const size_t nb = (size_t(depth) + 1) * 4;
+    const UploadPart parts[4] = {{host_ops, host_ops ? nops * 8 : 0, host_ops ? &dops : nullptr},
+                                 {offs, nb, &doffs},
+                                 {plan.at.data(), decode ? nb : 0, &dpoffs},
+                                 {plan.sched.data(), plan.sched.size() * 8, &dsched}};
+    int rc = upload_parts(c, parts, 4);
+    if (rc) return rc;
+  }
+  return run_encoded(t, static_cast<const uint64_t *>(dops), offs, static_cast<const uint32_t *>(doffs), depth,
+                     decode ? &plan : nullptr, waves, static_cast<const uint32_t *>(dpoffs),
+                     static_cast<const uint2 *>(dsched));
+}
+
 extern "C" int cliff_apply_layers(cliff_tab *t, const uint8_t *h, const uint8_t *s,
                                   const uint32_t *ctrl, const uint32_t *tgt, uint32_t npairs,
                                   uint32_t depth) {
@@ -556,11 +718,7 @@ extern "C" int cliff_apply_layers(cliff_tab *t, const uint8_t *h, const uint8_t 
   rc = cliff_encode_layers(t->d.n, h, s, ctrl, tgt, npairs, depth, ops.data(), nops, offs.data(), &nops);
   if (rc) return rc;
   DeviceGuard g(t->ctx->device);
-  const uint64_t *dops = nullptr;
-  const uint32_t *doffs = nullptr;
-  rc = upload_stream(t->ctx, ops.data(), ops.size(), offs.data(), offs.size(), &dops, &doffs);
-  if (rc) return rc;
-  return run_encoded(t, dops, offs.data(), doffs, depth);
+  return upload_and_run(t, ops.data(), ops.size(), nullptr, offs.data(), depth);
 }
 
 extern "C" int cliff_apply_encoded(cliff_tab *t, const uint64_t *dev_ops, const uint32_t *offs,
@@ -568,12 +726,7 @@ extern "C" int cliff_apply_encoded(cliff_tab *t, const uint64_t *dev_ops, const 
   if (!t || !offs || (!dev_ops && depth)) return fail(CLIFF_EINVAL, "cliff_apply_encoded: NULL argument");
   if (depth == 0) return CLIFF_OK;
   DeviceGuard g(t->ctx->device);
-  const uint32_t *doffs = nullptr;
-  if (fused_gates_fit(t->d.n) && t->ctx->gate_mode != CLIFF_GATES_PER_LAYER) {
-    int rc = upload_stream(t->ctx, nullptr, 0, offs, size_t(depth) + 1, nullptr, &doffs);
-    if (rc) return rc;
-  }
-  return run_encoded(t, dev_ops, offs, doffs, depth);
+  return upload_and_run(t, nullptr, 0, dev_ops, offs, depth);
 }
 
 // Gate list -> encoded layers.  Greedy layering: a gate joins the current
@@ -659,11 +812,7 @@ extern "C" int cliff_apply_gates(cliff_tab *t, const uint8_t *op, const uint32_t
   if (rc) return rc;
   if (ops.empty()) return CLIFF_OK;   // every gate cancelled out
   DeviceGuard g(t->ctx->device);
-  const uint64_t *dops = nullptr;
-  const uint32_t *doffs = nullptr;
-  rc = upload_stream(t->ctx, ops.data(), ops.size(), offs.data(), offs.size(), &dops, &doffs);
-  if (rc) return rc;
-  return run_encoded(t, dops, offs.data(), doffs, uint32_t(offs.size() - 1));
+  return upload_and_run(t, ops.data(), ops.size(), nullptr, offs.data(), uint32_t(offs.size() - 1));
 }
 
 // --------------------------------------------------------- many tableaux ---
@@ -737,11 +886,52 @@ static int run_many(cliff_tab *const *tabs, const std::vector<ManySource> &src, 
   size_t words = desc_words;
   for (const ManySource &m : src) words += (m.host_ops ? m.nops : 0) + (size_t(m.depth) + 2) / 2;
   DeviceGuard g(c->device);
+  // decoded: tableaux chunk_end[i - 1] .. chunk_end[i] share the scratch at a
+  // time (each its decoded stream, layer starts and rounds, in units of one
+  // step's 512 bytes), with waves for a usual layer
+  std::vector<size_t> stream_steps, own, chunk_end;   // scratch steps of tableau i: its stream, and with its plan
+  uint32_t waves = 1, most = 0, max_depth = 0;
+  uint2 *dec = nullptr;
+  bool decode = !capturing(c);
+  if (decode) {
+    own.resize(count);
+    stream_steps.resize(count);
+    size_t steps = 0, layers = 0;
+    for (size_t i = 0; decode && i < count; ++i) {
+      size_t total = 0;
+      decode = src[i].depth >= kDecodeMinDepth && count_steps(src[i].offs, src[i].depth, &most, &total);
+      stream_steps[i] = total;
+      steps += total;
+      layers += src[i].depth;
+      max_depth = std::max(max_depth, src[i].depth);
+    }
+    if (decode) {
+      waves = uint32_t(std::min<size_t>(4, std::max<size_t>(1, (steps + layers - 1) / layers)));
+      size_t held = 0, most_held = 0;
+      for (size_t i = 0; decode && i < count; ++i) {
+        const size_t bytes = align256((size_t(src[i].depth) + 1) * 4) + (stream_steps[i] / waves + src[i].depth + 64) * 8;
+        own[i] = stream_steps[i] + (bytes + 511) / 512;
+        decode = own[i] <= kDecodeSteps;
+        if (held + own[i] > kDecodeSteps) {
+          chunk_end.push_back(i);
+          held = 0;
+        }
+        held += own[i];
+        most_held = std::max(most_held, held);
+      }
+      chunk_end.push_back(count);
+      if (decode) {
+        const int rc = ctx_gate_scratch(c, most_held + kDecodeMaxWaves, &dec);
+        if (rc && rc != CLIFF_ENOMEM) return rc;
+        decode = rc == CLIFF_OK;
+      }
+    }
+  }
   uint64_t *host = nullptr, *dev = nullptr;
   int rc = upload_reserve(c, words, &host, &dev);
   if (rc) return rc;
   ManyDesc *hd = reinterpret_cast<ManyDesc *>(host);
-  size_t at = desc_words;
+  size_t at = desc_words, chunk = 0, dec_at = 0;
   for (size_t i = 0; i < count; ++i) {
     const ManySource &m = src[i];
     ManyDesc d{};
@@ -764,10 +954,33 @@ static int run_many(cliff_tab *const *tabs, const std::vector<ManySource> &src, 
     else reinterpret_cast<uint32_t *>(host + at)[0] = 0;
     d.offs = reinterpret_cast<const uint32_t *>(dev + at);
     at += ow;
+    if (decode) {
+      if (i == chunk_end[chunk]) {
+        ++chunk;
+        dec_at = 0;
+      }
+      d.dec = dec + dec_at * 64;
+      uint8_t *plan = reinterpret_cast<uint8_t *>(d.dec + stream_steps[i] * 64);
+      d.poffs = reinterpret_cast<uint32_t *>(plan);
+      d.sched = reinterpret_cast<uint2 *>(plan + align256((size_t(m.depth) + 1) * 4));
+      dec_at += own[i];
+    }
     hd[i] = d;
   }
   rc = upload_commit(c, words);
   if (rc) return rc;
+  if (decode) {
+    size_t i0 = 0;
+    for (size_t i1 : chunk_end) {
+      c->prof.begin(PK_GATE, c->stream);
+      hipError_t e = launch_gates_many_decoded(reinterpret_cast<const ManyDesc *>(dev) + i0, uint32_t(i1 - i0), max_n, rows,
+                                               max_depth, most, waves, c->stream);
+      c->prof.end(PK_GATE, c->stream);
+      HIP_TRY(e);
+      i0 = i1;
+    }
+    return CLIFF_OK;
+  }
   c->prof.begin(PK_GATE, c->stream);
   hipError_t e = launch_gates_many(reinterpret_cast<const ManyDesc *>(dev), uint32_t(count), max_n, rows,
                                    c->stream);
@@ -859,13 +1072,7 @@ static int measure_pass_lr(cliff_tab *t, const uint32_t *qubits, size_t cnt, uin
     dq = reinterpret_cast<uint32_t *>(sp);
     base = sp + qbytes;
   } else {
-    if (c->stream) {
-      hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-      if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return CLIFF_OK;
-      }
-    }
+    if (capturing(c)) return CLIFF_OK;
     int rc = ctx_persist_scratch(c, need, &base);
     if (rc == CLIFF_ENOMEM) return CLIFF_OK;
     if (rc) return rc;

@@ -188,12 +188,244 @@ __device__ __forceinline__ void fused_body(uint64_t *X, uint64_t *Z, uint64_t *P
   if (tid == 0 && nonzero(*s_r)) reinterpret_cast<T *>(P)[unit] ^= *s_r;   // this part of P is ours alone
 }
 
+// ---- decoded streams --------------------------------------------------------
+// For longer streams the op words are first decoded, once for all row groups,
+// into what a lane needs to work on LDS, each layer padded to whole waves:
+//   word 0: 8 x column a (bits 0..17) | code of a (bits 18..24)
+//   word 1: 8 x column b (bits 0..17) | code of b (bits 18..24) | two-qubit gate (bits 25..26)
+// Padding, malformed ops and the missing second qubit of a single-qubit op
+// refer to spare columns past the tableau's (identity, never written back), so
+// a step of the gate kernel has no test per lane.  Bound: instruction issue.
+// A wave issues one instruction in four cycles, and a step from an op word
+// took about 200 of them with its branches (decode, range checks, masks).
+// n = 1,500, 3,000 layers: 1,858 -> 1,304 us + 12 us to decode; n = 500 x 100
+// tableaux, 500 layers: 1,382 -> 1,134 + 149; n = 1,024, 100 layers: 60 -> 44;
+// n = 64: 34 -> 20; n = 10,000, 20 layers: 302 -> 281.
+constexpr uint32_t kSpareCols = 16;
+constexpr uint32_t kDecBits = (1u << 18) - 1;
+static_assert((kFusedGateLds / 8 + kSpareCols) * 8 <= kDecBits, "column offsets fit the decoded words");
+
+// Decodes the layers of tableau blockIdx.y: a wave a layer, blockIdx.z shares
+// out a layer's steps.  poffs: padded layer starts in steps of 64.
+__device__ __forceinline__ void decode_layers(const uint64_t *__restrict__ ops, const uint32_t *__restrict__ offs,
+                                              const uint32_t *__restrict__ poffs, uint32_t depth, uint32_t n,
+                                              uint2 *__restrict__ out) {
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t spare = 8 * (n + (lane & (kSpareCols - 1)));
+  for (uint32_t l = blockIdx.x * 4 + wave; l < depth; l += gridDim.x * 4) {
+    const uint32_t lo = offs[l], cnt = offs[l + 1] - lo, p0 = poffs[l];
+    for (uint32_t st = blockIdx.z; st * 64 < cnt; st += gridDim.z) {
+      const uint32_t i = st * 64 + lane;
+      const uint64_t op = i < cnt ? ops[lo + i] : ~0ull;
+      uint2 d = make_uint2(spare, spare);
+      if (op_valid(op, n)) {   // (~0 is not)
+        d.x = 8 * op_a(op) | op_ca(op) << 18;
+        if (op_pair(op) != PAIR_NONE) d.y = 8 * op_b(op) | op_cb(op) << 18 | op_pair(op) << 25;
+      }
+      out[size_t(p0 + st) * 64 + lane] = d;
+    }
+  }
+}
+__global__ void __launch_bounds__(256) k_decode_ops(const uint64_t *__restrict__ ops, const uint32_t *__restrict__ offs,
+                                                    const uint32_t *__restrict__ poffs, uint32_t depth, uint32_t n,
+                                                    uint2 *__restrict__ out) {
+  decode_layers(ops, offs, poffs, depth, n, out);
+}
+// Steps and rounds (decoded_body) of every tableau's layers, one workgroup a
+// tableau: each thread a run of layers, run totals scanned over the workgroup.
+__global__ void __launch_bounds__(1024) k_plan_many(const ManyDesc *__restrict__ descs, uint32_t waves) {
+  __shared__ uint32_t s_st[1024], s_rd[1024];
+  const ManyDesc d = descs[blockIdx.x];
+  const uint32_t tid = threadIdx.x, per = (d.depth + 1023) / 1024;
+  const uint32_t l0 = min(d.depth, tid * per), l1 = min(d.depth, l0 + per);
+  auto steps_of = [&](uint32_t l) -> uint32_t { return (d.offs[l + 1] - d.offs[l] + 63) / 64; };
+  uint32_t st = 0, rd = 0;
+  for (uint32_t l = l0; l < l1; ++l) {
+    const uint32_t c = steps_of(l);
+    st += c;
+    rd += (c + waves - 1) / waves;
+  }
+  s_st[tid] = st;
+  s_rd[tid] = rd;
+  __syncthreads();
+  for (uint32_t off = 1; off < 1024; off <<= 1) {
+    const uint32_t a = tid >= off ? s_st[tid - off] : 0u, b = tid >= off ? s_rd[tid - off] : 0u;
+    __syncthreads();
+    s_st[tid] += a;
+    s_rd[tid] += b;
+    __syncthreads();
+  }
+  uint32_t at = s_st[tid] - st, r = s_rd[tid] - rd;
+  for (uint32_t l = l0; l < l1; ++l) {
+    const uint32_t c = steps_of(l);
+    d.poffs[l] = at;
+    for (uint32_t k = 0; k < c; k += waves) {
+      const uint32_t cnt = min(waves, c - k);
+      d.sched[r++] = make_uint2(at + k, cnt | (k + cnt == c ? 256u : 0u));
+    }
+    at += c;
+  }
+  if (tid == 1023) d.poffs[d.depth] = s_rd[1023];   // the number of rounds
+}
+__global__ void __launch_bounds__(256) k_decode_many(const ManyDesc *__restrict__ descs) {
+  const ManyDesc d = descs[blockIdx.y];
+  decode_layers(d.ops, d.offs, d.poffs, d.depth, d.n, d.dec);
+}
+
+// x and z of a row group's columns in LDS, by a column's offset in the
+// decoded words.  32-row groups keep a column's two words side by side (one
+// 8-byte access each way); wider ones keep two planes (16- and 32-byte
+// accesses at random columns collide on the banks).
+template <typename T>
+struct GroupLds {
+  unsigned char *x, *z;
+  __device__ GroupLds(void *mem, uint32_t cols) : x(reinterpret_cast<unsigned char *>(mem)), z(x + cols * sizeof(T)) {}
+  __device__ void get(uint32_t off, T &vx, T &vz) const {
+    vx = *reinterpret_cast<const T *>(x + off * (sizeof(T) / 8));
+    vz = *reinterpret_cast<const T *>(z + off * (sizeof(T) / 8));
+  }
+  __device__ void put(uint32_t off, T vx, T vz) const {
+    *reinterpret_cast<T *>(x + off * (sizeof(T) / 8)) = vx;
+    *reinterpret_cast<T *>(z + off * (sizeof(T) / 8)) = vz;
+  }
+};
+template <>
+struct GroupLds<uint32_t> {
+  unsigned char *xz;
+  __device__ GroupLds(void *mem, uint32_t) : xz(reinterpret_cast<unsigned char *>(mem)) {}
+  __device__ void get(uint32_t off, uint32_t &vx, uint32_t &vz) const {
+    const uint2 v = *reinterpret_cast<const uint2 *>(xz + off);
+    vx = v.x;
+    vz = v.y;
+  }
+  __device__ void put(uint32_t off, uint32_t vx, uint32_t vz) const {
+    *reinterpret_cast<uint2 *>(xz + off) = make_uint2(vx, vz);
+  }
+};
+
+template <typename T>
+__device__ __forceinline__ void apply_decoded(uint2 d, const GroupLds<T> &g, T &racc) {
+  const uint32_t a = d.x & kDecBits, b = d.y & kDecBits;
+  T xa, za, xb, zb;
+  g.get(a, xa, za);
+  g.get(b, xb, zb);
+  if (__ballot(((d.x | d.y) & (0x7fu << 18)) != 0)) {   // (layers of two-qubit gates alone have none)
+    sq_apply((d.x >> 18) & 0x7fu, xa, za, racc);
+    sq_apply((d.y >> 18) & 0x7fu, xb, zb, racc);
+  }
+  // two-qubit gates under lane masks: CNOT alone where the wave has no other
+  const T mc = mask_if<T>((d.y >> 25) & ~(d.y >> 26) & 1u);
+  if (__ballot((d.y >> 26) != 0) == 0) {
+    racc = bop3<LUT_AND_XOR>(bop3<LUT_AND_ANDN>(xa, zb, xb ^ za), mc, racc);
+    xb = bop3<LUT_AND_XOR>(xa, mc, xb);
+    za = bop3<LUT_AND_XOR>(zb, mc, za);
+  } else {
+    const T mz = mask_if<T>((d.y >> 26) & ~(d.y >> 25) & 1u), ms = mask_if<T>((d.y >> 25) & (d.y >> 26) & 1u);
+    racc = bop3<LUT_AND_XOR>(bop3<LUT_AND_ANDN>(xa, zb, xb ^ za), mc, racc);
+    racc = bop3<LUT_AND_XOR>(bop3<LUT_AND3>(xa, xb, za ^ zb), mz, racc);
+    const T nxb = bop3<LUT_AND_XOR>(xa, mc, xb), nza = bop3<LUT_AND_XOR>(zb, mc, bop3<LUT_AND_XOR>(xb, mz, za));
+    const T nzb = bop3<LUT_AND_XOR>(xa, mz, zb);
+    const T sx = (xa ^ nxb) & ms, sz = (nza ^ nzb) & ms;
+    xa ^= sx;
+    xb = nxb ^ sx;
+    za = nza ^ sz;
+    zb = nzb ^ sz;
+  }
+  g.put(b, xb, zb);
+  g.put(a, xa, za);
+}
+
+// All layers of a decoded stream on one row group, as fused_body does, in
+// rounds of up to one step of 64 ops per wave (a layer takes one or more).
+// sched[r]: first step of the round, and its number of steps | 256 where the
+// layer ends with it; 64 rounds' entries sit in a wave's lanes.  A wave loads
+// its next kOpAhead rounds' ops ahead.
+constexpr int kOpAhead = 4;
+template <typename T>
+__device__ __forceinline__ void decoded_body(uint64_t *X, uint64_t *Z, uint64_t *P, uint32_t n, uint32_t Wp,
+                                             const uint2 *__restrict__ dec, const uint2 *__restrict__ sched,
+                                             uint32_t rounds, uint32_t unit, const GroupLds<T> &g, T *s_r) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63, nthr = blockDim.x;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool alone = nthr == 64;   // (one wave's LDS accesses are in order)
+  const size_t cs = size_t(Wp) * 8 / sizeof(T);
+  const T *XT = reinterpret_cast<const T *>(X);
+  const T *ZT = reinterpret_cast<const T *>(Z);
+  for (uint32_t j = tid; j < n; j += nthr) g.put(8 * j, XT[j * cs + unit], ZT[j * cs + unit]);
+  if (tid == 0) *s_r = T{};
+  const GlobalU64 *gsched = (const GlobalU64 *)sched;
+  const GlobalU64 *gdec = (const GlobalU64 *)dec + size_t(wave) * 64 + lane;
+  auto entries = [&](uint32_t r) -> uint2 {   // of rounds r + lane (none past the last)
+    const uint64_t v = r + lane < rounds ? uint64_t(gsched[r + lane]) : 0ull;
+    return make_uint2(uint32_t(v), uint32_t(v >> 32));
+  };
+  uint64_t ring[kOpAhead];
+  uint32_t ctl[kOpAhead];
+  auto load = [&](int d, uint2 e, uint32_t i) {
+    const uint32_t first = uint32_t(__builtin_amdgcn_readlane(int(e.x), int(i)));
+    ctl[d] = uint32_t(__builtin_amdgcn_readlane(int(e.y), int(i)));
+    // (a wave past the round's steps loads from the stream's start: in range,
+    // since the stream holds a round of every wave; see the launch)
+    ring[d] = gdec[size_t(wave < (ctl[d] & 255u) ? first : 0u) * 64];
+  };
+  uint2 e = entries(0);
+#pragma unroll
+  for (int d = 0; d < kOpAhead; ++d) load(d, e, uint32_t(d));
+  __syncthreads();
+  T racc{};
+  for (uint32_t r0 = 0; r0 < rounds; r0 += 64) {
+    e = entries(r0 + kOpAhead);
+    for (uint32_t q = 0; q < 64; q += kOpAhead) {
+#pragma unroll
+      for (int d = 0; d < kOpAhead; ++d) {
+        const uint64_t v = ring[d];
+        const uint32_t c = ctl[d];
+        load(d, e, q + uint32_t(d));
+        if (wave < (c & 255u)) apply_decoded(make_uint2(uint32_t(v), uint32_t(v >> 32)), g, racc);
+        if ((c & 256u) && !alone) lds_barrier();
+      }
+      if (r0 + q + kOpAhead >= rounds) break;
+    }
+  }
+  if (nonzero(racc)) lds_xor(s_r, racc);
+  __syncthreads();
+  T *XW = reinterpret_cast<T *>(X);
+  T *ZW = reinterpret_cast<T *>(Z);
+  for (uint32_t j = tid; j < n; j += nthr) {
+    T vx, vz;
+    g.get(8 * j, vx, vz);
+    XW[j * cs + unit] = vx;
+    ZW[j * cs + unit] = vz;
+  }
+  if (tid == 0 && nonzero(*s_r)) reinterpret_cast<T *>(P)[unit] ^= *s_r;   // this part of P is ours alone
+}
+
+constexpr uint32_t kFusedMaxThreads = 1024;
+// (the sign word sits past the columns, so that the columns start at LDS
+// address 0 and a decoded offset is an address)
+__global__ void __launch_bounds__(kFusedMaxThreads) k_gates_decoded(TabDev t, const uint2 *__restrict__ dec,
+                                                                   const uint2 *__restrict__ sched, uint32_t rounds) {
+  extern __shared__ uint64_t lds_u64[];
+  const GroupLds<uint32_t> g(lds_u64, t.n + kSpareCols);
+  decoded_body<uint32_t>(t.X, t.Z, t.P, t.n, t.Wp, dec, sched, rounds, blockIdx.x, g,
+                         reinterpret_cast<uint32_t *>(lds_u64 + t.n + kSpareCols));
+}
+template <typename T>
+__global__ void __launch_bounds__(256) k_gates_many_decoded(const ManyDesc *__restrict__ descs) {
+  extern __shared__ uint64_t lds_u64[];
+  const ManyDesc d = descs[blockIdx.y];
+  constexpr uint32_t kBits = 8 * sizeof(T);
+  if (blockIdx.x >= (2 * d.n + kBits - 1) / kBits) return;   // group past the tableau's 2n rows
+  const GroupLds<T> g(lds_u64, d.n + kSpareCols);
+  decoded_body<T>(d.X, d.Z, d.P, d.n, d.Wp, d.dec, d.sched, d.poffs[d.depth], blockIdx.x, g,
+                  reinterpret_cast<T *>(reinterpret_cast<unsigned char *>(lds_u64) + 2 * (d.n + kSpareCols) * sizeof(T)));
+}
+
 // One tableau, 32-row groups (twice as many workgroups as 64-row ones: a
 // single tableau is latency-bound, not throughput-bound).  Launched with up
 // to 1024 threads: 16 waves share a group's layer work, so that more LDS
 // round trips are in flight per SIMD (n = 10,000, 20 layers: 30 % less time
 // than with 256 threads).
-constexpr uint32_t kFusedMaxThreads = 1024;
 __global__ void __launch_bounds__(kFusedMaxThreads) k_gates_fused(TabDev t, const uint64_t *__restrict__ ops,
                                                      const uint32_t *__restrict__ offs, uint32_t depth) {
   extern __shared__ uint64_t lds_u64[];
@@ -377,6 +609,57 @@ hipError_t launch_gates_many(const ManyDesc *dev_descs, uint32_t count, uint32_t
     k_gates_many<uint64_t><<<grid, 256, lds, st>>>(dev_descs);
   else
     k_gates_many<uint32_t><<<grid, 256, lds, st>>>(dev_descs);
+  return hipGetLastError();
+}
+
+static hipError_t allow_gate_lds(const void *fn, size_t more) {
+  return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(kFusedGateLds + more));
+}
+
+// Workgroups of four waves for `depth` layers.
+static uint32_t decode_grid(uint32_t depth, uint32_t most) { return depth / 4 + 1 < most ? depth / 4 + 1 : most; }
+
+hipError_t launch_gates_decoded(const TabDev &t, const uint64_t *ops, const uint32_t *dev_offs,
+                                const uint32_t *dev_poffs, const uint2 *dev_sched, uint32_t depth, uint32_t rounds,
+                                uint32_t max_steps, uint32_t waves, uint2 *dec, uint2 *dec_base, hipStream_t st) {
+  if (rounds == 0) return hipSuccess;
+  constexpr size_t kMore = kSpareCols * 8 + 8;
+  static const hipError_t attr = allow_gate_lds(reinterpret_cast<const void *>(k_gates_decoded), kMore);
+  if (attr != hipSuccess) return attr;
+  const uint32_t gx = decode_grid(depth, 4096), gz = (max_steps + 3) / 4;
+  k_decode_ops<<<dim3(gx, 1, gz), 256, 0, st>>>(ops, dev_offs, dev_poffs, depth, t.n, dec);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  k_gates_decoded<<<(2 * t.n + 31) / 32, 64 * waves, size_t(t.n) * 8 + kMore, st>>>(t, dec_base, dev_sched, rounds);
+  return hipGetLastError();
+}
+
+hipError_t launch_gates_many_decoded(const ManyDesc *dev_descs, uint32_t count, uint32_t max_n, uint32_t rows,
+                                     uint32_t max_depth, uint32_t max_steps, uint32_t waves, hipStream_t st) {
+  if (count == 0 || max_depth == 0 || max_steps == 0) return hipSuccess;
+  const int v = rows == 128 ? 2 : rows == 64 ? 1 : 0;
+  static const void *const fns[3] = {reinterpret_cast<const void *>(k_gates_many_decoded<uint32_t>),
+                                     reinterpret_cast<const void *>(k_gates_many_decoded<uint64_t>),
+                                     reinterpret_cast<const void *>(k_gates_many_decoded<U128>)};
+  constexpr size_t kMore = kSpareCols * 32 + 16;
+  static const hipError_t attr[3] = {allow_gate_lds(fns[0], kMore), allow_gate_lds(fns[1], kMore),
+                                     allow_gate_lds(fns[2], kMore)};
+  if (attr[v] != hipSuccess) return attr[v];
+  const uint32_t gx = decode_grid(max_depth, 256), gz = (max_steps + 3) / 4;
+  k_plan_many<<<count, 1024, 0, st>>>(dev_descs, waves);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  k_decode_many<<<dim3(gx, count, gz), 256, 0, st>>>(dev_descs);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const size_t lds = 2 * size_t(max_n + kSpareCols) * (rows / 8) + 16;
+  const dim3 grid((2 * max_n + rows - 1) / rows, count);
+  if (v == 2)
+    k_gates_many_decoded<U128><<<grid, 64 * waves, lds, st>>>(dev_descs);
+  else if (v == 1)
+    k_gates_many_decoded<uint64_t><<<grid, 64 * waves, lds, st>>>(dev_descs);
+  else
+    k_gates_many_decoded<uint32_t><<<grid, 64 * waves, lds, st>>>(dev_descs);
   return hipGetLastError();
 }
 

@@ -1,0 +1,112 @@
+"""Decoded gate streams (16 layers and more) at the layer sizes where they can
+go wrong, bit for bit against the CPU oracle: the shortest stream that is
+decoded and the longest that is not, empty layers, layers of one gate, of one
+wave's 64 ops and one more, of more than 16 waves, every named gate, ops that
+a kernel has to skip, and row groups of every width."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2408_00384_amd import Context
+    c = Context(0)
+    yield c
+    c.close()
+
+
+def _stream(n, sizes, seed):
+    """A layer of sizes[l] ops on distinct qubits each (two-qubit ones while
+    the qubits last); every fifth layer has CNOTs alone.  Returns the device
+    words with one op out of range after every layer, the layer boundaries and
+    the gates as a list."""
+    from paper_2408_00384_amd import cliff_encode_gates
+    rng = np.random.default_rng([93, n, seed])
+    words, offs, gates = [], [0], []
+    for l, k in enumerate(sizes):
+        perm = rng.permutation(n)
+        pairs = min(k, n - k)            # 2 pairs + (k - pairs) <= n
+        if pairs < 1 or (l % 5 and k > 1):
+            pairs = pairs // 2
+        two = np.array([2, 7, 8], np.uint8)            # CNOT, CZ, SWAP
+        one = np.array([0, 1, 3, 4, 5, 6], np.uint8)   # H, S, S^-1, X, Y, Z
+        ops = np.concatenate([np.full(pairs, 2, np.uint8) if l % 5 == 0 else rng.choice(two, pairs),
+                              rng.choice(one, k - pairs)]).astype(np.uint8)
+        a = np.concatenate([perm[:pairs], perm[2 * pairs:pairs + k]]).astype(np.uint32)
+        b = np.concatenate([perm[pairs:2 * pairs], a[pairs:]]).astype(np.uint32)
+        w = np.concatenate([cliff_encode_gates(n, ops, a, b)[0] if k else np.empty(0, np.uint64),
+                            np.array([n], np.uint64)])
+        words.append(w)
+        offs.append(offs[-1] + len(w))
+        gates.append((ops, a, b))
+    return (np.concatenate(words), np.array(offs, np.uint32),
+            tuple(np.concatenate([g[i] for g in gates]) for i in range(3)))
+
+
+def _ref(n, gates, times=1):
+    t = oracle.Tableau(n)
+    for _ in range(times):
+        t.apply_gates(*gates)
+    return t.get()
+
+
+def _same(got, ref):
+    return all(np.array_equal(np.asarray(g).reshape(np.shape(r)), r) for g, r in zip(got, ref))
+
+
+def _upload(words):
+    import torch
+    d = torch.from_numpy(words.view(np.int64)).to("cuda:0")
+    torch.cuda.synchronize()
+    return d
+
+
+# sizes count the ops that act: 63 and the skipped one fill a step of 64
+@pytest.mark.parametrize("n,sizes", [
+    (1, [1] * 16), (2, [1, 0, 2] * 5), (2, [1, 0, 2] * 6), (130, [63, 64, 65, 0, 1, 130, 127, 128] * 2),
+    (130, [40] * 67 + [0] * 5 + [100] * 60), (1500, [1023, 1024, 1025, 1, 0, 1500, 700, 64] * 2),
+    (20352, [20352, 0, 1, 16383, 12000, 64, 63, 5] * 2)])
+def test_one_tableau(ctx, n, sizes):
+    from paper_2408_00384_amd import DeviceTableau, cliff_apply_encoded
+    words, offs, gates = _stream(n, sizes, 0)
+    dev = _upload(words)
+    t = DeviceTableau(ctx, n, 1)
+    for _ in range(2):   # (the second stream starts from the first one's signs)
+        cliff_apply_encoded(t.handle, dev.data_ptr(), offs)
+    if n <= 2000:
+        assert _same(t.export(), _ref(n, gates, 2))
+    else:                # the layers one launch each
+        from paper_2408_00384_amd import GATES_AUTO, GATES_PER_LAYER, cliff_ctx_set_gate_mode
+        u = DeviceTableau(ctx, n, 1)
+        cliff_ctx_set_gate_mode(ctx.handle, GATES_PER_LAYER)
+        try:
+            for _ in range(2):
+                cliff_apply_encoded(u.handle, dev.data_ptr(), offs)
+        finally:
+            cliff_ctx_set_gate_mode(ctx.handle, GATES_AUTO)
+        rows = np.concatenate([np.arange(0, 2 * n, 997), [2 * n - 1]]).astype(np.uint32)
+        assert _same(t.export_rows(rows), u.export_rows(rows))
+        u.close()
+    t.close()
+
+
+@pytest.mark.parametrize("rows", [32, 64, 128])
+@pytest.mark.parametrize("short", [16, 15])
+def test_many_tableaux(ctx, rows, short):
+    """Tableaux of 1 to 700 qubits and streams of 15 or 16 to 1,300 layers."""
+    from paper_2408_00384_amd import DeviceTableau, cliff_apply_encoded_many
+    shapes = [(1, [1] * short), (33, [33, 0, 7, 20] * 5), (130, [63, 64, 65, 130] * 8),
+              (64, [1, 30] * 650), (700, [700, 1, 0, 320, 319, 63, 64] * 3)]
+    streams = [_stream(n, sizes, 1 + i) for i, (n, sizes) in enumerate(shapes)]
+    dev = [_upload(w) for w, _, _ in streams]
+    tabs = [DeviceTableau(ctx, n, 1) for n, _ in shapes]
+    for _ in range(2):
+        cliff_apply_encoded_many([t.handle for t in tabs], [d.data_ptr() for d in dev],
+                                 [o for _, o, _ in streams], rows)
+    for t, (n, _), (_, _, gates) in zip(tabs, shapes, streams):
+        assert _same(t.export(), _ref(n, gates, 2)), "n = %d" % n
+        t.close()
