@@ -18,8 +18,10 @@
 namespace cliff {
 
 // |0...0>: X[j] has bit j (destabilizer j = X_j), Z[j] has bit n+j
-// (stabilizer n+j = Z_j); signs and pending flips zero.  One pass, no memset,
-// so the launch is safe inside a captured graph.
+// (stabilizer n+j = Z_j); signs, pending flips and the measurement state zero.
+// One pass, no memset, so the launch is safe inside a captured graph; at small
+// n a launch of its own for the state would cost as much again (100 tableaux
+// of n = 500: 414 -> 200 us).
 __global__ void __launch_bounds__(256) k_init_zero(TabDev t) {
   const size_t ncol = size_t(t.n) * t.Wp;
   const size_t stride = size_t(gridDim.x) * blockDim.x;
@@ -32,6 +34,7 @@ __global__ void __launch_bounds__(256) k_init_zero(TabDev t) {
   const size_t nr = size_t(t.Wp) * t.S;
   for (size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x; i < nr; i += stride) t.R[i] = 0;
   for (size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x; i < t.Wp; i += stride) t.P[i] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < kStateWords) t.state[threadIdx.x] = 0;
   if (blockIdx.x == 0 && threadIdx.x == 0) *t.abort_flag = 0;
 }
 
@@ -537,9 +540,7 @@ static inline uint32_t grid_for(size_t items, uint32_t block, uint32_t cap = 409
 hipError_t launch_init_zero(const TabDev &t, hipStream_t st) {
   const size_t items = size_t(t.n) * t.Wp;
   k_init_zero<<<grid_for(items, 256), 256, 0, st>>>(t);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_clear_state(t, st);
+  return hipGetLastError();
 }
 
 hipError_t launch_clear_state(const TabDev &t, hipStream_t st) {
