@@ -553,7 +553,7 @@ constexpr size_t kDecodeSteps = size_t(1) << 19;
 struct DecodePlan {
   std::vector<uint32_t> at;      // layer l: steps at[l] .. at[l + 1]
   uint32_t most = 0;             // of one layer
-  std::vector<uint64_t> sched;   // rounds (see launch_gates_decoded), steps counted from their segment's first
+  std::vector<uint32_t> sched;   // rounds (see launch_gates_decoded)
   struct Segment {
     uint32_t l0, l1;             // layers
     size_t r0, r1;               // their rounds
@@ -609,7 +609,7 @@ static void plan_rounds(DecodePlan *p, uint32_t waves) {
     const uint32_t s0 = p->at[l] - p->at[seg.l0], s1 = p->at[l + 1] - p->at[seg.l0];
     for (uint32_t s = s0; s < s1; s += waves) {
       const uint32_t cnt = std::min(waves, s1 - s);
-      p->sched.push_back(uint64_t(s) | uint64_t(cnt | (s + cnt == s1 ? 256u : 0u)) << 32);
+      p->sched.push_back(cnt | (s + cnt == s1 ? kRoundEnds : 0u));
     }
   }
   seg.l1 = depth;
@@ -637,7 +637,7 @@ static int ctx_gate_scratch(cliff_ctx *c, size_t steps, uint2 **base) {
 // slice of every column fits, otherwise one launch per layer.
 static int run_encoded(cliff_tab *t, const uint64_t *dev_ops, const uint32_t *host_offs,
                        const uint32_t *dev_offs, uint32_t depth, const DecodePlan *plan = nullptr,
-                       uint32_t waves = 0, const uint32_t *dev_poffs = nullptr, const uint2 *dev_sched = nullptr) {
+                       uint32_t waves = 0, const uint32_t *dev_poffs = nullptr, const uint32_t *dev_sched = nullptr) {
   for (uint32_t l = 0; l < depth; ++l)
     if (host_offs[l + 1] < host_offs[l])
       return fail(CLIFF_EINVAL, "layer offsets decrease at layer %u", l);
@@ -696,13 +696,13 @@ static int upload_and_run(cliff_tab *t, const uint64_t *host_ops, size_t nops, c
     const UploadPart parts[4] = {{host_ops, host_ops ? nops * 8 : 0, host_ops ? &dops : nullptr},
                                  {offs, nb, &doffs},
                                  {plan.at.data(), decode ? nb : 0, &dpoffs},
-                                 {plan.sched.data(), plan.sched.size() * 8, &dsched}};
+                                 {plan.sched.data(), plan.sched.size() * 4, &dsched}};
     int rc = upload_parts(c, parts, 4);
     if (rc) return rc;
   }
   return run_encoded(t, static_cast<const uint64_t *>(dops), offs, static_cast<const uint32_t *>(doffs), depth,
                      decode ? &plan : nullptr, waves, static_cast<const uint32_t *>(dpoffs),
-                     static_cast<const uint2 *>(dsched));
+                     static_cast<const uint32_t *>(dsched));
 }
 
 extern "C" int cliff_apply_layers(cliff_tab *t, const uint8_t *h, const uint8_t *s,
@@ -909,7 +909,7 @@ static int run_many(cliff_tab *const *tabs, const std::vector<ManySource> &src, 
       waves = uint32_t(std::min<size_t>(4, std::max<size_t>(1, (steps + layers - 1) / layers)));
       size_t held = 0, most_held = 0;
       for (size_t i = 0; decode && i < count; ++i) {
-        const size_t bytes = align256((size_t(src[i].depth) + 1) * 4) + (stream_steps[i] / waves + src[i].depth + 64) * 8;
+        const size_t bytes = align256((size_t(src[i].depth) + 1) * 4) + (stream_steps[i] / waves + src[i].depth + 64) * 4;
         own[i] = stream_steps[i] + (bytes + 511) / 512;
         decode = own[i] <= kDecodeSteps;
         if (held + own[i] > kDecodeSteps) {
@@ -962,7 +962,7 @@ static int run_many(cliff_tab *const *tabs, const std::vector<ManySource> &src, 
       d.dec = dec + dec_at * 64;
       uint8_t *plan = reinterpret_cast<uint8_t *>(d.dec + stream_steps[i] * 64);
       d.poffs = reinterpret_cast<uint32_t *>(plan);
-      d.sched = reinterpret_cast<uint2 *>(plan + align256((size_t(m.depth) + 1) * 4));
+      d.sched = reinterpret_cast<uint32_t *>(plan + align256((size_t(m.depth) + 1) * 4));
       dec_at += own[i];
     }
     hd[i] = d;

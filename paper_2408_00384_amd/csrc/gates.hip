@@ -194,37 +194,58 @@ __device__ __forceinline__ void fused_body(uint64_t *X, uint64_t *Z, uint64_t *P
 // ---- decoded streams --------------------------------------------------------
 // For longer streams the op words are first decoded, once for all row groups,
 // into what a lane needs to work on LDS, each layer padded to whole waves:
-//   word 0: 8 x column a (bits 0..17) | code of a (bits 18..24)
-//   word 1: 8 x column b (bits 0..17) | code of b (bits 18..24) | two-qubit gate (bits 25..26)
-// Padding, malformed ops and the missing second qubit of a single-qubit op
-// refer to spare columns past the tableau's (identity, never written back), so
-// a step of the gate kernel has no test per lane.  Bound: instruction issue.
-// A wave issues one instruction in four cycles, and a step from an op word
-// took about 200 of them with its branches (decode, range checks, masks).
-// n = 1,500, 3,000 layers: 1,858 -> 1,304 us + 12 us to decode; n = 500 x 100
-// tableaux, 500 layers: 1,382 -> 1,134 + 149; n = 1,024, 100 layers: 60 -> 44;
-// n = 64: 34 -> 20; n = 10,000, 20 layers: 302 -> 281.
+//   word 0: LDS address of column a (bits 0..17) | code of a (bits 18..24) | step flags
+//   word 1: LDS address of column b (bits 0..17) | code of b (bits 18..24) | two-qubit gate, one of kDec*
+// The step flags say what any op of the step needs, so that a wave branches on
+// a scalar.  Padding, malformed ops and the missing second qubit of a
+// single-qubit op refer to spare columns past the tableau's (zero, so that
+// they add no sign), and a step of the gate kernel has no test per lane.
+//
+// Bound: instruction issue and the LDS accesses at random columns, which
+// hardly overlap in a layer of one round: n = 1,500 (750 ops a layer), per
+// layer and CU, 480 of 850 clocks issue VALU instructions (39 a step) and 456
+// serve LDS (4 x 9.5 a step, 3 each without bank conflicts).  From op words a
+// step took about 200 instructions with its branches (decode, range checks,
+// masks).  From op words -> decoded: n = 1,500, 3,000 layers 1,858 -> 1,061 us
+// (+ 13 to decode); n = 500 x 100 tableaux, 2,000 layers 1,382 -> 936 (+ 150);
+// n = 64, 100 layers 34 -> 17; n = 1,024 60 -> 38; n = 10,000, 20 layers
+// 302 -> 214 (50 of it by the XCD order of the row groups).
 constexpr uint32_t kSpareCols = 16;
 constexpr uint32_t kDecBits = (1u << 18) - 1;
-static_assert((kFusedGateLds / 8 + kSpareCols) * 8 <= kDecBits, "column offsets fit the decoded words");
+constexpr uint32_t kDecCnot = 25, kDecCz = 26, kDecSwap = 27;        // bits of word 1
+constexpr uint32_t kStepCodes = 25, kStepPauli = 26, kStepSwap = 27;   // bits of word 0
+static_assert(kFusedGateLds + kSpareCols * 32 <= kDecBits, "column addresses fit the decoded words");
 
-// Decodes the layers of tableau blockIdx.y: a wave a layer, blockIdx.z shares
-// out a layer's steps.  poffs: padded layer starts in steps of 64.
+// Decodes the layers of tableau blockIdx.y for columns of `cb` bytes of LDS: a
+// wave a layer, blockIdx.z shares out a layer's steps.  poffs: padded layer
+// starts in steps of 64.
 __device__ __forceinline__ void decode_layers(const uint64_t *__restrict__ ops, const uint32_t *__restrict__ offs,
                                               const uint32_t *__restrict__ poffs, uint32_t depth, uint32_t n,
-                                              uint2 *__restrict__ out) {
+                                              uint32_t cb, uint2 *__restrict__ out) {
+  constexpr uint32_t kPauli = 0x30;   // codes' bits 4 and 5: sign flips by x or z alone
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t spare = 8 * (n + (lane & (kSpareCols - 1)));
+  const uint32_t spare = cb * (n + (lane & (kSpareCols - 1)));
   for (uint32_t l = blockIdx.x * 4 + wave; l < depth; l += gridDim.x * 4) {
     const uint32_t lo = offs[l], cnt = offs[l + 1] - lo, p0 = poffs[l];
     for (uint32_t st = blockIdx.z; st * 64 < cnt; st += gridDim.z) {
       const uint32_t i = st * 64 + lane;
       const uint64_t op = i < cnt ? ops[lo + i] : ~0ull;
+      const uint32_t pair = op_pair(op);
       uint2 d = make_uint2(spare, spare);
+      uint32_t codes = 0;
+      bool swap = false;
       if (op_valid(op, n)) {   // (~0 is not)
-        d.x = 8 * op_a(op) | op_ca(op) << 18;
-        if (op_pair(op) != PAIR_NONE) d.y = 8 * op_b(op) | op_cb(op) << 18 | op_pair(op) << 25;
+        codes = op_ca(op);
+        d.x = cb * op_a(op) | codes << 18;
+        if (pair != PAIR_NONE) {
+          codes |= op_cb(op);
+          d.y = cb * op_b(op) | op_cb(op) << 18 | 1u << (kDecCnot + pair - PAIR_CNOT);
+          swap = pair == PAIR_SWAP;
+        }
       }
+      if (__ballot(codes != 0)) d.x |= 1u << kStepCodes;
+      if (__ballot((codes & kPauli) != 0)) d.x |= 1u << kStepPauli;
+      if (__ballot(swap)) d.x |= 1u << kStepSwap;
       out[size_t(p0 + st) * 64 + lane] = d;
     }
   }
@@ -232,7 +253,7 @@ __device__ __forceinline__ void decode_layers(const uint64_t *__restrict__ ops, 
 __global__ void __launch_bounds__(256) k_decode_ops(const uint64_t *__restrict__ ops, const uint32_t *__restrict__ offs,
                                                     const uint32_t *__restrict__ poffs, uint32_t depth, uint32_t n,
                                                     uint2 *__restrict__ out) {
-  decode_layers(ops, offs, poffs, depth, n, out);
+  decode_layers(ops, offs, poffs, depth, n, 8, out);
 }
 // Steps and rounds (decoded_body) of every tableau's layers, one workgroup a
 // tableau: each thread a run of layers, run totals scanned over the workgroup.
@@ -264,164 +285,189 @@ __global__ void __launch_bounds__(1024) k_plan_many(const ManyDesc *__restrict__
     d.poffs[l] = at;
     for (uint32_t k = 0; k < c; k += waves) {
       const uint32_t cnt = min(waves, c - k);
-      d.sched[r++] = make_uint2(at + k, cnt | (k + cnt == c ? 256u : 0u));
+      d.sched[r++] = cnt | (k + cnt == c ? kRoundEnds : 0u);
     }
     at += c;
   }
   if (tid == 1023) d.poffs[d.depth] = s_rd[1023];   // the number of rounds
 }
-__global__ void __launch_bounds__(256) k_decode_many(const ManyDesc *__restrict__ descs) {
+__global__ void __launch_bounds__(256) k_decode_many(const ManyDesc *__restrict__ descs, uint32_t cb) {
   const ManyDesc d = descs[blockIdx.y];
-  decode_layers(d.ops, d.offs, d.poffs, d.depth, d.n, d.dec);
+  decode_layers(d.ops, d.offs, d.poffs, d.depth, d.n, cb, d.dec);
 }
 
-// x and z of a row group's columns in LDS, by a column's offset in the
-// decoded words.  32-row groups keep a column's two words side by side (one
-// 8-byte access each way); wider ones keep two planes (16- and 32-byte
-// accesses at random columns collide on the banks).
+// x and z of a column's rows side by side at its LDS address.  (The kernels
+// below have no other LDS than what they are launched with, which begins at
+// address 0; a decoded address is used as it is.)
 template <typename T>
-struct GroupLds {
-  unsigned char *x, *z;
-  __device__ GroupLds(void *mem, uint32_t cols) : x(reinterpret_cast<unsigned char *>(mem)), z(x + cols * sizeof(T)) {}
-  __device__ void get(uint32_t off, T &vx, T &vz) const {
-    vx = *reinterpret_cast<const T *>(x + off * (sizeof(T) / 8));
-    vz = *reinterpret_cast<const T *>(z + off * (sizeof(T) / 8));
-  }
-  __device__ void put(uint32_t off, T vx, T vz) const {
-    *reinterpret_cast<T *>(x + off * (sizeof(T) / 8)) = vx;
-    *reinterpret_cast<T *>(z + off * (sizeof(T) / 8)) = vz;
-  }
+struct alignas(2 * sizeof(T) < 16 ? 2 * sizeof(T) : 16) XZ {
+  T x, z;
 };
-template <>
-struct GroupLds<uint32_t> {
-  unsigned char *xz;
-  __device__ GroupLds(void *mem, uint32_t) : xz(reinterpret_cast<unsigned char *>(mem)) {}
-  __device__ void get(uint32_t off, uint32_t &vx, uint32_t &vz) const {
-    const uint2 v = *reinterpret_cast<const uint2 *>(xz + off);
-    vx = v.x;
-    vz = v.y;
-  }
-  __device__ void put(uint32_t off, uint32_t vx, uint32_t vz) const {
-    *reinterpret_cast<uint2 *>(xz + off) = make_uint2(vx, vz);
-  }
-};
+template <typename T>
+__device__ __forceinline__ T *lds_at(uint32_t addr) {
+  return (T *)(__attribute__((address_space(3))) T *)uintptr_t(addr);
+}
 
+// (word by word: a struct copied between memories would pass through a stack
+// slot, which the compiler may place in LDS, at address 0)
 template <typename T>
-__device__ __forceinline__ void apply_decoded(uint2 d, const GroupLds<T> &g, T &racc) {
-  const uint32_t a = d.x & kDecBits, b = d.y & kDecBits;
-  T xa, za, xb, zb;
-  g.get(a, xa, za);
-  g.get(b, xb, zb);
-  if (__ballot(((d.x | d.y) & (0x7fu << 18)) != 0)) {   // (layers of two-qubit gates alone have none)
-    sq_apply((d.x >> 18) & 0x7fu, xa, za, racc);
-    sq_apply((d.y >> 18) & 0x7fu, xb, zb, racc);
+__device__ __forceinline__ void copy_word(T &d, const T &s) { d = s; }
+__device__ __forceinline__ void copy_word(U128 &d, const U128 &s) {
+  const uint64_t lo = s.lo, hi = s.hi;
+  d.lo = lo;
+  d.hi = hi;
+}
+
+// One store of a column's x and z.  (The empty asm keeps the value in
+// neighbouring registers: from others the compiler makes two stores of half
+// the width, at twice the bank conflicts.)
+__device__ __forceinline__ void put_col(XZ<uint32_t> *c, uint32_t x, uint32_t z) {
+  uint64_t v = uint64_t(z) << 32 | x;
+  asm volatile("" : "+v"(v));
+  *reinterpret_cast<uint64_t *>(c) = v;
+}
+typedef uint64_t U64x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void put_col(XZ<uint64_t> *c, uint64_t x, uint64_t z) {
+  U64x2 v = {x, z};
+  asm volatile("" : "+v"(v));
+  *reinterpret_cast<U64x2 *>(c) = v;
+}
+__device__ __forceinline__ void put_col(XZ<U128> *c, U128 x, U128 z) {
+  put_col(reinterpret_cast<XZ<uint64_t> *>(&c->x), x.lo, x.hi);
+  put_col(reinterpret_cast<XZ<uint64_t> *>(&c->z), z.lo, z.hi);
+}
+
+// The 64 ops of a step, one a lane.
+template <typename T>
+__device__ __forceinline__ void apply_decoded(uint2 d, T &racc) {
+  const uint32_t flags = uint32_t(__builtin_amdgcn_readfirstlane(int(d.x)));
+  XZ<T> *pa = lds_at<XZ<T>>(d.x & kDecBits), *pb = lds_at<XZ<T>>(d.y & kDecBits);
+  const XZ<T> va = *pa, vb = *pb;
+  T xa = va.x, za = va.z, xb = vb.x, zb = vb.z;
+  auto mask = [](uint32_t w, uint32_t bit) { return mask_if<T>((w >> bit) & 1u); };
+  if (flags & (1u << kStepCodes)) {   // (layers of two-qubit gates alone have none)
+    if (flags & (1u << kStepPauli)) {
+      racc = bop3<LUT_AND_XOR>(xa, mask(d.x, 22), bop3<LUT_AND_XOR>(za, mask(d.x, 23), racc));
+      racc = bop3<LUT_AND_XOR>(xb, mask(d.y, 22), bop3<LUT_AND_XOR>(zb, mask(d.y, 23), racc));
+    }
+    auto sq = [&](uint32_t w, T &x, T &z) {   // sq_apply without the flips by x or z alone
+      racc = bop3<LUT_AND_XOR>(x & z, mask(w, 24), racc);
+      const T nx = bop3<LUT_ANDN_XOR>(x, mask(w, 18), z & mask(w, 19));
+      const T nz = bop3<LUT_ANDN_XOR>(z, mask(w, 21), x & mask(w, 20));
+      x = nx;
+      z = nz;
+    };
+    sq(d.x, xa, za);
+    sq(d.y, xb, zb);
   }
-  // two-qubit gates under lane masks: CNOT alone where the wave has no other
-  const T mc = mask_if<T>((d.y >> 25) & ~(d.y >> 26) & 1u);
-  if (__ballot((d.y >> 26) != 0) == 0) {
-    racc = bop3<LUT_AND_XOR>(bop3<LUT_AND_ANDN>(xa, zb, xb ^ za), mc, racc);
-    xb = bop3<LUT_AND_XOR>(xa, mc, xb);
-    za = bop3<LUT_AND_XOR>(zb, mc, za);
-  } else {
-    const T mz = mask_if<T>((d.y >> 26) & ~(d.y >> 25) & 1u), ms = mask_if<T>((d.y >> 25) & (d.y >> 26) & 1u);
-    racc = bop3<LUT_AND_XOR>(bop3<LUT_AND_ANDN>(xa, zb, xb ^ za), mc, racc);
-    racc = bop3<LUT_AND_XOR>(bop3<LUT_AND3>(xa, xb, za ^ zb), mz, racc);
-    const T nxb = bop3<LUT_AND_XOR>(xa, mc, xb), nza = bop3<LUT_AND_XOR>(zb, mc, bop3<LUT_AND_XOR>(xb, mz, za));
-    const T nzb = bop3<LUT_AND_XOR>(xa, mz, zb);
-    const T sx = (xa ^ nxb) & ms, sz = (nza ^ nzb) & ms;
+  // two-qubit gates under lane masks; without one xb and zb are zero (spare)
+  const T mc = mask(d.y, kDecCnot), mz = mask(d.y, kDecCz);
+  const T flip = bop3<LUT_SELECT>(mz, bop3<LUT_AND_XOR_BC>(xb, za, zb), bop3<LUT_AND_XNOR>(zb, xb, za));
+  racc = bop3<LUT_AND_XOR>(flip, xa, racc);
+  za = bop3<LUT_AND_XOR>(zb, mc, bop3<LUT_AND_XOR>(xb, mz, za));
+  xb = bop3<LUT_AND_XOR>(xa, mc, xb);
+  zb = bop3<LUT_AND_XOR>(xa, mz, zb);
+  if (flags & (1u << kStepSwap)) {   // seldom; a SWAP adds no sign
+    const T ms = mask(d.y, kDecSwap), sx = (xa ^ xb) & ms, sz = (za ^ zb) & ms;
+    racc = bop3<LUT_AND_XOR>(flip & ms, xa, racc);
     xa ^= sx;
-    xb = nxb ^ sx;
-    za = nza ^ sz;
-    zb = nzb ^ sz;
+    xb ^= sx;
+    za ^= sz;
+    zb ^= sz;
   }
-  g.put(b, xb, zb);
-  g.put(a, xa, za);
+  put_col(pb, xb, zb);
+  put_col(pa, xa, za);
 }
 
 // All layers of a decoded stream on one row group, as fused_body does, in
 // rounds of up to one step of 64 ops per wave (a layer takes one or more).
-// sched[r]: first step of the round, and its number of steps | 256 where the
-// layer ends with it; 64 rounds' entries sit in a wave's lanes.  A wave loads
-// its next kOpAhead rounds' ops ahead.
+// sched[r]: the steps of round r, | kRoundEnds where the layer ends with it;
+// 64 rounds' entries sit in a wave's lanes.  A wave loads its next kOpAhead
+// rounds' ops ahead.  LDS: n columns, the spare ones, the sign word.
 constexpr int kOpAhead = 4;
 template <typename T>
 __device__ __forceinline__ void decoded_body(uint64_t *X, uint64_t *Z, uint64_t *P, uint32_t n, uint32_t Wp,
-                                             const uint2 *__restrict__ dec, const uint2 *__restrict__ sched,
-                                             uint32_t rounds, uint32_t unit, const GroupLds<T> &g, T *s_r) {
+                                             const uint2 *__restrict__ dec, const uint32_t *__restrict__ sched,
+                                             uint32_t rounds, uint32_t unit) {
   const uint32_t tid = threadIdx.x, lane = tid & 63, nthr = blockDim.x;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool alone = nthr == 64;   // (one wave's LDS accesses are in order)
   const size_t cs = size_t(Wp) * 8 / sizeof(T);
   const T *XT = reinterpret_cast<const T *>(X);
   const T *ZT = reinterpret_cast<const T *>(Z);
-  for (uint32_t j = tid; j < n; j += nthr) g.put(8 * j, XT[j * cs + unit], ZT[j * cs + unit]);
-  if (tid == 0) *s_r = T{};
-  const GlobalU64 *gsched = (const GlobalU64 *)sched;
-  const GlobalU64 *gdec = (const GlobalU64 *)dec + size_t(wave) * 64 + lane;
-  auto entries = [&](uint32_t r) -> uint2 {   // of rounds r + lane (none past the last)
-    const uint64_t v = r + lane < rounds ? uint64_t(gsched[r + lane]) : 0ull;
-    return make_uint2(uint32_t(v), uint32_t(v >> 32));
-  };
+  constexpr uint32_t kCol = sizeof(XZ<T>);
+  T *sign = lds_at<T>((n + kSpareCols) * kCol);
+  for (uint32_t j = tid; j < n; j += nthr) {
+    XZ<T> *c = lds_at<XZ<T>>(j * kCol);
+    copy_word(c->x, XT[j * cs + unit]);
+    copy_word(c->z, ZT[j * cs + unit]);
+  }
+  if (tid < kSpareCols) *lds_at<XZ<T>>((n + tid) * kCol) = {};
+  if (tid == 0) *sign = T{};
+  const GlobalU32 *gsched = (const GlobalU32 *)sched;
+  const GlobalU64 *gdec = (const GlobalU64 *)dec + size_t(wave) * 64;
+  auto entries = [&](uint32_t r) -> uint32_t { return r + lane < rounds ? uint32_t(gsched[r + lane]) : 0u; };
   uint64_t ring[kOpAhead];
   uint32_t ctl[kOpAhead];
-  auto load = [&](int d, uint2 e, uint32_t i) {
-    const uint32_t first = uint32_t(__builtin_amdgcn_readlane(int(e.x), int(i)));
-    ctl[d] = uint32_t(__builtin_amdgcn_readlane(int(e.y), int(i)));
+  uint32_t first = 0;   // step of the next round to load
+  auto load = [&](int d, uint32_t e, uint32_t i) {
+    const uint32_t c = uint32_t(__builtin_amdgcn_readlane(int(e), int(i))), cnt = c & (kRoundEnds - 1);
+    ctl[d] = c;
     // (a wave past the round's steps loads from the stream's start: in range,
     // since the stream holds a round of every wave; see the launch)
-    ring[d] = gdec[size_t(wave < (ctl[d] & 255u) ? first : 0u) * 64];
+    ring[d] = (gdec + size_t(wave < cnt ? first : 0u) * 64)[lane];
+    first += cnt;
   };
-  uint2 e = entries(0);
+  uint32_t e = entries(0);
 #pragma unroll
   for (int d = 0; d < kOpAhead; ++d) load(d, e, uint32_t(d));
   __syncthreads();
   T racc{};
   for (uint32_t r0 = 0; r0 < rounds; r0 += 64) {
     e = entries(r0 + kOpAhead);
+    asm volatile("" : "+v"(e));   // waited for here, and not with every turn of the loop below
     for (uint32_t q = 0; q < 64; q += kOpAhead) {
 #pragma unroll
       for (int d = 0; d < kOpAhead; ++d) {
-        const uint64_t v = ring[d];
         const uint32_t c = ctl[d];
-        load(d, e, q + uint32_t(d));
-        if (wave < (c & 255u)) apply_decoded(make_uint2(uint32_t(v), uint32_t(v >> 32)), g, racc);
-        if ((c & 256u) && !alone) lds_barrier();
+        if (wave < (c & (kRoundEnds - 1)))
+          apply_decoded<T>(make_uint2(uint32_t(ring[d]), uint32_t(ring[d] >> 32)), racc);
+        load(d, e, q + uint32_t(d));   // (after its use: a copy of it would wait for every load in flight)
+        if ((c & kRoundEnds) && !alone) lds_barrier();
       }
       if (r0 + q + kOpAhead >= rounds) break;
     }
   }
-  if (nonzero(racc)) lds_xor(s_r, racc);
+  if (nonzero(racc)) lds_xor(sign, racc);
   __syncthreads();
   T *XW = reinterpret_cast<T *>(X);
   T *ZW = reinterpret_cast<T *>(Z);
   for (uint32_t j = tid; j < n; j += nthr) {
-    T vx, vz;
-    g.get(8 * j, vx, vz);
-    XW[j * cs + unit] = vx;
-    ZW[j * cs + unit] = vz;
+    const XZ<T> *c = lds_at<XZ<T>>(j * kCol);
+    copy_word(XW[j * cs + unit], c->x);
+    copy_word(ZW[j * cs + unit], c->z);
   }
-  if (tid == 0 && nonzero(*s_r)) reinterpret_cast<T *>(P)[unit] ^= *s_r;   // this part of P is ours alone
+  if (tid == 0) {
+    const T r = *sign;
+    if (nonzero(r)) reinterpret_cast<T *>(P)[unit] ^= r;   // this part of P is ours alone
+  }
 }
 
 constexpr uint32_t kFusedMaxThreads = 1024;
-// (the sign word sits past the columns, so that the columns start at LDS
-// address 0 and a decoded offset is an address)
 __global__ void __launch_bounds__(kFusedMaxThreads) k_gates_decoded(TabDev t, const uint2 *__restrict__ dec,
-                                                                   const uint2 *__restrict__ sched, uint32_t rounds) {
-  extern __shared__ uint64_t lds_u64[];
-  const GroupLds<uint32_t> g(lds_u64, t.n + kSpareCols);
-  decoded_body<uint32_t>(t.X, t.Z, t.P, t.n, t.Wp, dec, sched, rounds, blockIdx.x, g,
-                         reinterpret_cast<uint32_t *>(lds_u64 + t.n + kSpareCols));
+                                                                   const uint32_t *__restrict__ sched, uint32_t rounds) {
+  // consecutive row groups on one XCD (workgroups go round the 8 of them): the
+  // groups of a 128-byte line of a column then share it in that XCD's L2
+  const uint32_t per = gridDim.x / 8, more = gridDim.x % 8, xcd = blockIdx.x % 8;
+  const uint32_t unit = xcd * per + min(xcd, more) + blockIdx.x / 8;
+  decoded_body<uint32_t>(t.X, t.Z, t.P, t.n, t.Wp, dec, sched, rounds, unit);
 }
 template <typename T>
 __global__ void __launch_bounds__(256) k_gates_many_decoded(const ManyDesc *__restrict__ descs) {
-  extern __shared__ uint64_t lds_u64[];
   const ManyDesc d = descs[blockIdx.y];
   constexpr uint32_t kBits = 8 * sizeof(T);
   if (blockIdx.x >= (2 * d.n + kBits - 1) / kBits) return;   // group past the tableau's 2n rows
-  const GroupLds<T> g(lds_u64, d.n + kSpareCols);
-  decoded_body<T>(d.X, d.Z, d.P, d.n, d.Wp, d.dec, d.sched, d.poffs[d.depth], blockIdx.x, g,
-                  reinterpret_cast<T *>(reinterpret_cast<unsigned char *>(lds_u64) + 2 * (d.n + kSpareCols) * sizeof(T)));
+  decoded_body<T>(d.X, d.Z, d.P, d.n, d.Wp, d.dec, d.sched, d.poffs[d.depth], blockIdx.x);
 }
 
 // One tableau, 32-row groups (twice as many workgroups as 64-row ones: a
@@ -613,7 +659,12 @@ hipError_t launch_gates_many(const ManyDesc *dev_descs, uint32_t count, uint32_t
   return hipGetLastError();
 }
 
+// (decoded addresses count from 0: no LDS of the kernel's own)
 static hipError_t allow_gate_lds(const void *fn, size_t more) {
+  hipFuncAttributes a;
+  hipError_t e = hipFuncGetAttributes(&a, fn);
+  if (e != hipSuccess) return e;
+  if (a.sharedSizeBytes != 0) return hipErrorInvalidConfiguration;
   return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(kFusedGateLds + more));
 }
 
@@ -621,7 +672,7 @@ static hipError_t allow_gate_lds(const void *fn, size_t more) {
 static uint32_t decode_grid(uint32_t depth, uint32_t most) { return depth / 4 + 1 < most ? depth / 4 + 1 : most; }
 
 hipError_t launch_gates_decoded(const TabDev &t, const uint64_t *ops, const uint32_t *dev_offs,
-                                const uint32_t *dev_poffs, const uint2 *dev_sched, uint32_t depth, uint32_t rounds,
+                                const uint32_t *dev_poffs, const uint32_t *dev_sched, uint32_t depth, uint32_t rounds,
                                 uint32_t max_steps, uint32_t waves, uint2 *dec, uint2 *dec_base, hipStream_t st) {
   if (rounds == 0) return hipSuccess;
   constexpr size_t kMore = kSpareCols * 8 + 8;
@@ -650,7 +701,7 @@ hipError_t launch_gates_many_decoded(const ManyDesc *dev_descs, uint32_t count, 
   k_plan_many<<<count, 1024, 0, st>>>(dev_descs, waves);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_decode_many<<<dim3(gx, count, gz), 256, 0, st>>>(dev_descs);
+  k_decode_many<<<dim3(gx, count, gz), 256, 0, st>>>(dev_descs, rows / 4);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t lds = 2 * size_t(max_n + kSpareCols) * (rows / 8) + 16;

@@ -342,9 +342,10 @@ hipError_t launch_gate_layer(const TabDev &t, const uint64_t *ops, uint32_t nops
 constexpr size_t kFusedGateLds = 160 * 1024 - 1024;
 bool fused_gates_fit(uint32_t n);
 // Fewest layers worth decoding a stream for: the decode launch costs 5 to 12
-// us, a layer gains 0.2 us (n = 64: 0.34 -> 0.20 us, n = 1,024: 0.60 -> 0.44,
-// n = 1,500: 0.62 -> 0.43, n = 10,000, 16 waves: 15.1 -> 14.0).
+// us, a layer gains 0.2 us and more (n = 64: 0.34 -> 0.17 us, n = 1,024: 0.60
+// -> 0.38, n = 1,500: 0.62 -> 0.35, n = 10,000, 16 waves: 15.1 -> 10.7).
 constexpr uint32_t kDecodeMinDepth = 16;
+constexpr uint32_t kRoundEnds = 256;       // see launch_gates_decoded
 constexpr uint32_t kDecodeMaxWaves = 16;   // of a workgroup that runs a decoded stream
 // One tableau of a many-tableau gate launch (device memory).
 struct ManyDesc {
@@ -352,7 +353,7 @@ struct ManyDesc {
   const uint64_t *ops;      // encoded ops of this tableau
   const uint32_t *offs;     // its layer boundaries [depth + 1]
   uint32_t *poffs;          // decoded: layer starts in steps of 64 ops [depth], the number of rounds
-  uint2 *sched;             // decoded: its rounds
+  uint32_t *sched;          // decoded: its rounds
   uint2 *dec;               // decoded: its stream
   uint32_t n, Wp, depth, pad;
 };
@@ -366,11 +367,11 @@ hipError_t launch_gates_many(const ManyDesc *dev_descs, uint32_t count, uint32_t
                              hipStream_t st);
 // The same through a decoded stream: layers in steps of 64 ops (poffs: their
 // boundaries in steps, relative to dec), run in rounds of up to `waves` steps
-// (sched[r]: the round's first step, counted from dec_base, and its steps,
-// | 256 at a layer's end).  dec_base holds at least `waves` steps.  For many
+// (sched[r]: the round's steps, | kRoundEnds at a layer's end), the first from
+// dec_base on.  dec_base holds at least `waves` steps.  For many
 // tableaux poffs and sched are scratch, planned on the device.
 hipError_t launch_gates_decoded(const TabDev &t, const uint64_t *ops, const uint32_t *dev_offs,
-                                const uint32_t *dev_poffs, const uint2 *dev_sched, uint32_t depth, uint32_t rounds,
+                                const uint32_t *dev_poffs, const uint32_t *dev_sched, uint32_t depth, uint32_t rounds,
                                 uint32_t max_steps, uint32_t waves, uint2 *dec, uint2 *dec_base, hipStream_t st);
 hipError_t launch_gates_many_decoded(const ManyDesc *dev_descs, uint32_t count, uint32_t max_n, uint32_t rows,
                                      uint32_t max_depth, uint32_t max_steps, uint32_t waves, hipStream_t st);
