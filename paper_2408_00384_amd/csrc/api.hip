@@ -667,12 +667,20 @@ static int run_encoded(cliff_tab *t, const uint64_t *dev_ops, const uint32_t *ho
     HIP_TRY(e);
     return CLIFF_OK;
   }
-  for (uint32_t l = 0; l < depth; ++l) {
-    const uint32_t a = host_offs[l], b = host_offs[l + 1];
-    t->ctx->prof.begin(PK_GATE, st);
-    hipError_t e = launch_gate_layer(t->dev, dev_ops + a, b - a, st);
-    t->ctx->prof.end(PK_GATE, st);
-    HIP_TRY(e);
+  // Layer by layer, for as many row words at a time as stay in the last-level
+  // cache from one layer to the next (kLayerBytes of X and Z).
+  const uint32_t W = t->dev.W;
+  const size_t fit = std::max<size_t>(1, kLayerBytes / (size_t(t->d.n) * 16));
+  const uint32_t parts = depth > 1 ? uint32_t((W + fit - 1) / fit) : 1;
+  const uint32_t step = ((W + parts - 1) / parts + 63) / 64 * 64;
+  for (uint32_t w0 = 0; w0 < W; w0 += step) {
+    for (uint32_t l = 0; l < depth; ++l) {
+      const uint32_t a = host_offs[l], b = host_offs[l + 1];
+      t->ctx->prof.begin(PK_GATE, st);
+      hipError_t e = launch_gate_layer(t->dev, dev_ops + a, b - a, w0, std::min(W, w0 + step), st);
+      t->ctx->prof.end(PK_GATE, st);
+      HIP_TRY(e);
+    }
   }
   return CLIFF_OK;
 }

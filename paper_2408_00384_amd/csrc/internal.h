@@ -337,7 +337,11 @@ hipError_t launch_measure_lr(const TabDev &t, const LrDev &s, const uint32_t *de
 // ---- launchers (each defined in the .hip file holding its kernels) ----------
 hipError_t launch_init_zero(const TabDev &t, hipStream_t st);
 hipError_t launch_fold_pending(const TabDev &t, hipStream_t st);
-hipError_t launch_gate_layer(const TabDev &t, const uint64_t *ops, uint32_t nops, hipStream_t st);
+// (row words w0 .. w1).  kLayerBytes: X and Z of as many row words as a call
+// of several layers takes through them all at a time, of the 256 MB cache.
+constexpr size_t kLayerBytes = size_t(160) << 20;
+hipError_t launch_gate_layer(const TabDev &t, const uint64_t *ops, uint32_t nops, uint32_t w0, uint32_t w1,
+                             hipStream_t st);
 // LDS budget of the fused all-layers gate kernel (8 bytes per qubit).
 constexpr size_t kFusedGateLds = 160 * 1024 - 1024;
 bool fused_gates_fit(uint32_t n);
