@@ -388,49 +388,55 @@ int cliff_tab_init_zero(cliff_tab *t) {
 
 // ------------------------------------------------------------ gate encoding ---
 
-static int check_layers(uint32_t n, const uint8_t *h, const uint8_t *s, const uint32_t *ctrl,
-                        const uint32_t *tgt, uint32_t npairs, uint32_t depth) {
+static int check_layer_args(uint32_t n, const uint8_t *h, const uint8_t *s, const uint32_t *ctrl,
+                            const uint32_t *tgt, uint32_t npairs, uint32_t depth) {
   if (depth == 0) return CLIFF_OK;
   if (!h || !s) return fail(CLIFF_EINVAL, "layers: NULL h/s");
   if (npairs && (!ctrl || !tgt)) return fail(CLIFF_EINVAL, "layers: NULL ctrl/tgt");
   if (2ull * npairs > n) return fail(CLIFF_EINVAL, "layers: %u pairs on %u qubits", npairs, n);
-  std::vector<uint32_t> seen(n, 0xFFFFFFFFu);
-  for (uint32_t l = 0; l < depth; ++l) {
-    for (uint32_t k = 0; k < npairs; ++k) {
-      const uint32_t c = ctrl[size_t(l) * npairs + k], g = tgt[size_t(l) * npairs + k];
-      if (c >= n || g >= n)
-        return fail(CLIFF_EINVAL, "layer %u pair %u: qubit out of range (n=%u)", l, k, n);
-      if (c == g) return fail(CLIFF_EINVAL, "layer %u pair %u: CNOT control == target", l, k);
-      if (seen[c] == l || seen[g] == l)
-        return fail(CLIFF_EINVAL, "layer %u: qubit used by two CNOTs", l);
-      seen[c] = seen[g] = l;
-    }
-  }
   return CLIFF_OK;
 }
 
-// ops for one layer; returns the number of words written (cap permitting)
-static size_t encode_layer(uint32_t n, const uint8_t *h, const uint8_t *s, const uint32_t *ctrl,
-                           const uint32_t *tgt, uint32_t npairs, std::vector<uint8_t> &paired,
-                           uint64_t *ops, size_t cap) {
-  size_t cnt = 0;
-  auto emit = [&](uint64_t v) {
-    if (ops && cnt < cap) ops[cnt] = v;
-    ++cnt;
-  };
-  static const uint32_t kHS = sq_compose(SQ_H, SQ_S);
-  auto code = [&](uint32_t q) { return h[q] ? (s[q] ? kHS : SQ_H) : (s[q] ? SQ_S : SQ_I); };
-  std::fill(paired.begin(), paired.end(), 0);
+// Checks and encodes layer l of a layered circuit in one go, without a branch
+// that depends on the gates (random ones are mispredicted every other time:
+// 4 M pairs took 73 ms with a check, a count and a write pass over branches;
+// now 9).  state: n bytes of scratch, a qubit's code | 0x80 once a CNOT has
+// it.  ops: room for layer_room() words, *cnt of them written.
+static size_t layer_room(uint32_t n, uint32_t npairs) { return size_t(n) - npairs + 1; }
+static int encode_layer(uint32_t n, uint32_t l, const uint8_t *h, const uint8_t *s, const uint32_t *ctrl,
+                        const uint32_t *tgt, uint32_t npairs, uint8_t *state, uint64_t *ops, size_t *cnt) {
+  static const uint8_t kHS = uint8_t(sq_compose(SQ_H, SQ_S));
+  const uint8_t both = uint8_t(SQ_H ^ SQ_S ^ kHS);
+  h += size_t(l) * n;
+  s += size_t(l) * n;
+  for (uint32_t q = 0; q < n; ++q) {
+    const uint8_t hm = h[q] ? 0xFF : 0, sm = s[q] ? 0xFF : 0;
+    state[q] = uint8_t((hm & SQ_H) ^ (sm & SQ_S) ^ (hm & sm & both));
+  }
+  if (npairs) {
+    ctrl += size_t(l) * npairs;
+    tgt += size_t(l) * npairs;
+  }
   for (uint32_t k = 0; k < npairs; ++k) {
     const uint32_t c = ctrl[k], g = tgt[k];
-    paired[c] = paired[g] = 1;
-    emit(make_op(c, g, code(c), code(g), PAIR_CNOT));
+    if (c >= n || g >= n)
+      return fail(CLIFF_EINVAL, "layer %u pair %u: qubit out of range (n=%u)", l, k, n);
+    if (c == g) return fail(CLIFF_EINVAL, "layer %u pair %u: CNOT control == target", l, k);
+    const uint8_t cc = state[c], cg = state[g];
+    if ((cc | cg) & 0x80) return fail(CLIFF_EINVAL, "layer %u: qubit used by two CNOTs", l);
+    state[c] = cc | 0x80;
+    state[g] = cg | 0x80;
+    ops[k] = make_op(c, g, cc, cg, PAIR_CNOT);
   }
-  for (uint32_t q = 0; q < n; ++q) {
-    if (paired[q] || !(h[q] | s[q])) continue;
-    emit(make_op(q, 0, code(q), SQ_I, PAIR_NONE));
+  size_t at = npairs;
+  if (2 * size_t(npairs) < n) {
+    for (uint32_t q = 0; q < n; ++q) {
+      ops[at] = make_op(q, 0, state[q], SQ_I, PAIR_NONE);
+      at += state[q] - 1u < 0x7Fu;   // unpaired, and not the identity
+    }
   }
-  return cnt;
+  *cnt = at;
+  return CLIFF_OK;
 }
 
 extern "C" int cliff_encode_layers(uint32_t n, const uint8_t *h, const uint8_t *s,
@@ -439,17 +445,20 @@ extern "C" int cliff_encode_layers(uint32_t n, const uint8_t *h, const uint8_t *
                                    size_t *nops) {
   if (!nops) return fail(CLIFF_EINVAL, "cliff_encode_layers: nops is NULL");
   if (n == 0) return fail(CLIFF_EINVAL, "cliff_encode_layers: n == 0");
-  int rc = check_layers(n, h, s, ctrl, tgt, npairs, depth);
+  int rc = check_layer_args(n, h, s, ctrl, tgt, npairs, depth);
   if (rc) return rc;
-  std::vector<uint8_t> paired(n);
+  std::vector<uint8_t> state(n);
+  std::vector<uint64_t> row(depth ? layer_room(n, npairs) : 0);   // of a layer that may not fit
   size_t total = 0;
   for (uint32_t l = 0; l < depth; ++l) {
     if (offs) offs[l] = uint32_t(total);
     const size_t room = (ops && total < cap) ? cap - total : 0;
-    total += encode_layer(n, h + size_t(l) * n, s + size_t(l) * n,
-                          npairs ? ctrl + size_t(l) * npairs : nullptr,
-                          npairs ? tgt + size_t(l) * npairs : nullptr, npairs, paired,
-                          ops ? ops + std::min(total, cap) : nullptr, room);
+    uint64_t *to = room >= row.size() ? ops + total : row.data();
+    size_t cnt = 0;
+    rc = encode_layer(n, l, h, s, ctrl, tgt, npairs, state.data(), to, &cnt);
+    if (rc) return rc;
+    if (to == row.data() && room) memcpy(ops + total, to, std::min(cnt, room) * 8);
+    total += cnt;
     if (total > 0xFFFFFFF0ull) return fail(CLIFF_EINVAL, "cliff_encode_layers: stream too long");
   }
   if (offs) offs[depth] = uint32_t(total);
@@ -490,8 +499,9 @@ static int upload_reserve(cliff_ctx *c, size_t words, uint64_t **host, uint64_t 
   return CLIFF_OK;
 }
 
-static int upload_commit(cliff_ctx *c, size_t words) {
-  HIP_TRY(hipMemcpyAsync(c->dev_ops, c->pinned, words * 8, hipMemcpyHostToDevice, c->stream));
+// Words first .. words of the staged ones (the last copy of an upload).
+static int upload_commit(cliff_ctx *c, size_t words, size_t first = 0) {
+  HIP_TRY(hipMemcpyAsync(c->dev_ops + first, c->pinned + first, (words - first) * 8, hipMemcpyHostToDevice, c->stream));
   HIP_TRY(hipEventRecord(c->upload_done, c->stream));
   c->upload_pending = true;
   return CLIFF_OK;
@@ -685,48 +695,106 @@ static int run_encoded(cliff_tab *t, const uint64_t *dev_ops, const uint32_t *ho
   return CLIFF_OK;
 }
 
+// How a stream will be run.
+struct StreamPlan {
+  DecodePlan dec;
+  uint32_t waves = 0;
+  bool fused = false, decode = false;
+};
+static StreamPlan plan_stream(const cliff_tab *t, const uint32_t *offs, uint32_t depth) {
+  StreamPlan p;
+  p.fused = fused_gates_fit(t->d.n) && t->ctx->gate_mode != CLIFF_GATES_PER_LAYER;
+  p.decode = p.fused && !capturing(t->ctx) && plan_steps(offs, depth, &p.dec);
+  if (p.decode) {
+    p.waves = std::min(p.dec.most, kDecodeMaxWaves);
+    plan_rounds(&p.dec, p.waves);
+  }
+  return p;
+}
+
 // Upload a host stream (or, with host_ops NULL, the boundaries of one at
 // dev_ops) and run it.
 static int upload_and_run(cliff_tab *t, const uint64_t *host_ops, size_t nops, const uint64_t *dev_ops,
                           const uint32_t *offs, uint32_t depth) {
-  cliff_ctx *c = t->ctx;
-  DecodePlan plan;
-  uint32_t waves = 0;
-  const bool fused = fused_gates_fit(t->d.n) && c->gate_mode != CLIFF_GATES_PER_LAYER;
-  const bool decode = fused && !capturing(c) && plan_steps(offs, depth, &plan);
-  if (decode) {
-    waves = std::min(plan.most, kDecodeMaxWaves);
-    plan_rounds(&plan, waves);
-  }
+  const StreamPlan p = plan_stream(t, offs, depth);
   const void *dops = dev_ops, *doffs = nullptr, *dpoffs = nullptr, *dsched = nullptr;
-  if (host_ops || fused) {
+  if (host_ops || p.fused) {
     const size_t nb = (size_t(depth) + 1) * 4;
     const UploadPart parts[4] = {{host_ops, host_ops ? nops * 8 : 0, host_ops ? &dops : nullptr},
                                  {offs, nb, &doffs},
-                                 {plan.at.data(), decode ? nb : 0, &dpoffs},
-                                 {plan.sched.data(), plan.sched.size() * 4, &dsched}};
-    int rc = upload_parts(c, parts, 4);
+                                 {p.dec.at.data(), p.decode ? nb : 0, &dpoffs},
+                                 {p.dec.sched.data(), p.dec.sched.size() * 4, &dsched}};
+    int rc = upload_parts(t->ctx, parts, 4);
     if (rc) return rc;
   }
   return run_encoded(t, static_cast<const uint64_t *>(dops), offs, static_cast<const uint32_t *>(doffs), depth,
-                     decode ? &plan : nullptr, waves, static_cast<const uint32_t *>(dpoffs),
+                     p.decode ? &p.dec : nullptr, p.waves, static_cast<const uint32_t *>(dpoffs),
                      static_cast<const uint32_t *>(dsched));
 }
 
+// Layers are encoded straight into the staging area, and what is encoded goes
+// to the device while the next layers are; nothing acts on the tableau before
+// all of them have been checked.
 extern "C" int cliff_apply_layers(cliff_tab *t, const uint8_t *h, const uint8_t *s,
                                   const uint32_t *ctrl, const uint32_t *tgt, uint32_t npairs,
                                   uint32_t depth) {
   if (!t) return fail(CLIFF_EINVAL, "cliff_apply_layers: NULL tableau");
   if (depth == 0) return CLIFF_OK;
-  size_t nops = 0;
-  std::vector<uint32_t> offs(depth + 1);
-  int rc = cliff_encode_layers(t->d.n, h, s, ctrl, tgt, npairs, depth, nullptr, 0, offs.data(), &nops);
+  const uint32_t n = t->d.n;
+  int rc = check_layer_args(n, h, s, ctrl, tgt, npairs, depth);
   if (rc) return rc;
-  std::vector<uint64_t> ops(nops);
-  rc = cliff_encode_layers(t->d.n, h, s, ctrl, tgt, npairs, depth, ops.data(), nops, offs.data(), &nops);
-  if (rc) return rc;
+  constexpr size_t kSendWords = size_t(1) << 18;     // a copy of 2 MB costs 40 us beside its launch of 5
+  constexpr size_t kLooseWords = size_t(1) << 22;
+  const size_t room = layer_room(n, npairs);
+  std::vector<uint32_t> offs(size_t(depth) + 1);
+  // the most words there can be, or, where that is many and layers leave
+  // qubits unpaired (few of which may have a gate), their number
+  size_t bound = size_t(depth) * (room - 1);
+  if (bound > kLooseWords && n - 2 * size_t(npairs) > 1) {
+    rc = cliff_encode_layers(n, h, s, ctrl, tgt, npairs, depth, nullptr, 0, offs.data(), &bound);
+    if (rc) return rc;
+  }
+  if (bound > 0xFFFFFFF0ull) return fail(CLIFF_EINVAL, "cliff_apply_layers: stream too long");
   DeviceGuard g(t->ctx->device);
-  return upload_and_run(t, ops.data(), ops.size(), nullptr, offs.data(), depth);
+  const size_t ow = (size_t(depth) + 2) / 2, most = bound + room + 2 * ow + (bound / 64 + depth + 1) / 2 + 1;
+  uint64_t *host = nullptr, *dev = nullptr;
+  rc = upload_reserve(t->ctx, most, &host, &dev);
+  if (rc) return rc;
+  std::vector<uint8_t> state(n);
+  size_t at = 0, sent = 0;
+  for (uint32_t l = 0; l < depth; ++l) {
+    offs[l] = uint32_t(at);
+    size_t cnt = 0;
+    rc = encode_layer(n, l, h, s, ctrl, tgt, npairs, state.data(), host + at, &cnt);
+    if (rc) return rc;   // (a later upload waits for the copies below)
+    at += cnt;
+    if (at - sent >= kSendWords) {
+      rc = upload_commit(t->ctx, at, sent);
+      if (rc) return rc;
+      sent = at;
+    }
+  }
+  offs[depth] = uint32_t(at);
+  const StreamPlan p = plan_stream(t, offs.data(), depth);
+  auto put = [&](const uint32_t *src, size_t count) -> const uint32_t * {
+    const size_t w = (count + 1) / 2;
+    if (!w) return nullptr;
+    host[at + w - 1] = 0;
+    memcpy(host + at, src, count * 4);
+    at += w;
+    return reinterpret_cast<const uint32_t *>(dev + at - w);
+  };
+  const uint32_t *doffs = nullptr, *dpoffs = nullptr, *dsched = nullptr;
+  if (p.fused) doffs = put(offs.data(), offs.size());
+  if (p.decode) {
+    dpoffs = put(p.dec.at.data(), p.dec.at.size());
+    dsched = put(p.dec.sched.data(), p.dec.sched.size());
+  }
+  if (at > sent) {
+    rc = upload_commit(t->ctx, at, sent);
+    if (rc) return rc;
+  }
+  return run_encoded(t, dev, offs.data(), doffs, depth, p.decode ? &p.dec : nullptr, p.waves, dpoffs, dsched);
 }
 
 extern "C" int cliff_apply_encoded(cliff_tab *t, const uint64_t *dev_ops, const uint32_t *offs,
