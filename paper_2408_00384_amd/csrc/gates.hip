@@ -565,6 +565,32 @@ __global__ void __launch_bounds__(256) k_gather_words(TabDev t, const uint32_t *
 
 // Outcomes of the last measurement pass (staging: out[i * S + s], kind[i])
 // into a caller's record: rec[s * ld + col0 + i], random flags rnd[col0 + i].
+// Outcomes of shots s0 .. s0 + rows and cnt measurements, transposed from the
+// staging's [measurement][shot] into rows of `pitch` bytes (a multiple of 64)
+// in host memory, and the random flags into `rnd`.  A block turns a tile of 64
+// by 64 in LDS: reads and the writes over the host link are whole lines.
+__global__ void __launch_bounds__(256) k_emit(TabDev t, uint32_t cnt, uint32_t s0, uint32_t rows,
+                                              uint8_t *__restrict__ out, size_t pitch, uint8_t *__restrict__ rnd) {
+  constexpr uint32_t kPad = 80;   // bytes of a tile row: 16-byte aligned, banks 20 apart
+  __shared__ uint4 s_tile[64 * kPad / 16];
+  uint8_t *tile = reinterpret_cast<uint8_t *>(s_tile);
+  const uint32_t tid = threadIdx.x, i0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
+  const uint32_t iw = min(64u, cnt - i0);
+  if (r0 < rows) {
+    const uint32_t rw = min(64u, rows - r0);
+    const uint8_t *src = t.out + size_t(i0) * t.S + s0 + r0;
+    for (uint32_t j = tid; j < iw * rw; j += 256) {
+      const uint32_t i = j / rw, r = j % rw;
+      tile[r * kPad + i] = src[size_t(i) * t.S + r];
+    }
+    __syncthreads();
+    const uint32_t r = tid / 4, part = tid % 4;
+    if (r < rw && part * 16 < iw)   // (past cnt: whatever the tile holds, within the row's pitch)
+      *reinterpret_cast<uint4 *>(out + size_t(r0 + r) * pitch + i0 + part * 16) = s_tile[(r * kPad) / 16 + part];
+  }
+  if (blockIdx.y == 0 && tid < iw) rnd[i0 + tid] = t.kind[i0 + tid];
+}
+
 __global__ void __launch_bounds__(256) k_record(TabDev t, uint32_t cnt, uint8_t *__restrict__ rec, size_t ld,
                                                 size_t col0, uint8_t *__restrict__ rnd) {
   const size_t total = size_t(cnt) * t.S;
@@ -738,6 +764,13 @@ hipError_t launch_gates_many_decoded(const ManyDesc *dev_descs, uint32_t count, 
     k_gates_many_decoded<uint64_t><<<grid, 64 * waves, lds, st>>>(dev_descs);
   else
     k_gates_many_decoded<uint32_t><<<grid, 64 * waves, lds, st>>>(dev_descs);
+  return hipGetLastError();
+}
+
+hipError_t launch_emit(const TabDev &t, uint32_t cnt, uint32_t s0, uint32_t rows, uint8_t *out, size_t pitch,
+                       uint8_t *rnd, hipStream_t st) {
+  if (cnt == 0) return hipSuccess;
+  k_emit<<<dim3((cnt + 63) / 64, rows ? (rows + 63) / 64 : 1), 256, 0, st>>>(t, cnt, s0, rows, out, pitch, rnd);
   return hipGetLastError();
 }
 

@@ -363,6 +363,10 @@ struct ManyDesc {
 };
 static_assert(sizeof(ManyDesc) == 80, "descriptor layout");
 bool many_gates_fit(uint32_t max_n, uint32_t rows);
+// Outcomes and random flags of the last pass into host memory the device can
+// write; pitch a multiple of 64, out 16-byte aligned.
+hipError_t launch_emit(const TabDev &t, uint32_t cnt, uint32_t s0, uint32_t rows, uint8_t *out, size_t pitch,
+                       uint8_t *rnd, hipStream_t st);
 hipError_t launch_record(const TabDev &t, uint32_t cnt, uint8_t *rec, size_t ld, size_t col0, uint8_t *rnd,
                          hipStream_t st);
 hipError_t launch_cond_pauli(const TabDev &t, const uint64_t *ops, uint32_t k, const uint8_t *rec, size_t ld,

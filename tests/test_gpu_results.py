@@ -1,0 +1,45 @@
+"""Outcomes and random flags as the device hands them over (transposed in tiles
+of 64 measurements by 64 shots), at the edges of the tiles: against the
+device's own record of the same measurements."""
+import numpy as np
+import pytest
+
+from inputs import layered_circuit
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2408_00384_amd import Context
+    c = Context(0)
+    yield c
+    c.close()
+
+
+# k: past n (two passes, the second into later columns); the last two: rows
+# handed over in two parts (16 MB each at most)
+@pytest.mark.parametrize("n,shots,k", [(1, 1, 1), (2, 64, 2), (63, 65, 63), (64, 63, 64), (65, 1, 65), (130, 128, 127),
+                                       (40, 129, 90), (200, 1000, 193), (1030, 3, 1030), (300, 53000, 300),
+                                       (64, 262144, 64)])
+def test_outcomes_match_the_device_record(ctx, n, shots, k):
+    import torch
+    from paper_2408_00384_amd import DeviceTableau, cliff_measure_async, cliff_measure_record, cliff_tab_read_outcomes
+    c = layered_circuit(n, 6, 1, gen_seed=[94, n], circuit_id=31)
+    q = np.resize(np.random.default_rng(n).permutation(n), k).astype(np.uint32)
+    rec = torch.zeros((shots, k), dtype=torch.uint8, device="cuda:0")
+    rnd = torch.zeros(k, dtype=torch.uint8, device="cuda:0")
+    torch.cuda.synchronize()
+    t = DeviceTableau(ctx, n, shots).apply_circuit_gates(c)
+    cliff_measure_record(t.handle, q, rec.data_ptr(), k, 0, rnd.data_ptr(), c.seed, c.circuit_id)
+    torch.cuda.synchronize()
+    t.init_zero()
+    out, flags = t.apply_circuit_gates(c).measure(q, seed=c.seed, circuit=c.circuit_id)
+    assert np.array_equal(out, rec.cpu().numpy()) and np.array_equal(flags, rnd.cpu().numpy())
+    if k <= n:
+        t.init_zero()
+        t.apply_circuit_gates(c)
+        cliff_measure_async(t.handle, q, c.seed, c.circuit_id)
+        out, flags = cliff_tab_read_outcomes(t.handle, k)
+        assert np.array_equal(out, rec.cpu().numpy()) and np.array_equal(flags, rnd.cpu().numpy())
+    t.close()
