@@ -1270,7 +1270,7 @@ static int check_abort(cliff_tab *t) {
 // flags to host_random[i] (each nullable); waits for the stream.  The device
 // transposes and writes pinned memory, so that the host copies rows.  Two
 // copies to pageable memory and a byte-wise transposition on the host took
-// 217 of 419 us at 256 shots of n = 301, 30 of 148 us at n = 64 and 340 of 784
+// 217 of 419 us at 1,000 shots of n = 301, 30 of 148 us at n = 64 and 340 of 784
 // us at n = 1,024, one shot.
 constexpr size_t kResultBytes = size_t(16) << 20;
 static int read_results(cliff_tab *t, size_t cnt, uint8_t *host_out, size_t ld, uint8_t *host_random) {

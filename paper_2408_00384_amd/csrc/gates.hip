@@ -13,6 +13,8 @@
 // sign contributions are XOR-accumulated per thread and flushed once.
 #include <string.h>
 
+#include <algorithm>
+
 #include "internal.h"
 
 namespace cliff {
@@ -607,24 +609,55 @@ __global__ void __launch_bounds__(256) k_record(TabDev t, uint32_t cnt, uint8_t 
 // 24..25: 1 X, 2 Y, 3 Z) | record column (bits 32..63).  In shot s, when
 // rec[s * ld + column] is 1, every row that anticommutes with the Pauli
 // flips sign: X flips rows with z_a = 1, Z rows with x_a = 1, Y rows with
-// x_a ^ z_a = 1.  Thread <-> (row word, shot); the ops only XOR into signs,
-// so their order does not matter.
-__global__ void __launch_bounds__(256) k_cond_pauli(TabDev t, const uint64_t *__restrict__ ops, uint32_t k,
-                                                    const uint8_t *__restrict__ rec, size_t ld) {
-  const size_t total = size_t(t.W) * t.S;
-  const size_t stride = size_t(gridDim.x) * blockDim.x;
-  for (size_t j = size_t(blockIdx.x) * blockDim.x + threadIdx.x; j < total; j += stride) {
-    const size_t w = j / t.S, s = j % t.S;
-    uint64_t flip = 0;
-    for (uint32_t i = 0; i < k; ++i) {
-      const uint64_t op = ops[i];
-      const uint32_t a = uint32_t(op & kQubitMask), p = uint32_t(op >> 24) & 3u;
-      if (a >= t.n || !(rec[s * ld + (op >> 32)] & 1u)) continue;
-      const uint64_t x = t.X[size_t(a) * t.Wp + w], z = t.Z[size_t(a) * t.Wp + w];
-      // the Pauli's x part (X, Y) flips rows with z = 1, its z part (Y, Z) rows with x = 1
-      flip ^= (p != 3u ? z : 0ull) ^ (p != 1u ? x : 0ull);
+// x_a ^ z_a = 1.  The ops only XOR into signs, so their order does not matter:
+// a block takes 64 shots (one a lane) and kCondWords row words, and its waves
+// share out the ops, several loaded at a time (a thread a shot and word, op by
+// op: 15 us a launch at n = 97, 256 shots, a chain of loads; now 5.7).
+constexpr uint32_t kCondWaves = 8, kCondWords = 4, kCondOps = 4;
+__global__ void __launch_bounds__(64 * kCondWaves) k_cond_pauli(TabDev t, const uint64_t *__restrict__ ops, uint32_t k,
+                                                                const uint8_t *__restrict__ rec, size_t ld) {
+  __shared__ uint64_t s_flip[kCondWaves][kCondWords][64];
+  const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t tiles = (t.S + 63) / 64, total = tiles * ((t.W + kCondWords - 1) / kCondWords);
+  for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) {
+    const uint32_t s = (b % tiles) * 64 + lane, w0 = (b / tiles) * kCondWords;
+    const uint8_t *row = rec + size_t(min(s, t.S - 1)) * ld;
+    uint64_t flip[kCondWords] = {};
+    for (uint32_t i0 = wave * kCondOps; i0 < k; i0 += kCondWaves * kCondOps) {
+      uint64_t op[kCondOps], x[kCondOps][kCondWords], z[kCondOps][kCondWords];
+      uint32_t bit[kCondOps];
+#pragma unroll
+      for (uint32_t i = 0; i < kCondOps; ++i) {
+        op[i] = ops[min(i0 + i, k - 1)];
+        const uint32_t a = uint32_t(op[i] & kQubitMask);
+        const bool on = i0 + i < k && a < t.n;
+        bit[i] = on ? row[op[i] >> 32] & 1u : 0u;
+#pragma unroll
+        for (uint32_t w = 0; w < kCondWords; ++w) {
+          const size_t at = size_t(on ? a : 0) * t.Wp + min(w0 + w, t.W - 1);
+          x[i][w] = t.X[at];
+          z[i][w] = t.Z[at];
+        }
+      }
+#pragma unroll
+      for (uint32_t i = 0; i < kCondOps; ++i) {
+        const uint32_t p = uint32_t(op[i] >> 24) & 3u;
+        const uint64_t on = 0ull - bit[i];
+        // the Pauli's x part (X, Y) flips rows with z = 1, its z part (Y, Z) rows with x = 1
+#pragma unroll
+        for (uint32_t w = 0; w < kCondWords; ++w) flip[w] ^= ((p != 3u ? z[i][w] : 0ull) ^ (p != 1u ? x[i][w] : 0ull)) & on;
+      }
     }
-    if (flip) t.R[w * t.S + s] ^= flip;
+#pragma unroll
+    for (uint32_t w = 0; w < kCondWords; ++w) s_flip[wave][w][lane] = flip[w];
+    __syncthreads();
+    if (wave < kCondWords && w0 + wave < t.W && s < t.S) {
+      uint64_t f = 0;
+#pragma unroll
+      for (uint32_t v = 0; v < kCondWaves; ++v) f ^= s_flip[v][wave][lane];
+      if (f) t.R[size_t(w0 + wave) * t.S + s] ^= f;
+    }
+    __syncthreads();
   }
 }
 
@@ -784,7 +817,8 @@ hipError_t launch_record(const TabDev &t, uint32_t cnt, uint8_t *rec, size_t ld,
 hipError_t launch_cond_pauli(const TabDev &t, const uint64_t *ops, uint32_t k, const uint8_t *rec, size_t ld,
                              hipStream_t st) {
   if (k == 0) return hipSuccess;
-  k_cond_pauli<<<grid_for(size_t(t.W) * t.S, 256), 256, 0, st>>>(t, ops, k, rec, ld);
+  const size_t tiles = size_t((t.S + 63) / 64) * ((t.W + kCondWords - 1) / kCondWords);
+  k_cond_pauli<<<uint32_t(std::min<size_t>(tiles, 4096)), 64 * kCondWaves, 0, st>>>(t, ops, k, rec, ld);
   return hipGetLastError();
 }
 

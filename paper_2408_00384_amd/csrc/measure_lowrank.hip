@@ -932,29 +932,37 @@ __device__ __forceinline__ uint64_t det_rows(const TabDev &t, const uint64_t *co
 // The x/z terms of the ordered product of the rows (-1)^r i^(x.z) X^x Z^z: the
 // pairs s < t with z_s x_t, and the Y count.  They come from the columns with
 // x bits in stabilizer rows (none after a measure-all), which the grid's x
-// dimension shares out; its y dimension shares out the measurements.
+// dimension shares out; its y dimension shares out the measurements.  A wave
+// takes as many columns at a time as their row words fill lanes (n = 97: 16.5
+// us a launch with one at a time, now 3.9).
 __global__ void __launch_bounds__(256) k_lr_det_terms(TabDev t, LrDev s, LrArgs a) {
   const uint32_t nd = s.cnt[0], ncol = s.cnt[1];
   const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t w0 = t.n >> 6, W = t.W, wv = blockIdx.x * 4 + wave, nwv = gridDim.x * 4;
-  if (ncol == 0 || wv >= ncol) return;
+  const uint32_t w0 = t.n >> 6, W = t.W;
+  // a column's words w0 .. W in 2^lg neighbouring lanes, and in turns of 64
+  const uint32_t lg = W - w0 >= 64 ? 6u : 32u - uint32_t(__builtin_clz(max(W - w0, 2u) - 1));
+  const uint32_t grp = lane >> lg, lw = lane & ((1u << lg) - 1), per = 64u >> lg;
+  const uint64_t mine = lg == 6 ? ~0ull : (lbit(1u << lg) - 1) << (grp << lg);   // this column's lanes
+  const uint32_t wv = (blockIdx.x * 4 + wave) * per, nwv = gridDim.x * 4 * per;
+  if (wv >= ncol) return;
   for (uint32_t d = blockIdx.y; d < nd; d += gridDim.y) {
     const uint32_t m = s.dets[d];
     const uint64_t *col = t.X + size_t(a.q[m]) * t.Wp;
     uint32_t y = 0, par = 0;
-    for (uint32_t ic = wv; ic < ncol; ic += nwv) {
-      const size_t at = size_t(s.list[ic]) * t.Wp;
+    for (uint32_t ic = wv + grp; ic - grp < ncol; ic += nwv) {
+      const bool on = ic < ncol;
+      const size_t at = size_t(s.list[on ? ic : 0]) * t.Wp;
       uint32_t carry = 0;   // z parity of the product rows in earlier words
 #pragma unroll 2
       for (uint32_t wb = w0; wb < W; wb += 64) {
-        const uint32_t w = wb + lane;
-        const uint64_t tm = w < W ? det_rows(t, col, w) : 0ull;
+        const uint32_t w = wb + lw;
+        const uint64_t tm = on && w < W ? det_rows(t, col, w) : 0ull;
         const uint64_t xt = tm ? t.X[at + w] & tm : 0ull, zt = tm ? t.Z[at + w] & tm : 0ull;
         y += uint32_t(__popcll(xt & zt));
         uint64_t pre = zt << 1;   // exclusive prefix parity inside the word
         pre ^= pre << 1; pre ^= pre << 2; pre ^= pre << 4;
         pre ^= pre << 8; pre ^= pre << 16; pre ^= pre << 32;
-        const uint64_t zb = __ballot(__popcll(zt) & 1);
+        const uint64_t zb = __ballot(__popcll(zt) & 1) & mine;
         const uint32_t cin = (carry ^ uint32_t(__popcll(zb & (lbit(lane) - 1)))) & 1u;
         par ^= (uint32_t(__popcll(xt & pre)) & 1u) ^ (cin & uint32_t(__popcll(xt)) & 1u);
         carry ^= uint32_t(__popcll(zb)) & 1u;
@@ -1102,7 +1110,8 @@ hipError_t launch_measure_lr(const TabDev &t, const LrDev &s, const uint32_t *de
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (prof) prof->begin(PK_FINAL, st);
-  k_lr_det_terms<<<dim3(std::min(div_up(t.n, 32), 256u), std::min(k, 4u)), 256, 0, st>>>(t, s, a);
+  const uint32_t dx = std::min(div_up(t.n, 32), 256u);
+  k_lr_det_terms<<<dim3(dx, std::min(k, std::max(4u, 256u / dx))), 256, 0, st>>>(t, s, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   k_lr_det<<<std::min(k, 1024u), 256, 0, st>>>(t, s, a);
   if (prof) prof->end(PK_FINAL, st);

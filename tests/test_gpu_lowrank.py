@@ -134,3 +134,21 @@ def test_large_equals_step(ctx, n, depth, k):
         assert np.array_equal(a, b)
     assert res[0][-1] == res[1][-1]
     assert 0 < int(res[0][1].sum()) < k
+
+
+# the columns' stabilizer words fill 2, 2, 4, 32 and 64 lanes, and more
+@pytest.mark.parametrize("n", [33, 64, 130, 1500, 2049, 4200])
+def test_deterministic_terms_by_columns(ctx, n):
+    """Repeats while half the qubits are unmeasured, at every packing of the
+    columns' words into lanes."""
+    from paper_2408_00384_amd import DeviceTableau
+    c = layered_circuit(n, 6, 1, gen_seed=[95, n], circuit_id=24)
+    rng = np.random.default_rng(n)
+    q = rng.permutation(n)[:min(n // 2, 70)]
+    q = np.concatenate([q, q[::3]]).astype(np.uint32)
+    t = DeviceTableau(ctx, n, 1).apply_circuit_gates(c)
+    out, rnd = t.measure(q, seed=c.seed, circuit=24)
+    ref = oracle.Tableau(n).apply_circuit_gates(c)
+    o, k = ref.measure_list(q, seed=c.seed, circuit=24, shot=0)
+    assert np.array_equal(out[0], o) and np.array_equal(rnd, k) and t.anomalies() == 0
+    t.close()

@@ -1,9 +1,11 @@
-"""Outcomes and random flags as the device hands them over (transposed in tiles
+"""Results and records: conditioned Paulis at the edges of a block's 64 shots,
+4 row words and 32 ops, and outcomes and random flags as the device hands them over (transposed in tiles
 of 64 measurements by 64 shots), at the edges of the tiles: against the
 device's own record of the same measurements."""
 import numpy as np
 import pytest
 
+import oracle
 from inputs import layered_circuit
 
 pytestmark = pytest.mark.gpu
@@ -42,4 +44,29 @@ def test_outcomes_match_the_device_record(ctx, n, shots, k):
         cliff_measure_async(t.handle, q, c.seed, c.circuit_id)
         out, flags = cliff_tab_read_outcomes(t.handle, k)
         assert np.array_equal(out, rec.cpu().numpy()) and np.array_equal(flags, rnd.cpu().numpy())
+    t.close()
+
+
+@pytest.mark.parametrize("n,shots,k", [(1, 1, 1), (31, 63, 3), (32, 64, 31), (127, 65, 32), (129, 130, 33),
+                                       (500, 5, 200)])
+def test_cond_paulis_vs_oracle(ctx, n, shots, k):
+    import torch
+    from paper_2408_00384_amd import DeviceTableau, cliff_apply_cond_paulis
+    c = layered_circuit(n, 6, 1, gen_seed=[96, n], circuit_id=32)
+    rng = np.random.default_rng([n, k])
+    q, p, col = rng.integers(0, n, k).astype(np.uint32), rng.integers(1, 4, k).astype(np.uint8), \
+        rng.integers(0, 9, k).astype(np.uint32)
+    bits = rng.integers(0, 2, (shots, 9)).astype(np.uint8)
+    rec = torch.from_numpy(bits).to("cuda:0")
+    torch.cuda.synchronize()
+    t = DeviceTableau(ctx, n, shots).apply_circuit_gates(c)
+    cliff_apply_cond_paulis(t.handle, q, p, col, rec.data_ptr(), 9)
+    gx, gz, gr = t.export()
+    for s in {0, shots // 2, shots - 1}:
+        r = oracle.Tableau(n).apply_circuit_gates(c)
+        for i in range(k):
+            if bits[s, col[i]]:
+                r.pauli(int(q[i]), int(p[i]))
+        x, z, rr = r.get()
+        assert np.array_equal(gx, x) and np.array_equal(gz, z) and np.array_equal(gr[s], rr)
     t.close()
