@@ -22,6 +22,13 @@
 // Occupancy follows from that size, so a launch of small circuits keeps more
 // teams per compute unit.
 //
+// Bound: VALU instructions (95 % of the busy cycles at 4,096 circuits of n = 8
+// to 256, depth n to 4 n), two thirds of them the gates'.  That batch took 3.31
+// ms with sign flips of Pauli codes in every op, a CNOT of 6 instructions a
+// 32-bit word and a measurement item of 60; 2.96 with 5 and 36.  (Four row
+// words per thread instead of two: 7 % fewer instructions, twice the bank
+// conflicts, no faster.)
+//
 // LDS banks (64 of 4 bytes): with the power-of-two column stride, column j
 // starts at bank 2 Wl j mod 64, so a gate op's accesses fall in one of 32 / Wl
 // bank ranges set by its qubit (mod 32 / Wl; for W >= 5, two half-ranges
@@ -206,19 +213,30 @@ __global__ void __launch_bounds__(TEAM) k_batch(const BatchDescDev *__restrict__
           // branch (nearly every op has one).  When the wave's two-qubit ops
           // are all CNOTs (a wave-uniform test), the CNOT runs under a lane
           // mask instead of the per-kind branches.
-          bool other = false;
-#pragma unroll
-          for (int u = 0; u < N; ++u) other |= pr[u] != PAIR_NONE && pr[u] != PAIR_CNOT;
-          const bool only_cnot = __ballot(other) == 0;
+          // Likewise the flips by x or z alone, which codes of H and S have not.
+          bool other = false, pauli = false;
 #pragma unroll
           for (int u = 0; u < N; ++u) {
-            sq_apply(ca[u], xa[u], za[u], racc);
-            sq_apply(cb[u], xb[u], zb[u], racc);   // cb = 0 without a second qubit
+            other |= pr[u] != PAIR_NONE && pr[u] != PAIR_CNOT;
+            pauli |= ((ca[u] | cb[u]) & kSqPauli) != 0;
+          }
+          const bool only_cnot = __ballot(other) == 0;
+          if (__ballot(pauli)) {
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+              sq_pauli(ca[u], xa[u], za[u], racc);
+              sq_pauli(cb[u], xb[u], zb[u], racc);   // cb = 0 without a second qubit
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < N; ++u) {
+            sq_rest(ca[u], xa[u], za[u], racc);
+            sq_rest(cb[u], xb[u], zb[u], racc);
             if (only_cnot) {
               const T mc = mask_if<T>(pr[u] == PAIR_CNOT);
-              racc ^= bop3<LUT_AND3>(mc, xa[u], bop3<LUT_AND_ANDN>(zb[u], mc, xb[u] ^ za[u]));
-              xb[u] ^= xa[u] & mc;
-              za[u] ^= zb[u] & mc;
+              racc = bop3<LUT_AND_XOR>(xa[u] & bop3<LUT_AND_XNOR>(zb[u], xb[u], za[u]), mc, racc);
+              xb[u] = bop3<LUT_AND_XOR>(xa[u], mc, xb[u]);
+              za[u] = bop3<LUT_AND_XOR>(zb[u], mc, za[u]);
             } else if (pr[u] != PAIR_NONE) {
               pair_apply(pr[u], xa[u], za[u], xb[u], zb[u], racc);
             }
@@ -342,51 +360,57 @@ __global__ void __launch_bounds__(TEAM) k_batch(const BatchDescDev *__restrict__
       uint32_t p_next = kNone;
       uint64_t m_next = 0;
       if (p != kNone) {
+        p = __builtin_amdgcn_readfirstlane(p);   // (the wave's)
         const uint32_t pn = p - n, wpn = pn >> 6, wp = p >> 6;
         const uint64_t bpn = 1ull << (pn & 63), bpb = 1ull << (p & 63);
         // this lane's bits of rows p - n and p (zero where its word holds
-        // neither): overwritten in every column by the pivot row's bits, and
-        // by x = 0, z = [column is a], as masked selects
-        const uint64_t Bpn = wl == wpn ? bpn : 0ull, Bp = wl == wp ? bpb : 0ull, F = Bpn | Bp;
+        // neither), F: in every column they become the pivot row's bits and,
+        // but for z of column a, zero: (x ^ X1 & m) outside F and X1 & Bpn
+        // inside is (x & keep) ^ (X1 & add)
+        const uint64_t Bpn = wl == wpn ? bpn : 0ull, F = Bpn | (wl == wp ? bpb : 0ull);
+        const uint64_t keep = ~F, add = (m & keep) | Bpn;
+        const uint32_t half = 2 * wp + ((p >> 5) & 1u), hb = p & 31;   // the pivot's bit in a column's 32-bit words
         uint64_t c0 = 0, c1 = 0;
         if (wl < W) {
-          // two columns per pass, all loads first (distinct columns: the
-          // second's reads need not wait for the first's writes)
-          for (uint32_t j0 = slot; j0 < n; j0 += 2 * slots) {
-            const uint32_t j1 = j0 + slots < n ? j0 + slots : j0;
-            const bool two = j0 + slots < n;
-            uint64_t xp[2], zp[2], xv[2], zv[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-              const uint32_t j = u ? j1 : j0;
-              xp[u] = sX[j * Wl + wp];
-              zp[u] = sZ[j * Wl + wp];
-              xv[u] = sX[j * Wl + wl];
-              zv[u] = sZ[j * Wl + wl];
+          // word i of a plane is word wl of column j = slot (mod slots): two
+          // a pass, all loads first (distinct columns: the second's reads need
+          // not wait for the first's writes), each plane at a fixed step
+          uint64_t *xq = sX + tid, *zq = sZ + tid;
+          const uint32_t *xh = reinterpret_cast<const uint32_t *>(sX + (tid - wl)) + half;
+          const uint32_t *zh = reinterpret_cast<const uint32_t *>(sZ + (tid - wl)) + half;
+          auto sweep = [&](uint64_t *xo, uint64_t *zo, uint32_t xp, uint32_t zp, uint64_t x, uint64_t z) {
+            const uint64_t X1 = mask_if<uint64_t>((xp >> hb) & 1u), Z1 = mask_if<uint64_t>((zp >> hb) & 1u);
+            // rows in M anticommuting with the pivot's Pauli on column j (X:
+            // z, Z: x, Y: x ^ z); g = +1 on them where (X: x; Z: ~z; Y: z),
+            // else -1, and adding +-1 to the 2-bit counter flips c1 where c0
+            // equals that condition: c1 ^= anti & ~(c0 ^ sel), c0 ^= anti
+            const uint64_t anti = bop3<LUT_AND_XOR>(Z1, x, X1 & z) & m;
+            const uint64_t sel = bop3<LUT_SELECT>(Z1, ~(z ^ X1), x);
+            c1 ^= bop3<LUT_AND_XNOR>(anti, c0, sel);
+            c0 ^= anti;
+            *xo = bop3<LUT_AND_XOR>(X1, add, x & keep);
+            *zo = bop3<LUT_AND_XOR>(Z1, add, z & keep);
+          };
+          for (uint32_t i = tid; i < n * Wl; i += 2 * TEAM) {
+            const bool two = i + TEAM < n * Wl;
+            const uint32_t xp0 = xh[0], zp0 = zh[0];
+            const uint64_t x0 = xq[0], z0 = zq[0];
+            uint32_t xp1 = 0, zp1 = 0;
+            uint64_t x1 = 0, z1 = 0;
+            if (two) {
+              xp1 = xh[2 * TEAM];
+              zp1 = zh[2 * TEAM];
+              x1 = xq[TEAM];
+              z1 = zq[TEAM];
             }
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-              const uint32_t j = u ? j1 : j0;
-              if (u && !two) break;
-              const uint32_t xpj = uint32_t(xp[u] >> (p & 63)) & 1u;
-              const uint32_t zpj = uint32_t(zp[u] >> (p & 63)) & 1u;
-              const uint64_t x = xv[u], z = zv[u];
-              const uint64_t X1 = mask_if<uint64_t>(xpj), Z1 = mask_if<uint64_t>(zpj);
-              // rows in M anticommuting with the pivot's Pauli on column j (X:
-              // z, Z: x, Y: x ^ z); g = +1 on them where (X: x; Z: ~z; Y: z),
-              // else -1, and adding +-1 to the 2-bit counter flips c1 where c0
-              // equals that condition: c1 ^= anti & ~(c0 ^ sel), c0 ^= anti
-              const uint64_t anti = bop3<LUT_AND_XOR>(Z1, x, X1 & z) & m;
-              const uint64_t sel = (Z1 & ~(z ^ X1)) | (~Z1 & x);
-              c1 ^= bop3<LUT_AND_XNOR>(anti, c0, sel);
-              c0 ^= anti;
-              uint64_t nx = bop3<LUT_AND_XOR>(X1, m, x), nz = bop3<LUT_AND_XOR>(Z1, m, z);
-              nx = (nx & ~F) | (X1 & Bpn);
-              nz = (nz & ~F) | (Z1 & Bpn) | (mask_if<uint64_t>(j == a) & Bp);
-              sX[j * Wl + wl] = nx;
-              sZ[j * Wl + wl] = nz;
-            }
+            sweep(xq, zq, xp0, zp0, x0, z0);
+            if (two) sweep(xq + TEAM, zq + TEAM, xp1, zp1, x1, z1);
+            xq += 2 * TEAM;
+            zq += 2 * TEAM;
+            xh += 4 * TEAM;
+            zh += 4 * TEAM;
           }
+          if (slot == a % slots && wl == wp) sZ[a * Wl + wl] |= bpb;   // (this lane has swept column a)
         }
         // counters: the cpw column slots of a word sit in lanes sub * Wl + wl
         // of one wave (same wl): mod-4 sums by a butterfly over them, then

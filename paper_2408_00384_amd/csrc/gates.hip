@@ -250,7 +250,6 @@ static_assert(kFusedGateLds + kSpareCols * 32 <= kDecBits, "column addresses fit
 __device__ __forceinline__ void decode_layers(const uint64_t *__restrict__ ops, const uint32_t *__restrict__ offs,
                                               const uint32_t *__restrict__ poffs, uint32_t depth, uint32_t n,
                                               uint32_t cb, uint2 *__restrict__ out) {
-  constexpr uint32_t kPauli = 0x30;   // codes' bits 4 and 5: sign flips by x or z alone
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t spare = cb * (n + (lane & (kSpareCols - 1)));
   for (uint32_t l = blockIdx.x * 4 + wave; l < depth; l += gridDim.x * 4) {
@@ -272,7 +271,7 @@ __device__ __forceinline__ void decode_layers(const uint64_t *__restrict__ ops, 
         }
       }
       if (__ballot(codes != 0)) d.x |= 1u << kStepCodes;
-      if (__ballot((codes & kPauli) != 0)) d.x |= 1u << kStepPauli;
+      if (__ballot((codes & kSqPauli) != 0)) d.x |= 1u << kStepPauli;
       if (__ballot(swap)) d.x |= 1u << kStepSwap;
       out[size_t(p0 + st) * 64 + lane] = d;
     }
@@ -375,18 +374,11 @@ __device__ __forceinline__ void apply_decoded(uint2 d, T &racc) {
   auto mask = [](uint32_t w, uint32_t bit) { return mask_if<T>((w >> bit) & 1u); };
   if (flags & (1u << kStepCodes)) {   // (layers of two-qubit gates alone have none)
     if (flags & (1u << kStepPauli)) {
-      racc = bop3<LUT_AND_XOR>(xa, mask(d.x, 22), bop3<LUT_AND_XOR>(za, mask(d.x, 23), racc));
-      racc = bop3<LUT_AND_XOR>(xb, mask(d.y, 22), bop3<LUT_AND_XOR>(zb, mask(d.y, 23), racc));
+      sq_pauli(d.x >> 18, xa, za, racc);
+      sq_pauli(d.y >> 18, xb, zb, racc);
     }
-    auto sq = [&](uint32_t w, T &x, T &z) {   // sq_apply without the flips by x or z alone
-      racc = bop3<LUT_AND_XOR>(x & z, mask(w, 24), racc);
-      const T nx = bop3<LUT_ANDN_XOR>(x, mask(w, 18), z & mask(w, 19));
-      const T nz = bop3<LUT_ANDN_XOR>(z, mask(w, 21), x & mask(w, 20));
-      x = nx;
-      z = nz;
-    };
-    sq(d.x, xa, za);
-    sq(d.y, xb, zb);
+    sq_rest(d.x >> 18, xa, za, racc);
+    sq_rest(d.y >> 18, xb, zb, racc);
   }
   // two-qubit gates under lane masks; without one xb and zb are zero (spare)
   const T mc = mask(d.y, kDecCnot), mz = mask(d.y, kDecCz);
