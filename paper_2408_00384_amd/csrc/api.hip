@@ -123,6 +123,7 @@ struct cliff_ctx {
   uint64_t *pinned = nullptr;    // pinned staging for uploads
   size_t pinned_cap = 0;         // words
   hipEvent_t upload_done = nullptr;
+  hipEvent_t half_done[2] = {nullptr, nullptr};   // copies out of the halves of the staging area (StagedUpload)
   bool upload_pending = false;
   // register-resident measurement: second stream and its events, and the
   // chunk scratch (grown on demand to the largest shape measured)
@@ -221,6 +222,8 @@ int cliff_ctx_create(int device, void *hip_stream, cliff_ctx **out) {
   }
   c->num_cus = prop.multiProcessorCount;
   e = hipEventCreateWithFlags(&c->upload_done, hipEventDisableTiming);
+  for (hipEvent_t &ev : c->half_done)
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking);
   for (hipEvent_t &ev : c->persist_ev)
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
@@ -244,6 +247,8 @@ int cliff_ctx_destroy(cliff_ctx *c) {
   if (c->pinned) (void)hipHostFree(c->pinned);
   if (c->results) (void)hipHostFree(c->results);
   if (c->upload_done) (void)hipEventDestroy(c->upload_done);
+  for (hipEvent_t ev : c->half_done)
+    if (ev) (void)hipEventDestroy(ev);
   if (c->aux) {
     (void)hipStreamSynchronize(c->aux);
     (void)hipStreamDestroy(c->aux);
@@ -475,7 +480,9 @@ extern "C" int cliff_encode_layers(uint32_t n, const uint8_t *h, const uint8_t *
 // pinned and device buffers if needed), fill the returned pinned area, then
 // commit the copy.  The device base address is known before the copy, so the
 // staged words may point into themselves.
-static int upload_reserve(cliff_ctx *c, size_t words, uint64_t **host, uint64_t **dev) {
+// `pinned` (default: all) words of it are staged at a time.
+static int upload_reserve(cliff_ctx *c, size_t words, uint64_t **host, uint64_t **dev, size_t pinned = SIZE_MAX) {
+  pinned = std::min(pinned, words);
   if (c->upload_pending) {
     HIP_TRY(hipEventSynchronize(c->upload_done));
     c->upload_pending = false;
@@ -489,11 +496,11 @@ static int upload_reserve(cliff_ctx *c, size_t words, uint64_t **host, uint64_t 
     HIP_TRY(hipMalloc(&c->dev_ops, cap * 8));
     c->dev_ops_cap = cap;
   }
-  if (words > c->pinned_cap) {
+  if (pinned > c->pinned_cap) {
     if (c->pinned) HIP_TRY(hipHostFree(c->pinned));
     c->pinned = nullptr;
     c->pinned_cap = 0;
-    size_t cap = std::max<size_t>(words, 1 << 16);
+    size_t cap = std::max<size_t>(pinned, 1 << 16);
     HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&c->pinned), cap * 8, hipHostMallocDefault));
     c->pinned_cap = cap;
   }
@@ -502,9 +509,8 @@ static int upload_reserve(cliff_ctx *c, size_t words, uint64_t **host, uint64_t 
   return CLIFF_OK;
 }
 
-// Words first .. words of the staged ones (the last copy of an upload).
-static int upload_commit(cliff_ctx *c, size_t words, size_t first = 0) {
-  HIP_TRY(hipMemcpyAsync(c->dev_ops + first, c->pinned + first, (words - first) * 8, hipMemcpyHostToDevice, c->stream));
+static int upload_commit(cliff_ctx *c, size_t words) {
+  HIP_TRY(hipMemcpyAsync(c->dev_ops, c->pinned, words * 8, hipMemcpyHostToDevice, c->stream));
   HIP_TRY(hipEventRecord(c->upload_done, c->stream));
   c->upload_pending = true;
   return CLIFF_OK;
@@ -559,6 +565,66 @@ static bool capturing(const cliff_ctx *c) {
   (void)hipGetLastError();
   return true;
 }
+
+// An upload written piece by piece: what is written goes to the device while
+// the next pieces are.  Long ones (not while capturing, where the staged words
+// are read again at replay) pass through two halves of a small staging area:
+// pinning the whole of a 33 MB stream took 8 ms of a context's first call.
+struct StagedUpload {
+  static constexpr size_t kHalf = size_t(1) << 18;   // words (2 MB: a copy of 40 us beside its launch of 5)
+  cliff_ctx *c = nullptr;
+  uint64_t *host = nullptr, *dev = nullptr;
+  size_t half = 0, fill = 0, sent = 0;   // words of a half (0: one area for all); written since `sent`
+  uint32_t h = 0;
+  bool used[2] = {false, false};
+  // pieces of at most `piece` words, `words` in all
+  int begin(cliff_ctx *ctx, size_t words, size_t piece) {
+    c = ctx;
+    const size_t want = std::max(kHalf, piece);
+    half = words > 2 * want && !capturing(c) ? want : 0;
+    return upload_reserve(c, words, &host, &dev, half ? 2 * half : words);
+  }
+  // room for `words` (at most a piece) at the returned place; then fill += written
+  int room(size_t words, uint64_t **at) {
+    if (half ? fill + words > half : fill >= kHalf) {
+      const int rc = flush();
+      if (rc) return rc;
+    }
+    *at = host + (half ? h * half : sent) + fill;
+    return CLIFF_OK;
+  }
+  int flush() {
+    if (!fill) return CLIFF_OK;
+    HIP_TRY(hipMemcpyAsync(dev + sent, host + (half ? h * half : sent), fill * 8, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(hipEventRecord(c->upload_done, c->stream));
+    c->upload_pending = true;
+    sent += fill;
+    fill = 0;
+    if (half) {
+      HIP_TRY(hipEventRecord(c->half_done[h], c->stream));
+      used[h] = true;
+      h ^= 1;
+      if (used[h]) HIP_TRY(hipEventSynchronize(c->half_done[h]));
+    }
+    return CLIFF_OK;
+  }
+  // an array of 32-bit words, from a 64-bit boundary on; *on_dev: its address there
+  int put(const uint32_t *src, size_t count, const uint32_t **on_dev) {
+    *on_dev = reinterpret_cast<const uint32_t *>(dev + sent + fill);
+    while (count) {
+      const size_t now = std::min(count, size_t(8192)), w = (now + 1) / 2;
+      uint64_t *at = nullptr;
+      const int rc = room(w, &at);
+      if (rc) return rc;
+      at[w - 1] = 0;
+      memcpy(at, src, now * 4);
+      fill += w;
+      src += now;
+      count -= now;
+    }
+    return CLIFF_OK;
+  }
+};
 
 // Decoded gate streams: layers in steps of 64 ops, each rounded up, at most
 // kDecodeSteps (256 MB) at a time.
@@ -746,7 +812,6 @@ extern "C" int cliff_apply_layers(cliff_tab *t, const uint8_t *h, const uint8_t 
   const uint32_t n = t->d.n;
   int rc = check_layer_args(n, h, s, ctrl, tgt, npairs, depth);
   if (rc) return rc;
-  constexpr size_t kSendWords = size_t(1) << 18;     // a copy of 2 MB costs 40 us beside its launch of 5
   constexpr size_t kLooseWords = size_t(1) << 22;
   const size_t room = layer_room(n, npairs);
   std::vector<uint32_t> offs(size_t(depth) + 1);
@@ -760,44 +825,30 @@ extern "C" int cliff_apply_layers(cliff_tab *t, const uint8_t *h, const uint8_t 
   if (bound > 0xFFFFFFF0ull) return fail(CLIFF_EINVAL, "cliff_apply_layers: stream too long");
   DeviceGuard g(t->ctx->device);
   const size_t ow = (size_t(depth) + 2) / 2, most = bound + room + 2 * ow + (bound / 64 + depth + 1) / 2 + 1;
-  uint64_t *host = nullptr, *dev = nullptr;
-  rc = upload_reserve(t->ctx, most, &host, &dev);
+  StagedUpload up;
+  rc = up.begin(t->ctx, most, std::max(room, size_t(4096)));
   if (rc) return rc;
   std::vector<uint8_t> state(n);
-  size_t at = 0, sent = 0;
+  size_t at = 0;
   for (uint32_t l = 0; l < depth; ++l) {
     offs[l] = uint32_t(at);
+    uint64_t *to = nullptr;
     size_t cnt = 0;
-    rc = encode_layer(n, l, h, s, ctrl, tgt, npairs, state.data(), host + at, &cnt);
-    if (rc) return rc;   // (a later upload waits for the copies below)
+    rc = up.room(room, &to);
+    if (!rc) rc = encode_layer(n, l, h, s, ctrl, tgt, npairs, state.data(), to, &cnt);
+    if (rc) return rc;   // (a later upload waits for this one's copies)
+    up.fill += cnt;
     at += cnt;
-    if (at - sent >= kSendWords) {
-      rc = upload_commit(t->ctx, at, sent);
-      if (rc) return rc;
-      sent = at;
-    }
   }
   offs[depth] = uint32_t(at);
   const StreamPlan p = plan_stream(t, offs.data(), depth);
-  auto put = [&](const uint32_t *src, size_t count) -> const uint32_t * {
-    const size_t w = (count + 1) / 2;
-    if (!w) return nullptr;
-    host[at + w - 1] = 0;
-    memcpy(host + at, src, count * 4);
-    at += w;
-    return reinterpret_cast<const uint32_t *>(dev + at - w);
-  };
   const uint32_t *doffs = nullptr, *dpoffs = nullptr, *dsched = nullptr;
-  if (p.fused) doffs = put(offs.data(), offs.size());
-  if (p.decode) {
-    dpoffs = put(p.dec.at.data(), p.dec.at.size());
-    dsched = put(p.dec.sched.data(), p.dec.sched.size());
-  }
-  if (at > sent) {
-    rc = upload_commit(t->ctx, at, sent);
-    if (rc) return rc;
-  }
-  return run_encoded(t, dev, offs.data(), doffs, depth, p.decode ? &p.dec : nullptr, p.waves, dpoffs, dsched);
+  if (p.fused) rc = up.put(offs.data(), offs.size(), &doffs);
+  if (!rc && p.decode) rc = up.put(p.dec.at.data(), p.dec.at.size(), &dpoffs);
+  if (!rc && p.decode) rc = up.put(p.dec.sched.data(), p.dec.sched.size(), &dsched);
+  if (!rc) rc = up.flush();
+  if (rc) return rc;
+  return run_encoded(t, up.dev, offs.data(), doffs, depth, p.decode ? &p.dec : nullptr, p.waves, dpoffs, dsched);
 }
 
 extern "C" int cliff_apply_encoded(cliff_tab *t, const uint64_t *dev_ops, const uint32_t *offs,

@@ -110,3 +110,29 @@ def test_many_tableaux(ctx, rows, short):
     for t, (n, _), (_, _, gates) in zip(tabs, shapes, streams):
         assert _same(t.export(), _ref(n, gates, 2)), "n = %d" % n
         t.close()
+
+
+# streams that pass through the staging area in halves (more than 4 MB, the
+# last qubit unpaired), and one whose layers leave most qubits without a gate
+@pytest.mark.parametrize("n,npairs,depth,p", [(1501, 750, 900, 0.5), (3000, 10, 1500, 0.01)])
+def test_long_layers_through_the_staging_area(ctx, n, npairs, depth, p):
+    from paper_2408_00384_amd import DeviceTableau, cliff_apply_encoded, cliff_encode_layers
+    rng = np.random.default_rng([97, n])
+    h, s = ((rng.random((depth, n)) < p).astype(np.uint8) for _ in range(2))
+    perm = rng.permuted(np.tile(np.arange(n, dtype=np.uint32), (depth, 1)), axis=1)
+    ctrl, tgt = np.ascontiguousarray(perm[:, :npairs]), np.ascontiguousarray(perm[:, npairs:2 * npairs])
+    words, offs = cliff_encode_layers(n, h, s, ctrl, tgt)
+    dev = _upload(words)
+    t, u = DeviceTableau(ctx, n, 1), DeviceTableau(ctx, n, 1)
+    for _ in range(2):
+        t.apply_layers(h, s, ctrl, tgt)
+        cliff_apply_encoded(u.handle, dev.data_ptr(), offs)
+    rows = np.arange(0, 2 * n, 61, dtype=np.uint32)
+    assert _same(t.export_rows(rows), u.export_rows(rows))
+    bad = ctrl.copy()
+    bad[depth - 1, 0] = tgt[depth - 1, 0]          # refused after most of it was staged: no change
+    with pytest.raises(Exception, match="control == target"):
+        t.apply_layers(h, s, bad, tgt)
+    assert _same(t.export_rows(rows), u.export_rows(rows))
+    t.close()
+    u.close()
