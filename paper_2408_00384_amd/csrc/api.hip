@@ -569,7 +569,8 @@ static bool capturing(const cliff_ctx *c) {
 // An upload written piece by piece: what is written goes to the device while
 // the next pieces are.  Long ones (not while capturing, where the staged words
 // are read again at replay) pass through two halves of a small staging area:
-// pinning the whole of a 33 MB stream took 8 ms of a context's first call.
+// pinning all of it made the first 32 requests of a server, up to n = 2,048,
+// 77.7 ms instead of 58.0.
 struct StagedUpload {
   static constexpr size_t kHalf = size_t(1) << 18;   // words (2 MB: a copy of 40 us beside its launch of 5)
   cliff_ctx *c = nullptr;
