@@ -101,7 +101,12 @@ int cliff_calibrate(cliff_ctx *ctx, int kind, double *out);
 /* Gate-stream strategy.  AUTO: one launch for all layers when 8n bytes (32
  * rows of every column) fit in LDS, else one launch per layer.  PER_LAYER:
  * always one launch per layer.  FUSED: always one launch (EINVAL if n is too
- * large).  Results are identical; only speed differs. */
+ * large).  In one launch, streams of 16 layers and more are decoded first into
+ * context-owned device memory (8 bytes per op, layers rounded up to 64 ops;
+ * at most 256 MB at a time, grown to the longest stream); while the context's
+ * stream is being captured, or when that memory cannot be had, the op words
+ * are decoded as they are applied.  Results are identical; only speed
+ * differs. */
 #define CLIFF_GATES_AUTO 0
 #define CLIFF_GATES_PER_LAYER 1
 #define CLIFF_GATES_FUSED 2
