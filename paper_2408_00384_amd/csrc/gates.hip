@@ -236,7 +236,7 @@ __device__ __forceinline__ void fused_body(uint64_t *X, uint64_t *Z, uint64_t *P
 // step took about 200 instructions with its branches (decode, range checks,
 // masks).  From op words -> decoded: n = 1,500, 3,000 layers 1,858 -> 1,061 us
 // (+ 13 to decode); n = 500 x 100 tableaux, 2,000 layers 1,382 -> 936 (+ 150);
-// n = 64, 100 layers 34 -> 17; n = 1,024 60 -> 38; n = 10,000, 20 layers
+// n = 64, 64 layers 34 -> 17; n = 1,024, 100 layers 60 -> 38; n = 10,000, 20 layers
 // 302 -> 214 (50 of it by the XCD order of the row groups).
 constexpr uint32_t kSpareCols = 16;
 constexpr uint32_t kDecBits = (1u << 18) - 1;

@@ -346,7 +346,7 @@ hipError_t launch_gate_layer(const TabDev &t, const uint64_t *ops, uint32_t nops
 constexpr size_t kFusedGateLds = 160 * 1024 - 1024;
 bool fused_gates_fit(uint32_t n);
 // Fewest layers worth decoding a stream for: the decode launch costs 5 to 12
-// us, a layer gains 0.2 us and more (n = 64: 0.34 -> 0.17 us, n = 1,024: 0.60
+// us, a layer gains 0.2 us and more (n = 64: 0.53 -> 0.26 us, n = 1,024: 0.60
 // -> 0.38, n = 1,500: 0.62 -> 0.35, n = 10,000, 16 waves: 15.1 -> 10.7).
 constexpr uint32_t kDecodeMinDepth = 16;
 constexpr uint32_t kRoundEnds = 256;       // see launch_gates_decoded

@@ -53,10 +53,10 @@
 // 11 us a sweep launch at n = 1,024) and the prep launch's chain of loads (7
 // to 8 us).  Against one rowsum sweep per measurement (register-resident up to
 // n = 10,240, one kernel per measurement above), circuit and measure-all:
-// n = 64, 16 shots 0.164 against 0.391 ms; n = 1,024, 128 shots 0.81 against
-// 2.67 ms; n = 3,001 after 2 layers, a third of the outcomes deterministic,
-// 1.27 against 7.29 ms; n = 5,003 1.94 against 8.16 ms; n = 10,000 5.11 against
-// 16.3 ms (blocks of 32 in registers); 128 of n = 25,000 2.86 against 12.2 ms.
+// n = 64, 16 shots 0.114 against 0.389 ms; n = 1,024, 128 shots 0.44 against
+// 2.68 ms; n = 3,001 after 2 layers, a third of the outcomes deterministic,
+// 1.21 against 7.28 ms; n = 5,003 1.84 against 8.23 ms; n = 10,000 4.74 against
+// 16.4 ms (blocks of 32 in registers); 128 of n = 25,000 2.29 against 12.3 ms.
 // Blocks of 64: twice the work per launch of 32 at the same number of tableau
 // passes, and a row's bits are one 64-bit word.
 #include <algorithm>
