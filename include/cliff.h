@@ -103,7 +103,7 @@ int cliff_calibrate(cliff_ctx *ctx, int kind, double *out);
  * always one launch per layer.  FUSED: always one launch (EINVAL if n is too
  * large).  In one launch, streams of 16 layers and more are decoded first into
  * context-owned device memory (8 bytes per op, layers rounded up to 64 ops;
- * at most 256 MB at a time, grown to the longest stream); while the context's
+ * at most 576 MB at a time, grown to the longest stream); while the context's
  * stream is being captured, or when that memory cannot be had, the op words
  * are decoded as they are applied.  Results are identical; only speed
  * differs. */

@@ -110,17 +110,19 @@ constexpr uint32_t LUT_AND_XNOR = 0x90;    // a & ~(b ^ c)
 constexpr uint32_t LUT_AND_XOR_BC = 0x60;  // a & (b ^ c)
 constexpr uint32_t LUT_SELECT = 0xCA;      // a ? b : c
 
-// Apply a single-qubit code to x / z words of rows (32, 64 or 128 rows at once).
-// Its sign flips by x or z alone (those of a Pauli in the code; kSqPauli) and
-// the rest come apart, since most codes have none of the former.
+// Apply a single-qubit code (bits SH .. SH + 6 of c) to x / z words of rows (32,
+// 64 or 128 rows at once).  Its sign flips by x or z alone (those of a Pauli in
+// the code; kSqPauli) and the rest come apart, since most codes have none of
+// the former.
 constexpr uint32_t kSqPauli = 0x30;
-template <typename T>
+template <uint32_t SH = 0, typename T>
 __device__ __forceinline__ void sq_pauli(uint32_t c, T x, T z, T &racc) {
-  racc = bop3<LUT_AND_XOR>(x, mask_if<T>((c >> 4) & 1u), bop3<LUT_AND_XOR>(z, mask_if<T>((c >> 5) & 1u), racc));
+  racc = bop3<LUT_AND_XOR>(x, mask_if<T>((c >> (SH + 4)) & 1u),
+                           bop3<LUT_AND_XOR>(z, mask_if<T>((c >> (SH + 5)) & 1u), racc));
 }
-template <typename T>
+template <uint32_t SH = 0, typename T>
 __device__ __forceinline__ void sq_rest(uint32_t c, T &x, T &z, T &racc) {
-  auto bit = [c](uint32_t k) { return mask_if<T>((c >> k) & 1u); };   // all-ones if set
+  auto bit = [c](uint32_t k) { return mask_if<T>((c >> (SH + k)) & 1u); };   // all-ones if set
   racc = bop3<LUT_AND_XOR>(x & z, bit(6), racc);
   const T nx = bop3<LUT_ANDN_XOR>(x, bit(0), z & bit(1));   // (x & m00) ^ (z & m01)
   const T nz = bop3<LUT_ANDN_XOR>(z, bit(3), x & bit(2));   // (x & m10) ^ (z & m11)

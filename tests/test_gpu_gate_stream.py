@@ -136,3 +136,27 @@ def test_long_layers_through_the_staging_area(ctx, n, npairs, depth, p):
     assert _same(t.export_rows(rows), u.export_rows(rows))
     t.close()
     u.close()
+
+
+@pytest.mark.parametrize("rows", [32, 64])
+def test_many_tableaux_in_parts(ctx, rows):
+    """Streams of over 512 MB decoded, so that they go through the scratch in
+    parts of all tableaux' layers: the shortest stream has 16 layers, the
+    longest 80,000 of one gate each."""
+    from paper_2408_00384_amd import DeviceTableau, cliff_apply_encoded_many
+    shapes = [(40, [1, 40] * 40000), (3, [1, 2, 3, 0] * 4), (70, [70, 65, 1] * 30)]
+    streams = [_stream(n, sizes, 7 + i) for i, (n, sizes) in enumerate(shapes)]
+    dev = [_upload(w) for w, _, _ in streams]
+    copies = [14, 2, 2]            # 14 x 80,000 steps of 64 ops
+    tabs, ds, os_, refs = [], [], [], []
+    for (n, _), (_, o, gates), d, k in zip(shapes, streams, dev, copies):
+        ref = _ref(n, gates)
+        for _ in range(k):
+            tabs.append(DeviceTableau(ctx, n, 1))
+            ds.append(d.data_ptr())
+            os_.append(o)
+            refs.append(ref)
+    cliff_apply_encoded_many([t.handle for t in tabs], ds, os_, rows)
+    for t, ref in zip(tabs, refs):
+        assert _same(t.export(), ref)
+        t.close()
