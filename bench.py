@@ -13,11 +13,10 @@ One JSON line is printed with circuits/s, the roofline of the dominant kernel
 and the CPU oracle timed on a bounded sample of the same workload.  At the
 default size the dominant kernel is k_lr_sweep (64 measurements applied at
 a time as one low-rank update of the tableau, which stays in the Infinity
-Cache), reported against the ALU: the method's algorithmic 32-bit lane
-operations (from the device-side support counters) over the kernel's time
-(HIP events recorded on its stream around every launch of the timed steps),
-against the MI355X's vector rate.  The HBM-equivalent rate of the same work
-is kept as effective_alg_gbs.
+Cache), reported as the tableau bytes it reads and writes over its time (HIP
+events around every launch of as many steps again after the timed ones)
+against the HBM peak.  The operations of one sweep per measurement over the
+same time are kept as method_ops_per_s.
 
 Further legs on the same line: the n = 64 and n = 1,024 workloads, the
 batched 4,096-circuit workload (batched vs one circuit per launch, wall and
@@ -38,9 +37,6 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E peak
 LDS_PEAK_GBS = 256 * 128 * 2.4   # 256 CUs x 128 B/clk x 2.4 GHz = 78,643 GB/s
-# MI355X vector ALU: 157.3 TFLOP/s fp32 counts a fused multiply-add as two
-# operations, so the chip retires 78.6e12 32-bit lane operations per second
-VALU_PEAK_TOPS = 157.3 / 2
 
 WORKLOADS = {
     "small": dict(desc="plain CHP n=64, 64 layers, measure all, 16 shots", steps=20, warmup=3),
@@ -49,42 +45,42 @@ WORKLOADS = {
 }
 
 
-def alu_roofline(counters, n, steps, sweep_ms, launches):
-    """Roofline of the measuring kernel (k_lr_sweep).
+def sweep_roofline(counters, n, steps, sweep_ms, launches):
+    """Roofline of the measuring kernel (k_lr_sweep): a launch reads and writes
+    the tableau's X and Z once (launches that only plan or sign a block, one
+    each a pass, do not), so its bytes are 32 n W per 64 measurements, against
+    the HBM peak.
 
-    Per random measurement with pivot-row support s (columns where the pivot
-    row is not I), s_x (with an X part) and s_z (with a Z part), the sweep
-    does per 64-bit row word of a supported column: the anticommuting rows
-    (1 op, 2 for Y), the -1 rows (1), the mod-4 counter (3) and the updates of
-    the planes the pivot row touches (1 each): 4 s + 2 (s_x + s_z) word
-    operations, i.e. 8 s + 4 (s_x + s_z) = 4 (2 s + s_x + s_z) 32-bit lane
+    Beside it the work of the method it stands for, one sweep per measurement:
+    per random measurement with pivot-row support s (columns where the pivot
+    row is not I), s_x (with an X part) and s_z (with a Z part) that sweep does
+    per 64-bit row word of a supported column the anticommuting rows (1 op, 2
+    for Y), the -1 rows (1), the mod-4 counter (3) and the updates of the
+    planes the pivot row touches (1 each): 4 (2 s + s_x + s_z) 32-bit lane
     operations per row word.  The device counters give sum(2 s + s_x + s_z)
     through the algorithmic bytes (8 W (2 s + s_x + s_z + 3) + 80 n per random
-    measurement, 8 n W per deterministic one).  The low-rank update does the
-    same measurements with fewer operations (the phase terms are summed once
-    per block of 64); the count stays the method's."""
+    measurement, 8 n W per deterministic one).  The low-rank update executes a
+    fraction of those."""
     W = (2 * n + 63) // 64
     nr, nd = counters["random"], counters["deterministic"]
     sup = (counters["alg_bytes"] - nr * (24 * W + 80 * n) - nd * 8 * n * W) // (8 * W)
-    ops_step = 4 * W * sup
-    ops_launch = steps * ops_step / max(1, launches)
     avg_s = sweep_ms * 1e-3 / max(1, launches)
-    achieved = ops_launch / avg_s / 1e12 if avg_s > 0 else 0.0
-    sweep_bytes = counters["alg_bytes"] - (8 * W * 3 + 80 * n) * nr
+    launch_bytes = 32 * n * W
+    achieved = launch_bytes / avg_s / 1e9 if avg_s > 0 else 0.0
     return {
         "kernel": "k_lr_sweep (64 measurements per launch as one low-rank update; the launch also plans the next 64 "
                   "and updates the signs of the last)",
-        "bound": "alu", "achieved": achieved, "peak": VALU_PEAK_TOPS, "unit": "TOP/s",
-        "frac": achieved / VALU_PEAK_TOPS,
+        "bound": "memory", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        "frac": achieved / HBM_PEAK_GBS,
         "traffic": None,
         "launches": launches, "avg_launch_us": avg_s * 1e6,
-        "alg_lane_ops_per_launch": ops_launch,
+        "bytes_per_launch": launch_bytes,
         "support_sum_per_step": int(sup),
-        "effective_alg_gbs": steps * sweep_bytes / (sweep_ms * 1e-3) / 1e9 if sweep_ms > 0 else 0.0,
-        "note": "32-bit lane operations 4 W sum(2 s + s_x + s_z) per launch over the launch time; peak "
-                "157.3 TFLOP/s fp32 / 2 = 78.6e12 lane ops/s (65.8e12 measured for v_xor_b32 by "
-                "cliff_calibrate); effective_alg_gbs = the bytes a sweep per measurement would stream over "
-                "the same time (not a roofline)",
+        "method_ops_per_s": steps * 4 * W * sup / (sweep_ms * 1e-3) if sweep_ms > 0 else 0.0,
+        "note": "bytes: X and Z read and written once per launch (at n = 10,000 the 50 MB stay in the last-level cache), "
+                "over the launch time by HIP events; method_ops_per_s: 32-bit lane operations of one sweep per "
+                "measurement, 4 W sum(2 s + s_x + s_z), over the same time (not a roofline: the kernel executes a "
+                "fraction of them)",
     }
 
 
@@ -723,10 +719,6 @@ def main():
         step()
         print("# warmup %d done" % (i + 1), file=sys.stderr, flush=True)
     torch.cuda.synchronize()
-    # per-kernel HIP events on the library's stream for every launch of the
-    # timed steps (a few microseconds per launch of overhead)
-    if not args.no_profile:
-        P.cliff_ctx_profile(ctx.handle, True)
     stream = torch.cuda.current_stream()
     ev0, ev1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     t0 = time.perf_counter()
@@ -747,6 +739,14 @@ def main():
     if gold is not None and c.shots == 1:
         parity = bool(np.array_equal(out[0], gold[: c.n]))
 
+    # kernel times: the same steps again with HIP events around every launch,
+    # which cost a few microseconds each (2.4 ms a step at n = 10,000), so the
+    # timed steps go without
+    if not args.no_profile:
+        P.cliff_ctx_profile(ctx.handle, True)
+        for i in range(steps):
+            step()
+        torch.cuda.synchronize()
     prof = {k: P.cliff_ctx_profile_read(ctx.handle, k) for k in P.PROF_KINDS}
     if not args.no_profile:
         P.cliff_ctx_profile(ctx.handle, False)
@@ -755,7 +755,7 @@ def main():
     alg_step = counters["alg_bytes"]
     blk_ms, blk_launches = prof["blocked"]
     meas_ms = sum(prof[k][0] for k in ("select", "sweep", "final", "blocked"))
-    roofline = alu_roofline(counters, c.n, steps, blk_ms, blk_launches)
+    roofline = sweep_roofline(counters, c.n, steps, blk_ms, blk_launches)
     tab.close()
     ctx.close()
     print("# kernels over %d steps: " % steps
