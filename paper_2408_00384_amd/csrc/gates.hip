@@ -755,7 +755,7 @@ hipError_t launch_gates_decoded(const TabDev &t, const uint64_t *ops, const uint
   constexpr size_t kMore = kSpareCols * 8 + 8;
   static const hipError_t attr = allow_gate_lds(reinterpret_cast<const void *>(k_gates_decoded), kMore);
   if (attr != hipSuccess) return attr;
-  const uint32_t gx = decode_grid(depth, 4096), gz = (max_steps + 3) / 4;
+  const uint32_t gx = decode_grid(depth, 4096), gz = std::min((max_steps + 3) / 4, 1024u);
   k_decode_ops<<<dim3(gx, 1, gz), 256, 0, st>>>(ops, dev_offs, dev_poffs, depth, t.n, dec);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -774,7 +774,7 @@ hipError_t launch_gates_many_decoded(const ManyDesc *dev_descs, uint32_t count, 
   static const hipError_t attr[3] = {allow_gate_lds(fns[0], kMore), allow_gate_lds(fns[1], kMore),
                                      allow_gate_lds(fns[2], kMore)};
   if (attr[v] != hipSuccess) return attr[v];
-  const uint32_t gx = decode_grid(max_depth, 256), gz = (max_steps + 3) / 4;
+  const uint32_t gx = decode_grid(max_depth, 256), gz = std::min((max_steps + 3) / 4, 1024u);
   k_plan_many<<<count, 1024, 0, st>>>(dev_descs, waves);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
