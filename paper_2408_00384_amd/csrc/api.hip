@@ -750,10 +750,16 @@ static int run_encoded(cliff_tab *t, const uint64_t *dev_ops, const uint32_t *ho
     return CLIFF_OK;
   }
   // Layer by layer, for as many row words at a time as stay in the last-level
-  // cache from one layer to the next (kLayerBytes of X and Z).
+  // cache from one layer to the next (kLayerBytes of X and Z), where a part of
+  // a layer's columns (an op has up to two) still takes kLayerPartBytes: more
+  // launches cost more than the cache gives below that.  A layer at n = 25,000
+  // in one part and in two: 12,500 CNOTs 114 and 90 us, 4,000 44 and 40, 3,000
+  // 32 and 34, 10 3.8 and 9; at n = 100,000, in one and in 25: 10 4.5 and 93.
   const uint32_t W = t->dev.W;
   const size_t fit = std::max<size_t>(1, kLayerBytes / (size_t(t->d.n) * 16));
-  const uint32_t parts = depth > 1 ? uint32_t((W + fit - 1) / fit) : 1;
+  const uint32_t most = uint32_t((W + fit - 1) / fit);
+  const size_t cols = std::min<size_t>(t->d.n, 2 * (size_t(host_offs[depth]) - host_offs[0]) / std::max(depth, 1u));
+  const uint32_t parts = depth > 1 && cols * W * 16 >= most * kLayerPartBytes ? most : 1;
   const uint32_t step = ((W + parts - 1) / parts + 63) / 64 * 64;
   for (uint32_t w0 = 0; w0 < W; w0 += step) {
     for (uint32_t l = 0; l < depth; ++l) {

@@ -340,6 +340,7 @@ hipError_t launch_fold_pending(const TabDev &t, hipStream_t st);
 // (row words w0 .. w1).  kLayerBytes: X and Z of as many row words as a call
 // of several layers takes through them all at a time, of the 256 MB cache.
 constexpr size_t kLayerBytes = size_t(160) << 20;
+constexpr size_t kLayerPartBytes = size_t(48) << 20;   // of a layer's columns, for a launch of its own to pay
 hipError_t launch_gate_layer(const TabDev &t, const uint64_t *ops, uint32_t nops, uint32_t w0, uint32_t w1,
                              hipStream_t st);
 // LDS budget of the fused all-layers gate kernel (8 bytes per qubit).

@@ -160,3 +160,37 @@ def test_many_tableaux_in_parts(ctx, rows):
     for t, ref in zip(tabs, refs):
         assert _same(t.export(), ref)
         t.close()
+
+
+# n past the one-launch kernels: layers of most qubits go through the cache in
+# parts of the row words, layers of few qubits in one launch each
+@pytest.mark.parametrize("n,pairs,depth,launches", [(21000, 10, 30, 30), (21000, 10500, 3, 6), (30000, 1, 5, 5)])
+def test_row_parts_only_where_layers_fill_them(ctx, n, pairs, depth, launches):
+    from paper_2408_00384_amd import (DeviceTableau, cliff_apply_encoded, cliff_ctx_profile, cliff_ctx_profile_read,
+                                      cliff_encode_layers)
+    rng = np.random.default_rng([98, n, pairs])
+    perm = np.stack([rng.permutation(n)[: 2 * pairs] for _ in range(depth)]).astype(np.uint32)
+    zero = np.zeros((depth, n), np.uint8)
+    words, offs = cliff_encode_layers(n, zero, zero, np.ascontiguousarray(perm[:, :pairs]),
+                                      np.ascontiguousarray(perm[:, pairs:]))
+    dev = _upload(words)
+    t = DeviceTableau(ctx, n, 1)
+    cliff_ctx_profile(ctx.handle, True)
+    try:
+        cliff_apply_encoded(t.handle, dev.data_ptr(), offs)
+        got = cliff_ctx_profile_read(ctx.handle, "gate")[1]
+    finally:
+        cliff_ctx_profile(ctx.handle, False)
+    assert got == launches
+    # CNOTs on |0...0>: destabilizer X_j and stabilizer Z_j spread as the bits below
+    q = perm[:, :].ravel()[:8]
+    x, z = np.eye(n, dtype=np.uint8)[q], np.eye(n, dtype=np.uint8)[q]
+    for l in range(depth):
+        for c, g in zip(perm[l, :pairs], perm[l, pairs:]):
+            x[:, g] ^= x[:, c]
+            z[:, c] ^= z[:, g]
+    gx, gz, gr = t.export_rows(np.concatenate([q, q + n]).astype(np.uint32))
+    k = len(q)
+    assert np.array_equal(gx[:k], x) and not gz[:k].any() and np.array_equal(gz[k:], z) and not gx[k:].any()
+    assert not gr.any()
+    t.close()
