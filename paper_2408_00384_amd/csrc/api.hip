@@ -1344,16 +1344,20 @@ static int check_abort(cliff_tab *t) {
 
 // The last pass's cnt outcomes per shot to host_out[s * ld + i] and its random
 // flags to host_random[i] (each nullable); waits for the stream.  The device
-// transposes and writes pinned memory, so that the host copies rows.  Two
+// transposes and writes pinned memory, so that the host copies rows; short
+// rows (packed_results) come without gaps, and are copied all at once where the
+// caller's rows have none either.  Two
 // copies to pageable memory and a byte-wise transposition on the host took
 // 217 of 419 us at 1,000 shots of n = 301, 30 of 148 us at n = 64 and 340 of 784
 // us at n = 1,024, one shot.
 constexpr size_t kResultBytes = size_t(16) << 20;
 static int read_results(cliff_tab *t, size_t cnt, uint8_t *host_out, size_t ld, uint8_t *host_random) {
   cliff_ctx *c = t->ctx;
-  const size_t S = t->d.S, pitch = (cnt + 63) / 64 * 64;
-  const size_t most = std::max<size_t>(1, kResultBytes / pitch), rows = host_out ? S : 0;
-  const size_t need = pitch * (1 + std::min(rows, most));
+  const size_t S = t->d.S, rows = host_out ? S : 0;
+  const bool packed = packed_results(cnt, rows);
+  const size_t head = (cnt + 63) / 64 * 64, pitch = packed ? cnt : head;   // random flags; a shot's bytes
+  const size_t most = std::max<size_t>(1, kResultBytes / pitch);
+  const size_t need = head + (pitch * std::min(rows, most) + 63) / 64 * 64;
   if (c->results_bytes < need) {
     if (c->results) HIP_TRY(hipHostFree(c->results));   // (idle: every user waits for its stream)
     c->results = nullptr;
@@ -1362,12 +1366,12 @@ static int read_results(cliff_tab *t, size_t cnt, uint8_t *host_out, size_t ld, 
     HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&c->results), bytes, hipHostMallocDefault));
     c->results_bytes = bytes;
   }
-  uint8_t *rnd = c->results, *out = c->results + pitch;
+  uint8_t *rnd = c->results, *out = c->results + head;
   size_t s0 = 0;
   do {
     const size_t now = std::min(most, rows - s0);
     c->prof.begin(PK_OTHER, c->stream);
-    const hipError_t e = launch_emit(t->dev, uint32_t(cnt), uint32_t(s0), uint32_t(now), out, pitch, rnd, c->stream);
+    const hipError_t e = launch_emit(t->dev, uint32_t(cnt), uint32_t(s0), uint32_t(now), packed, out, pitch, rnd, c->stream);
     c->prof.end(PK_OTHER, c->stream);
     HIP_TRY(e);
     HIP_TRY(hipStreamSynchronize(c->stream));
@@ -1375,7 +1379,9 @@ static int read_results(cliff_tab *t, size_t cnt, uint8_t *host_out, size_t ld, 
       const int arc = check_abort(t);
       if (arc) return arc;
     }
-    for (size_t s = 0; s < now; ++s) memcpy(host_out + (s0 + s) * ld, out + s * pitch, cnt);
+    if (packed && ld == cnt) memcpy(host_out + s0 * ld, out, now * cnt);
+    else
+      for (size_t s = 0; s < now; ++s) memcpy(host_out + (s0 + s) * ld, out + s * pitch, cnt);
     s0 += now;
   } while (s0 < rows);
   if (host_random) memcpy(host_random, rnd, cnt);

@@ -585,6 +585,24 @@ __global__ void __launch_bounds__(256) k_emit(TabDev t, uint32_t cnt, uint32_t s
   if (blockIdx.y == 0 && tid < iw) rnd[i0 + tid] = t.kind[i0 + tid];
 }
 
+// The same for short rows, written without gaps (fewer than 64 outcomes): a
+// thread gathers 16 bytes, each read from a cached line of the staging.
+__global__ void __launch_bounds__(256) k_emit_packed(TabDev t, uint32_t cnt, uint32_t s0, uint32_t rows,
+                                                     uint8_t *__restrict__ out, uint8_t *__restrict__ rnd) {
+  const uint32_t total = rows * cnt;   // (the caller's parts are of 16 MB at most)
+  const uint32_t o = (blockIdx.x * 256 + threadIdx.x) * 16;
+  if (o < total) {
+    uint32_t s = o / cnt, i = o % cnt, v[4] = {};
+#pragma unroll
+    for (uint32_t k = 0; k < 16; ++k) {
+      if (o + k < total) v[k / 4] |= uint32_t(t.out[size_t(i) * t.S + s0 + s]) << (8 * (k % 4));
+      if (++i == cnt) i = 0, ++s;
+    }
+    *reinterpret_cast<uint4 *>(out + o) = make_uint4(v[0], v[1], v[2], v[3]);
+  }
+  if (blockIdx.x == 0 && threadIdx.x < cnt) rnd[threadIdx.x] = t.kind[threadIdx.x];
+}
+
 __global__ void __launch_bounds__(256) k_record(TabDev t, uint32_t cnt, uint8_t *__restrict__ rec, size_t ld,
                                                 size_t col0, uint8_t *__restrict__ rnd) {
   const size_t total = size_t(cnt) * t.S;
@@ -792,9 +810,14 @@ hipError_t launch_gates_many_decoded(const ManyDesc *dev_descs, uint32_t count, 
   return hipGetLastError();
 }
 
-hipError_t launch_emit(const TabDev &t, uint32_t cnt, uint32_t s0, uint32_t rows, uint8_t *out, size_t pitch,
-                       uint8_t *rnd, hipStream_t st) {
+hipError_t launch_emit(const TabDev &t, uint32_t cnt, uint32_t s0, uint32_t rows, bool packed, uint8_t *out,
+                       size_t pitch, uint8_t *rnd, hipStream_t st) {
   if (cnt == 0) return hipSuccess;
+  if (packed) {
+    const size_t groups = (size_t(rows) * cnt + 15) / 16;
+    k_emit_packed<<<uint32_t(std::max<size_t>(1, (groups + 255) / 256)), 256, 0, st>>>(t, cnt, s0, rows, out, rnd);
+    return hipGetLastError();
+  }
   k_emit<<<dim3((cnt + 63) / 64, rows ? (rows + 63) / 64 : 1), 256, 0, st>>>(t, cnt, s0, rows, out, pitch, rnd);
   return hipGetLastError();
 }

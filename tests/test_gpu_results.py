@@ -70,3 +70,49 @@ def test_cond_paulis_vs_oracle(ctx, n, shots, k):
         x, z, rr = r.get()
         assert np.array_equal(gx, x) and np.array_equal(gz, z) and np.array_equal(gr[s], rr)
     t.close()
+
+
+# rows of fewer than 48 outcomes of more than 64 shots come without gaps, 16
+# bytes a thread: ends inside and at a thread's bytes, either side of both
+# limits, and two parts of 16 MB
+@pytest.mark.parametrize("n,shots,k", [(9, 64, 9), (9, 65, 9), (16, 255, 16), (20, 257, 17), (70, 100, 47),
+                                       (70, 100, 48), (9, 4097, 1), (9, 262147, 7), (9, 3000001, 8)])
+def test_few_outcomes_of_many_shots(ctx, n, shots, k):
+    import torch
+    from paper_2408_00384_amd import DeviceTableau, cliff_measure_async, cliff_measure_record, cliff_tab_read_outcomes
+    c = layered_circuit(n, 6, 1, gen_seed=[97, n], circuit_id=33)
+    q = np.random.default_rng(k).permutation(n)[:k].astype(np.uint32)
+    rec = torch.zeros((shots, k), dtype=torch.uint8, device="cuda:0")
+    rnd = torch.zeros(k, dtype=torch.uint8, device="cuda:0")
+    torch.cuda.synchronize()
+    t = DeviceTableau(ctx, n, shots).apply_circuit_gates(c)
+    cliff_measure_record(t.handle, q, rec.data_ptr(), k, 0, rnd.data_ptr(), c.seed, c.circuit_id)
+    torch.cuda.synchronize()
+    t.init_zero()
+    t.apply_circuit_gates(c)
+    cliff_measure_async(t.handle, q, c.seed, c.circuit_id)
+    out, flags = cliff_tab_read_outcomes(t.handle, k)
+    assert np.array_equal(out, rec.cpu().numpy()) and np.array_equal(flags, rnd.cpu().numpy())
+    t.init_zero()
+    many = np.concatenate([np.arange(n), q]).astype(np.uint32)   # (past n: a second pass into later columns)
+    out, flags = t.apply_circuit_gates(c).measure(many, seed=c.seed, circuit=c.circuit_id)
+    assert np.array_equal(out[:, n:], out[:, q]) and not flags[n:].any()   # (a Z outcome repeats)
+    t.close()
+
+
+def test_one_outcome_costs_less_than_many(ctx):
+    """One outcome of 2^20 shots is read in a fraction of the time of 64."""
+    import time
+    from paper_2408_00384_amd import DeviceTableau, cliff_measure_async, cliff_tab_read_outcomes
+    t = DeviceTableau(ctx, 64, 1 << 20)
+    cliff_measure_async(t.handle, np.arange(64, dtype=np.uint32))
+    best = {}
+    for k in (1, 64):
+        times = []
+        for _ in range(6):
+            t0 = time.perf_counter()
+            cliff_tab_read_outcomes(t.handle, k)
+            times.append(time.perf_counter() - t0)
+        best[k] = min(times)
+    assert best[1] < best[64] / 4, best
+    t.close()
