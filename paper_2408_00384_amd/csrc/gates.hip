@@ -14,6 +14,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -619,55 +620,79 @@ __global__ void __launch_bounds__(256) k_record(TabDev t, uint32_t cnt, uint8_t 
 // 24..25: 1 X, 2 Y, 3 Z) | record column (bits 32..63).  In shot s, when
 // rec[s * ld + column] is 1, every row that anticommutes with the Pauli
 // flips sign: X flips rows with z_a = 1, Z rows with x_a = 1, Y rows with
-// x_a ^ z_a = 1.  The ops only XOR into signs, so their order does not matter:
-// a block takes 64 shots (one a lane) and kCondWords row words, and its waves
-// share out the ops, several loaded at a time (a thread a shot and word, op by
-// op: 15 us a launch at n = 97, 256 shots, a chain of loads; now 5.7).
-constexpr uint32_t kCondWaves = 8, kCondWords = 4, kCondOps = 4;
+// x_a ^ z_a = 1.  The ops only XOR into signs, so their order does not matter.
+// A piece of work is 64 shots (one a lane) and a few row words.  With SPLIT a
+// block takes a piece and its waves share out the ops, several loaded at a time
+// (a thread a shot and word, op by op: 15 us a launch at n = 97, 256 shots, 20
+// ops, a chain of loads; now 5.7); else every wave takes a piece of its own, of
+// one row word.  That is for few ops, which do not fill a block's eight waves:
+// 10^6 shots of n = 100, the whole call, 1 op 34 us (71 split), 5 54 (86), 10 80
+// (95), 15 105 (108), 16 110 (107); 100 ops of 10^5 shots 84 (69).
+constexpr uint32_t kCondWaves = 8, kCondOps = 4;
+constexpr uint32_t kCondSplit = 16;
+constexpr uint32_t cond_words(bool split) { return split ? 4 : 1; }
+template <bool SPLIT>
 __global__ void __launch_bounds__(64 * kCondWaves) k_cond_pauli(TabDev t, const uint64_t *__restrict__ ops, uint32_t k,
                                                                 const uint8_t *__restrict__ rec, size_t ld) {
-  __shared__ uint64_t s_flip[kCondWaves][kCondWords][64];
+  constexpr uint32_t kWords = cond_words(SPLIT);
+  __shared__ uint64_t s_flip[SPLIT ? kCondWaves : 1][kWords][64];
   const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t tiles = (t.S + 63) / 64, total = tiles * ((t.W + kCondWords - 1) / kCondWords);
-  for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) {
-    const uint32_t s = (b % tiles) * 64 + lane, w0 = (b / tiles) * kCondWords;
+  const uint32_t tiles = (t.S + 63) / 64, total = tiles * ((t.W + kWords - 1) / kWords);
+  const uint32_t first = SPLIT ? blockIdx.x : blockIdx.x * kCondWaves + wave, step = SPLIT ? gridDim.x : gridDim.x * kCondWaves;
+  for (uint32_t b = first; b < total; b += step) {
+    const uint32_t s = (b % tiles) * 64 + lane, w0 = (b / tiles) * kWords;
     const uint8_t *row = rec + size_t(min(s, t.S - 1)) * ld;
-    uint64_t flip[kCondWords] = {};
-    for (uint32_t i0 = wave * kCondOps; i0 < k; i0 += kCondWaves * kCondOps) {
-      uint64_t op[kCondOps], x[kCondOps][kCondWords], z[kCondOps][kCondWords];
-      uint32_t bit[kCondOps];
+    uint64_t flip[kWords] = {};
+    auto take = [&](auto count, uint32_t i0) {   // ops i0 .. i0 + count - 1, past k none
+      constexpr uint32_t N = decltype(count)::value;
+      uint64_t op[N], x[N][kWords], z[N][kWords];
+      uint32_t bit[N];
 #pragma unroll
-      for (uint32_t i = 0; i < kCondOps; ++i) {
+      for (uint32_t i = 0; i < N; ++i) {
         op[i] = ops[min(i0 + i, k - 1)];
         const uint32_t a = uint32_t(op[i] & kQubitMask);
         const bool on = i0 + i < k && a < t.n;
         bit[i] = on ? row[op[i] >> 32] & 1u : 0u;
 #pragma unroll
-        for (uint32_t w = 0; w < kCondWords; ++w) {
+        for (uint32_t w = 0; w < kWords; ++w) {
           const size_t at = size_t(on ? a : 0) * t.Wp + min(w0 + w, t.W - 1);
           x[i][w] = t.X[at];
           z[i][w] = t.Z[at];
         }
       }
 #pragma unroll
-      for (uint32_t i = 0; i < kCondOps; ++i) {
+      for (uint32_t i = 0; i < N; ++i) {
         const uint32_t p = uint32_t(op[i] >> 24) & 3u;
         const uint64_t on = 0ull - bit[i];
         // the Pauli's x part (X, Y) flips rows with z = 1, its z part (Y, Z) rows with x = 1
 #pragma unroll
-        for (uint32_t w = 0; w < kCondWords; ++w) flip[w] ^= ((p != 3u ? z[i][w] : 0ull) ^ (p != 1u ? x[i][w] : 0ull)) & on;
+        for (uint32_t w = 0; w < kWords; ++w) flip[w] ^= ((p != 3u ? z[i][w] : 0ull) ^ (p != 1u ? x[i][w] : 0ull)) & on;
       }
+    };
+    using Four = std::integral_constant<uint32_t, kCondOps>;
+    if constexpr (SPLIT) {
+      for (uint32_t i0 = wave * kCondOps; i0 < k; i0 += kCondWaves * kCondOps) take(Four{}, i0);
+    } else {
+      uint32_t i0 = 0;
+      for (; i0 + kCondOps <= k; i0 += kCondOps) take(Four{}, i0);
+      for (; i0 < k; ++i0) take(std::integral_constant<uint32_t, 1>{}, i0);
     }
+    if constexpr (SPLIT) {
 #pragma unroll
-    for (uint32_t w = 0; w < kCondWords; ++w) s_flip[wave][w][lane] = flip[w];
-    __syncthreads();
-    if (wave < kCondWords && w0 + wave < t.W && s < t.S) {
-      uint64_t f = 0;
+      for (uint32_t w = 0; w < kWords; ++w) s_flip[wave][w][lane] = flip[w];
+      __syncthreads();
+      if (wave < kWords && w0 + wave < t.W && s < t.S) {
+        uint64_t f = 0;
 #pragma unroll
-      for (uint32_t v = 0; v < kCondWaves; ++v) f ^= s_flip[v][wave][lane];
-      if (f) t.R[size_t(w0 + wave) * t.S + s] ^= f;
+        for (uint32_t v = 0; v < kCondWaves; ++v) f ^= s_flip[v][wave][lane];
+        if (f) t.R[size_t(w0 + wave) * t.S + s] ^= f;
+      }
+      __syncthreads();
+    } else if (s < t.S) {
+#pragma unroll
+      for (uint32_t w = 0; w < kWords; ++w)
+        if (w0 + w < t.W && flip[w]) t.R[size_t(w0 + w) * t.S + s] ^= flip[w];
     }
-    __syncthreads();
   }
 }
 
@@ -832,8 +857,11 @@ hipError_t launch_record(const TabDev &t, uint32_t cnt, uint8_t *rec, size_t ld,
 hipError_t launch_cond_pauli(const TabDev &t, const uint64_t *ops, uint32_t k, const uint8_t *rec, size_t ld,
                              hipStream_t st) {
   if (k == 0) return hipSuccess;
-  const size_t tiles = size_t((t.S + 63) / 64) * ((t.W + kCondWords - 1) / kCondWords);
-  k_cond_pauli<<<uint32_t(std::min<size_t>(tiles, 4096)), 64 * kCondWaves, 0, st>>>(t, ops, k, rec, ld);
+  const bool split = k >= kCondSplit;
+  const size_t pieces = size_t((t.S + 63) / 64) * ((t.W + cond_words(split) - 1) / cond_words(split));
+  const size_t blocks = split ? pieces : (pieces + kCondWaves - 1) / kCondWaves;
+  (split ? k_cond_pauli<true> : k_cond_pauli<false>)<<<uint32_t(std::min<size_t>(blocks, 4096)), 64 * kCondWaves, 0, st>>>(
+      t, ops, k, rec, ld);
   return hipGetLastError();
 }
 

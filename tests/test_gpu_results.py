@@ -50,6 +50,40 @@ def test_outcomes_match_the_device_record(ctx, n, shots, k):
 @pytest.mark.parametrize("n,shots,k", [(1, 1, 1), (31, 63, 3), (32, 64, 31), (127, 65, 32), (129, 130, 33),
                                        (500, 5, 200)])
 def test_cond_paulis_vs_oracle(ctx, n, shots, k):
+    _cond_paulis(ctx, n, shots, k)
+
+
+# the ops of a wave in fours and one by one, and either side of 16, from where
+# on a block's waves share them
+@pytest.mark.parametrize("n,shots,k", [(33, 1, 4), (64, 64, 5), (65, 600, 7), (130, 129, 15), (130, 129, 16)])
+def test_few_cond_paulis_vs_oracle(ctx, n, shots, k):
+    _cond_paulis(ctx, n, shots, k)
+
+
+def test_one_cond_pauli_costs_less_than_sixteen(ctx):
+    import time
+    import torch
+    from paper_2408_00384_amd import DeviceTableau, cliff_apply_cond_paulis
+    n, shots = 100, 1 << 20
+    t = DeviceTableau(ctx, n, shots)
+    rec = torch.randint(0, 2, (shots, 8), dtype=torch.uint8, device="cuda:0")
+    best = {}
+    for k in (1, 16):
+        q, p, col = np.arange(k, dtype=np.uint32), np.ones(k, np.uint8), np.arange(k, dtype=np.uint32) % 8
+        times = []
+        for _ in range(12):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(8):
+                cliff_apply_cond_paulis(t.handle, q, p, col, rec.data_ptr(), 8)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t0)
+        best[k] = min(times)
+    assert best[1] < best[16] / 2, best
+    t.close()
+
+
+def _cond_paulis(ctx, n, shots, k):
     import torch
     from paper_2408_00384_amd import DeviceTableau, cliff_apply_cond_paulis
     c = layered_circuit(n, 6, 1, gen_seed=[96, n], circuit_id=32)
