@@ -784,7 +784,7 @@ static StreamPlan plan_stream(const cliff_tab *t, const uint32_t *offs, uint32_t
   p.fused = fused_gates_fit(t->d.n) && t->ctx->gate_mode != CLIFF_GATES_PER_LAYER;
   p.decode = p.fused && !capturing(t->ctx) && plan_steps(offs, depth, &p.dec);
   if (p.decode) {
-    p.waves = std::min(p.dec.most, kDecodeMaxWaves);
+    p.waves = std::max(kDecodeMinWaves, std::min(p.dec.most, kDecodeMaxWaves));
     plan_rounds(&p.dec, p.waves);
   }
   return p;

@@ -352,6 +352,11 @@ bool fused_gates_fit(uint32_t n);
 constexpr uint32_t kDecodeMinDepth = 16;
 constexpr uint32_t kRoundEnds = 256;       // see launch_gates_decoded
 constexpr uint32_t kDecodeMaxWaves = 16;   // of a workgroup that runs a decoded stream
+// and fewest for one tableau: they load and store its columns, a cache line a
+// lane, which one wave for layers of up to 64 ops did slower than the op-word
+// kernel's 16 (16 layers of 5 CNOTs: n = 4,000 65 us, four waves 48, op words
+// 53; n = 20,000 889, 478, 691; 1,000 layers at n = 20,000 1,601 and 1,174).
+constexpr uint32_t kDecodeMinWaves = 4;
 // One tableau of a many-tableau gate launch (device memory).
 struct ManyDesc {
   uint64_t *X, *Z, *P;

@@ -194,3 +194,31 @@ def test_row_parts_only_where_layers_fill_them(ctx, n, pairs, depth, launches):
     assert np.array_equal(gx[:k], x) and not gz[:k].any() and np.array_equal(gz[k:], z) and not gx[k:].any()
     assert not gr.any()
     t.close()
+
+
+@pytest.mark.parametrize("n", [4000, 20000])
+def test_sparse_layers_decoded_no_slower(ctx, n):
+    """16 layers of five CNOTs, which are decoded, take no longer than the
+    first 15, which are not: loading and storing the columns is most of it."""
+    import time
+    import torch
+    from paper_2408_00384_amd import DeviceTableau, cliff_apply_encoded, cliff_encode_layers
+    rng = np.random.default_rng([99, n])
+    perm = np.stack([rng.permutation(n)[:10] for _ in range(16)]).astype(np.uint32)
+    zero = np.zeros((16, n), np.uint8)
+    words, offs = cliff_encode_layers(n, zero, zero, np.ascontiguousarray(perm[:, :5]), np.ascontiguousarray(perm[:, 5:]))
+    dev = _upload(words)
+    t = DeviceTableau(ctx, n, 1)
+    best = {}
+    for depth in (15, 16):
+        times = []
+        for _ in range(12):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(4):
+                cliff_apply_encoded(t.handle, dev.data_ptr(), offs[: depth + 1])
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t0)
+        best[depth] = min(times)
+    assert best[16] < 1.1 * best[15], best
+    t.close()
