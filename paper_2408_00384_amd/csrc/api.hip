@@ -642,18 +642,42 @@ struct DecodePlan {
   std::vector<Segment> segs;     // as many layers each as the scratch holds
   size_t total() const { return at.back(); }
 };
-// Steps of the largest layer (raised in *most) and of all; false without any.
+// Steps of all layers, and in *most at least those of the largest (less than
+// twice as many); false where the boundaries decrease.  (Bitwise only, so that
+// four layers go at a time: at 1,000 tableaux of 512 layers a check and two
+// counts of one layer at a time were 0.6 ms of the call's 2.2.)
 static bool count_steps(const uint32_t *offs, uint32_t depth, uint32_t *most, size_t *total) {
   size_t sum = 0;
-  uint32_t m = 0;
-  for (uint32_t l = 0; l < depth; ++l) {
-    const uint32_t s = uint32_t((uint64_t(offs[l + 1] - offs[l]) + 63) / 64);
-    m = std::max(m, s);
-    sum += s;
+  uint32_t m = *most, borrow = 0;
+  for (uint32_t l = 0; l < depth;) {
+    const uint32_t l1 = l + std::min(depth - l, 1u << 16);
+    uint32_t part = 0;   // (boundaries that do not decrease: 2^26 + 2^16 at most)
+    for (; l < l1; ++l) {
+      const uint32_t lo = offs[l], hi = offs[l + 1], cnt = hi - lo;
+      const uint32_t s = (cnt >> 6) + (((cnt & 63u) + 63u) >> 6);
+      borrow |= (~hi & lo) | ((~hi | lo) & cnt);
+      m |= s;
+      part += s;
+    }
+    sum += part;
   }
-  *most = std::max(*most, m);
+  *most = m;
   *total = sum;
-  return m != 0;
+  return !(borrow >> 31);
+}
+// Whether decoding pays for many tableaux (`groups`: row groups of all).  The
+// plan and the decode are two launches more, which a layer of usual size earns
+// back 0.2 us at a time, one of many steps sooner: op words / decoded, us, 10
+// tableaux of n = 256, 32 layers of 5 CNOTs 48.9 / 51.0, 48 layers 55.2 / 54.5,
+// 128 85.7 / 67.8; of n = 1,000 48 layers 70 / 73, 128 104 / 88; 100 of n = 1,000,
+// 16 full layers 304 / 320, 32 355 / 349; 10 of n = 3,000, 16 full ones 284 / 258.
+// And a decoded stream has 512 bytes a step: past the cache it is read
+// more slowly than few row groups decode op words for themselves (3,000
+// tableaux, 512 layers of a step, 2 groups each 5.4 / 6.4 ms, 4 groups 6.3 / 6.7;
+// 1,000, 512 layers of two steps, 7 groups 3.10 / 2.69, of one, 3 groups 2.04 /
+// 1.96).
+static bool many_decode_pays(size_t steps, size_t layers, size_t count, size_t groups) {
+  return std::max(steps, 6 * layers) >= 384 * count && (steps <= size_t(1) << 19 || groups >= 6 * count);
 }
 // First layer of part k of `segs` equal ones.
 static uint32_t part_layer(uint32_t depth, size_t k, size_t segs) { return uint32_t(uint64_t(depth) * k / segs); }
@@ -993,14 +1017,17 @@ static int run_many(cliff_tab *const *tabs, const std::vector<ManySource> &src, 
   if (!tabs) return fail(CLIFF_EINVAL, "many-tableau gates: NULL tableau array");
   cliff_ctx *c = tabs[0] ? tabs[0]->ctx : nullptr;
   uint32_t max_n = 0;
+  uint32_t most = 0;   // steps of the largest layer, about
   size_t groups64 = 0;
+  std::vector<size_t> totals(count);   // steps of each stream
   for (size_t i = 0; i < count; ++i) {
     if (!tabs[i]) return fail(CLIFF_EINVAL, "many-tableau gates: tableau %zu is NULL", i);
     if (tabs[i]->ctx != c) return fail(CLIFF_EINVAL, "many-tableau gates: tableaux on different contexts");
     if (src[i].depth && !src[i].offs) return fail(CLIFF_EINVAL, "many-tableau gates: NULL offsets (%zu)", i);
-    for (uint32_t l = 0; l < src[i].depth; ++l)
-      if (src[i].offs[l + 1] < src[i].offs[l])
-        return fail(CLIFF_EINVAL, "tableau %zu: layer offsets decrease at layer %u", i, l);
+    if (!count_steps(src[i].offs, src[i].depth, &most, &totals[i]))
+      for (uint32_t l = 0; l < src[i].depth; ++l)
+        if (src[i].offs[l + 1] < src[i].offs[l])
+          return fail(CLIFF_EINVAL, "tableau %zu: layer offsets decrease at layer %u", i, l);
     if (src[i].depth && src[i].offs[src[i].depth] && !src[i].host_ops && !src[i].dev_ops)
       return fail(CLIFF_EINVAL, "many-tableau gates: NULL ops (%zu)", i);
     max_n = std::max(max_n, tabs[i]->d.n);
@@ -1033,23 +1060,23 @@ static int run_many(cliff_tab *const *tabs, const std::vector<ManySource> &src, 
   // 100 of n = 500 in one part, 1.51 in parts of 64 MB.)
   std::vector<size_t> stream, held;
   uint32_t min_depth = UINT32_MAX;
-  uint32_t waves = 1, most = 0, max_depth = 0;
+  uint32_t waves = 1, max_depth = 0;
   size_t segs = 0, need = 0;
   uint2 *dec = nullptr;
   bool decode = !capturing(c);
   if (decode) {
     size_t steps = 0, layers = 0;
     for (size_t i = 0; decode && i < count; ++i) {
-      size_t total = 0;
-      decode = src[i].depth >= kDecodeMinDepth && count_steps(src[i].offs, src[i].depth, &most, &total);
-      steps += total;
+      decode = src[i].depth >= kDecodeMinDepth && totals[i] != 0;
+      steps += totals[i];
       layers += src[i].depth;
       max_depth = std::max(max_depth, src[i].depth);
       min_depth = std::min(min_depth, src[i].depth);
     }
+    decode = decode && many_decode_pays(steps, layers, count, groups64 * 64 / rows);
     if (decode) {
       const size_t most_segs = std::min<size_t>(min_depth, 64);
-      waves = uint32_t(std::min<size_t>(4, std::max<size_t>(1, (steps + layers - 1) / layers)));
+      waves = uint32_t(std::min<size_t>(4, std::max<size_t>(max_n >= kManyLoadN ? 4 : 1, (steps + layers - 1) / layers)));
       for (segs = steps / kDecodeSteps + 1; segs <= most_segs; ++segs) {
         stream.assign(segs * count, 0);
         held.assign(segs * count, 0);
@@ -1059,7 +1086,8 @@ static int run_many(cliff_tab *const *tabs, const std::vector<ManySource> &src, 
           for (size_t i = 0; i < count; ++i) {
             const uint32_t l0 = part_layer(src[i].depth, k, segs), l1 = part_layer(src[i].depth, k + 1, segs);
             size_t &own = stream[k * count + i];
-            (void)count_steps(src[i].offs + l0, l1 - l0, &most, &own);
+            if (segs == 1) own = totals[i];
+            else (void)count_steps(src[i].offs + l0, l1 - l0, &most, &own);
             const size_t bytes = align256((size_t(l1 - l0) + 1) * 4) + (own / waves + (l1 - l0) + 64) * 4;
             held[k * count + i] = own + (bytes + 511) / 512;
             sum += held[k * count + i];

@@ -356,7 +356,10 @@ constexpr uint32_t kDecodeMaxWaves = 16;   // of a workgroup that runs a decoded
 // lane, which one wave for layers of up to 64 ops did slower than the op-word
 // kernel's 16 (16 layers of 5 CNOTs: n = 4,000 65 us, four waves 48, op words
 // 53; n = 20,000 889, 478, 691; 1,000 layers at n = 20,000 1,601 and 1,174).
-constexpr uint32_t kDecodeMinWaves = 4;
+// Many tableaux have other workgroups beside them, until the columns leave room
+// for few (64 layers of 5 CNOTs, one wave / four / op words: 8 of n = 1,000 71 /
+// 66 / 72 us, 100 of them 309 / 313 / 314, 100 of n = 4,000 3,542 / 2,542 / 2,862).
+constexpr uint32_t kDecodeMinWaves = 4, kManyLoadN = 1024;
 // One tableau of a many-tableau gate launch (device memory).
 struct ManyDesc {
   uint64_t *X, *Z, *P;

@@ -222,3 +222,86 @@ def test_sparse_layers_decoded_no_slower(ctx, n):
         best[depth] = min(times)
     assert best[16] < 1.1 * best[15], best
     t.close()
+
+
+# either side of what decoding needs of many tableaux: 64 layers of one step, 16
+# of 24 steps (with the skipped op: 1,537)
+@pytest.mark.parametrize("n,sizes", [(30, [5] * 63), (30, [5] * 64), (1600, [1535] * 16), (1600, [1536] * 16)])
+def test_many_at_the_least_worth_decoding(ctx, n, sizes):
+    from paper_2408_00384_amd import DeviceTableau, cliff_apply_encoded_many
+    words, offs, gates = _stream(n, sizes, 3)
+    dev = _upload(words)
+    tabs = [DeviceTableau(ctx, n, 1) for _ in range(3)]
+    for _ in range(2):
+        cliff_apply_encoded_many([t.handle for t in tabs], [dev.data_ptr()] * 3, [offs] * 3)
+    ref = _ref(n, gates, 2)
+    for t in tabs:
+        assert _same(t.export(), ref)
+        t.close()
+
+
+@pytest.mark.parametrize("n,rows", [(200, 32), (200, 64), (64, 32)])
+def test_many_tableaux_over_the_scratch(ctx, n, rows):
+    """Over 2^20 steps: in parts by layers where a tableau has six row groups
+    and more (n = 200), as op words where it has fewer."""
+    from paper_2408_00384_amd import DeviceTableau, cliff_apply_encoded_many
+    shapes = [(n, [1, 3] * 40000), (n, [2, 0, min(n, 65), 1] * 5), (n, [1] * 17)]
+    streams = [_stream(m, sizes, 11 + i) for i, (m, sizes) in enumerate(shapes)]
+    dev = [_upload(w) for w, _, _ in streams]
+    tabs, ds, os_, refs = [], [], [], []
+    for (m, _), (_, o, gates), d, k in zip(shapes, streams, dev, [14, 1, 1]):
+        ref = _ref(m, gates)
+        for _ in range(k):
+            tabs.append(DeviceTableau(ctx, m, 1))
+            ds.append(d.data_ptr())
+            os_.append(o)
+            refs.append(ref)
+    cliff_apply_encoded_many([t.handle for t in tabs], ds, os_, rows)
+    for t, ref in zip(tabs, refs):
+        assert _same(t.export(), ref)
+        t.close()
+
+
+def test_many_refuses_decreasing_boundaries(ctx):
+    """At any layer and by any amount (the check is arithmetic on borrows)."""
+    from paper_2408_00384_amd import CLIFF_EINVAL, CliffError, DeviceTableau, cliff_apply_encoded_many
+    words, offs, _ = _stream(9, [3] * 70, 5)
+    dev = _upload(words)
+    t = DeviceTableau(ctx, 9, 1)
+    for l, v in [(1, 0xFFFFFFFF), (35, 0x80000000), (70, 0), (70, int(offs[69]) - 1)]:
+        bad = offs.copy()
+        bad[l] = v
+        with pytest.raises(CliffError, match="decrease at layer %d" % (l if l < 70 else 69)) as e:
+            cliff_apply_encoded_many([t.handle], [dev.data_ptr()], [bad])
+        assert e.value.code == CLIFF_EINVAL
+    assert _same(t.export(), _ref(9, (np.empty(0, np.uint8), np.empty(0, np.uint32), np.empty(0, np.uint32))))
+    t.close()
+
+
+def test_many_sparse_layers_no_slower(ctx):
+    """16 layers of five CNOTs, and 64, on 8 tableaux of n = 8,000: the longer
+    stream is decoded, and loading the columns is still most of it."""
+    import time
+    import torch
+    from paper_2408_00384_amd import DeviceTableau, cliff_apply_encoded_many, cliff_encode_layers
+    n = 8000
+    rng = np.random.default_rng([100, n])
+    perm = np.stack([rng.permutation(n)[:10] for _ in range(64)]).astype(np.uint32)
+    zero = np.zeros((64, n), np.uint8)
+    words, offs = cliff_encode_layers(n, zero, zero, np.ascontiguousarray(perm[:, :5]), np.ascontiguousarray(perm[:, 5:]))
+    dev = _upload(words)
+    tabs = [DeviceTableau(ctx, n, 1) for _ in range(8)]
+    hs, ptrs = [t.handle for t in tabs], [dev.data_ptr()] * 8
+    best = {}
+    for depth in (15, 64):
+        times = []
+        for _ in range(10):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            cliff_apply_encoded_many(hs, ptrs, [offs[: depth + 1]] * 8)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t0)
+        best[depth] = min(times)
+    assert best[64] < 1.3 * best[15], best
+    for t in tabs:
+        t.close()
