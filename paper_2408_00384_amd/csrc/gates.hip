@@ -364,14 +364,31 @@ __device__ __forceinline__ void put_col(XZ<U128> *c, U128 x, U128 z) {
   put_col(reinterpret_cast<XZ<uint64_t> *>(&c->x), x.lo, x.hi);
   put_col(reinterpret_cast<XZ<uint64_t> *>(&c->z), z.lo, z.hi);
 }
+// And its load, of the same type: one wave has no barrier between layers, and
+// accesses of different types the compiler may reorder.
+__device__ __forceinline__ void get_col(const XZ<uint32_t> *c, uint32_t &x, uint32_t &z) {
+  const uint64_t v = *reinterpret_cast<const uint64_t *>(c);
+  x = uint32_t(v);
+  z = uint32_t(v >> 32);
+}
+__device__ __forceinline__ void get_col(const XZ<uint64_t> *c, uint64_t &x, uint64_t &z) {
+  const U64x2 v = *reinterpret_cast<const U64x2 *>(c);
+  x = v.x;
+  z = v.y;
+}
+__device__ __forceinline__ void get_col(const XZ<U128> *c, U128 &x, U128 &z) {
+  get_col(reinterpret_cast<const XZ<uint64_t> *>(&c->x), x.lo, x.hi);
+  get_col(reinterpret_cast<const XZ<uint64_t> *>(&c->z), z.lo, z.hi);
+}
 
 // The 64 ops of a step, one a lane.
 template <typename T>
 __device__ __forceinline__ void apply_decoded(uint2 d, T &racc) {
   const uint32_t flags = uint32_t(__builtin_amdgcn_readfirstlane(int(d.x)));
   XZ<T> *pa = lds_at<XZ<T>>(d.x & kDecBits), *pb = lds_at<XZ<T>>(d.y & kDecBits);
-  const XZ<T> va = *pa, vb = *pb;
-  T xa = va.x, za = va.z, xb = vb.x, zb = vb.z;
+  T xa, za, xb, zb;
+  get_col(pa, xa, za);
+  get_col(pb, xb, zb);
   auto mask = [](uint32_t w, uint32_t bit) { return mask_if<T>((w >> bit) & 1u); };
   if (flags & (1u << kStepCodes)) {   // (layers of two-qubit gates alone have none)
     if (flags & (1u << kStepPauli)) {

@@ -305,3 +305,19 @@ def test_many_sparse_layers_no_slower(ctx):
     assert best[64] < 1.3 * best[15], best
     for t in tabs:
         t.close()
+
+
+@pytest.mark.parametrize("rows", [32, 64, 128])
+@pytest.mark.parametrize("n", [2, 3, 30])
+def test_one_wave_keeps_the_layers_in_order(ctx, n, rows):
+    """Layers of one step on the same few columns, each reading what the last
+    one wrote, in workgroups of one wave, which has no barrier between them."""
+    from paper_2408_00384_amd import DeviceTableau, cliff_apply_encoded_many
+    words, offs, gates = _stream(n, [n, max(1, n // 2), 1] * 150, 6)
+    dev = _upload(words)
+    tabs = [DeviceTableau(ctx, n, 1) for _ in range(2)]
+    cliff_apply_encoded_many([t.handle for t in tabs], [dev.data_ptr()] * 2, [offs] * 2, rows)
+    ref = _ref(n, gates)
+    for t in tabs:
+        assert _same(t.export(), ref)
+        t.close()
