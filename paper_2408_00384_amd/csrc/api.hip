@@ -806,7 +806,7 @@ struct StreamPlan {
 static StreamPlan plan_stream(const cliff_tab *t, const uint32_t *offs, uint32_t depth) {
   StreamPlan p;
   p.fused = fused_gates_fit(t->d.n) && t->ctx->gate_mode != CLIFF_GATES_PER_LAYER;
-  p.decode = p.fused && !capturing(t->ctx) && plan_steps(offs, depth, &p.dec);
+  p.decode = p.fused && !capturing(t->ctx) && decoded_gates_ready() && plan_steps(offs, depth, &p.dec);
   if (p.decode) {
     p.waves = std::max(kDecodeMinWaves, std::min(p.dec.most, kDecodeMaxWaves));
     plan_rounds(&p.dec, p.waves);
@@ -1063,7 +1063,7 @@ static int run_many(cliff_tab *const *tabs, const std::vector<ManySource> &src, 
   uint32_t waves = 1, max_depth = 0;
   size_t segs = 0, need = 0;
   uint2 *dec = nullptr;
-  bool decode = !capturing(c);
+  bool decode = !capturing(c) && decoded_gates_ready();
   if (decode) {
     size_t steps = 0, layers = 0;
     for (size_t i = 0; decode && i < count; ++i) {

@@ -14,6 +14,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "internal.h"
@@ -805,6 +806,20 @@ static hipError_t allow_gate_lds(const void *fn, size_t more) {
   return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(kFusedGateLds + more));
 }
 
+constexpr size_t kMoreLds = kSpareCols * 8 + 8, kMoreLdsMany = kSpareCols * 32 + 16;
+bool decoded_gates_ready() {
+  static std::atomic<bool> ready{false};   // (only success is kept: another call may ask again)
+  if (ready) return true;
+  const void *const many[3] = {reinterpret_cast<const void *>(k_gates_many_decoded<uint32_t>),
+                               reinterpret_cast<const void *>(k_gates_many_decoded<uint64_t>),
+                               reinterpret_cast<const void *>(k_gates_many_decoded<U128>)};
+  bool ok = allow_gate_lds(reinterpret_cast<const void *>(k_gates_decoded), kMoreLds) == hipSuccess;
+  for (const void *fn : many) ok = ok && allow_gate_lds(fn, kMoreLdsMany) == hipSuccess;
+  if (!ok) (void)hipGetLastError();
+  ready = ok;
+  return ok;
+}
+
 // Workgroups of four waves for `depth` layers.
 static uint32_t decode_grid(uint32_t depth, uint32_t most) { return depth / 4 + 1 < most ? depth / 4 + 1 : most; }
 
@@ -812,14 +827,11 @@ hipError_t launch_gates_decoded(const TabDev &t, const uint64_t *ops, const uint
                                 const uint32_t *dev_poffs, const uint32_t *dev_sched, uint32_t depth, uint32_t rounds,
                                 uint32_t max_steps, uint32_t waves, uint2 *dec, uint2 *dec_base, hipStream_t st) {
   if (rounds == 0) return hipSuccess;
-  constexpr size_t kMore = kSpareCols * 8 + 8;
-  static const hipError_t attr = allow_gate_lds(reinterpret_cast<const void *>(k_gates_decoded), kMore);
-  if (attr != hipSuccess) return attr;
   const uint32_t gx = decode_grid(depth, 4096), gz = std::min((max_steps + 3) / 4, 1024u);
   k_decode_ops<<<dim3(gx, 1, gz), 256, 0, st>>>(ops, dev_offs, dev_poffs, depth, t.n, dec);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_gates_decoded<<<(2 * t.n + 31) / 32, 64 * waves, size_t(t.n) * 8 + kMore, st>>>(t, dec_base, dev_sched, rounds);
+  k_gates_decoded<<<(2 * t.n + 31) / 32, 64 * waves, size_t(t.n) * 8 + kMoreLds, st>>>(t, dec_base, dev_sched, rounds);
   return hipGetLastError();
 }
 
@@ -827,13 +839,6 @@ hipError_t launch_gates_many_decoded(const ManyDesc *dev_descs, uint32_t count, 
                                      uint32_t max_depth, uint32_t max_steps, uint32_t waves, hipStream_t st) {
   if (count == 0 || max_depth == 0 || max_steps == 0) return hipSuccess;
   const int v = rows == 128 ? 2 : rows == 64 ? 1 : 0;
-  static const void *const fns[3] = {reinterpret_cast<const void *>(k_gates_many_decoded<uint32_t>),
-                                     reinterpret_cast<const void *>(k_gates_many_decoded<uint64_t>),
-                                     reinterpret_cast<const void *>(k_gates_many_decoded<U128>)};
-  constexpr size_t kMore = kSpareCols * 32 + 16;
-  static const hipError_t attr[3] = {allow_gate_lds(fns[0], kMore), allow_gate_lds(fns[1], kMore),
-                                     allow_gate_lds(fns[2], kMore)};
-  if (attr[v] != hipSuccess) return attr[v];
   const uint32_t gx = decode_grid(max_depth, 256), gz = std::min((max_steps + 3) / 4, 1024u);
   k_plan_many<<<count, 1024, 0, st>>>(dev_descs, waves);
   hipError_t e = hipGetLastError();

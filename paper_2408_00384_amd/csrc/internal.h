@@ -388,6 +388,9 @@ hipError_t launch_cond_pauli(const TabDev &t, const uint64_t *ops, uint32_t k, c
                              hipStream_t st);
 hipError_t launch_gates_many(const ManyDesc *dev_descs, uint32_t count, uint32_t max_n, uint32_t rows,
                              hipStream_t st);
+// Whether the kernels of decoded streams can have the LDS they need, and none
+// of their own (their addresses begin at 0); without it the op words are run.
+bool decoded_gates_ready();
 // The same through a decoded stream: layers in steps of 64 ops (poffs: their
 // boundaries in steps, relative to dec), run in rounds of up to `waves` steps
 // (sched[r]: the round's steps, | kRoundEnds at a layer's end), the first from
