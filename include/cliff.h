@@ -101,11 +101,11 @@ int cliff_calibrate(cliff_ctx *ctx, int kind, double *out);
 /* Gate-stream strategy.  AUTO: one launch for all layers when 8n bytes (32
  * rows of every column) fit in LDS, else one launch per layer.  PER_LAYER:
  * always one launch per layer.  FUSED: always one launch (EINVAL if n is too
- * large).  In one launch, streams of 16 layers and more are decoded first into
+ * large).  In one launch, streams of 16 layers and more (of many tableaux: of
+ * 64 layers of up to 384 ops, fewer of larger ones) are decoded first into
  * context-owned device memory (8 bytes per op, layers rounded up to 64 ops;
- * at most 576 MB at a time, grown to the longest stream); while the context's
- * stream is being captured, or when that memory cannot be had, the op words
- * are decoded as they are applied.  Results are identical; only speed
+ * at most 576 MB at a time, see above); when that memory cannot be had, the op
+ * words are decoded as they are applied.  Results are identical; only speed
  * differs. */
 #define CLIFF_GATES_AUTO 0
 #define CLIFF_GATES_PER_LAYER 1
@@ -125,10 +125,12 @@ int cliff_ctx_set_gate_mode(cliff_ctx *ctx, int mode);
  * measurement.  AUTO: any n, in blocks of 64 measurements, random and
  * deterministic ones alike, each block one low-rank update of the tableau in
  * memory (two launches per block, a few MB of context-owned scratch).  AUTO
- * takes the register-resident path instead while the context's stream is
- * being captured (BLOCKED for n >= 2048, PERSISTENT below), and STEP for
- * lists of up to 32 qubits above n = 10,240, under capture above n = 10,240,
- * or when the scratch cannot be had.  Results are identical; only speed
+ * takes STEP instead for lists of up to 32 qubits above n = 10,240, while the
+ * context's stream is being captured above n = 10,240 (for n <= 10,240 see
+ * cliff_graph_begin), and where the scratch cannot be had above n = 10,240; up
+ * to there the register-resident path is tried then (BLOCKED for n >= 2048,
+ * PERSISTENT below), and CLIFF_ENOMEM returned if its larger scratch cannot be
+ * had either.  Results are identical; only speed
  * differs.  A measure-all of a dense state at n = 10,000 takes 4.8 ms with
  * AUTO, 16.1 ms with BLOCKED and 38.7 ms with PERSISTENT.  From n = 3,000 the
  * BLOCKED pass works in chunks of 2048 measurements, whose scratch (about
@@ -414,7 +416,16 @@ int cliff_batch_status(cliff_ctx *ctx, const void *dev_work, uint64_t *out2);
  * Capture everything the context enqueues between begin and end into a HIP
  * graph, replayable with cliff_graph_launch on the same stream.  The context
  * must use a non-default stream.  Captured work must not change shape between
- * replays (the same pointers and sizes are reused). */
+ * replays (the same pointers and sizes are reused).
+ * Calls that upload through the context's staging area cannot be recorded: the
+ * runtime refuses them, with CLIFF_EDEVICE, and the capture with them.  Those
+ * are most gate calls, conditioned Paulis and resets, measurements in X or Y,
+ * and for n <= 10,240 cliff_measure_record and cliff_measure_async in any mode
+ * but STEP (also after a warm-up).  What can be recorded: cliff_tab_init_zero,
+ * cliff_apply_encoded layer by layer (PER_LAYER, or n > 20,352), cliff_batch_run,
+ * cliff_measure_record_noalloc in AUTO and STEP, and cliff_measure_record and
+ * _async in STEP, or in AUTO above n = 10,240.  Calls that return host data wait
+ * for the stream and cannot be. */
 typedef struct cliff_graph cliff_graph;
 int cliff_graph_begin(cliff_ctx *ctx);
 int cliff_graph_end(cliff_ctx *ctx, cliff_graph **out);
