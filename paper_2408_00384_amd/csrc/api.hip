@@ -722,18 +722,27 @@ static void plan_rounds(DecodePlan *p, uint32_t waves) {
   seg.r1 = p->sched.size();
   p->segs.push_back(seg);
 }
+// (Grown at least twofold, so that streams a little longer each time do not each
+// wait for the device.)
 static int ctx_gate_scratch(cliff_ctx *c, size_t steps, uint2 **base) {
   if (c->gscratch_steps < steps) {
+    const size_t roomy = std::max(steps, std::min(2 * c->gscratch_steps, kDecodeSteps));
     HIP_TRY(hipStreamSynchronize(c->stream));
     if (c->gscratch) HIP_TRY(hipFree(c->gscratch));
     c->gscratch = nullptr;
     c->gscratch_steps = 0;
-    const hipError_t e = hipMalloc(reinterpret_cast<void **>(&c->gscratch), steps * 512);
+    size_t take = roomy;
+    hipError_t e = hipMalloc(reinterpret_cast<void **>(&c->gscratch), take * 512);
+    if (e != hipSuccess && roomy > steps) {
+      (void)hipGetLastError();
+      take = steps;
+      e = hipMalloc(reinterpret_cast<void **>(&c->gscratch), take * 512);
+    }
     if (e != hipSuccess) {
       (void)hipGetLastError();
       return fail(CLIFF_ENOMEM, "decoded gate stream of %zu bytes: %s", steps * 512, hipGetErrorString(e));
     }
-    c->gscratch_steps = steps;
+    c->gscratch_steps = take;
   }
   *base = c->gscratch;
   return CLIFF_OK;
@@ -1387,10 +1396,10 @@ static int read_results(cliff_tab *t, size_t cnt, uint8_t *host_out, size_t ld, 
   const size_t most = std::max<size_t>(1, kResultBytes / pitch);
   const size_t need = head + (pitch * std::min(rows, most) + 63) / 64 * 64;
   if (c->results_bytes < need) {
+    const size_t bytes = std::max({need, size_t(1) << 16, std::min(2 * c->results_bytes, kResultBytes)});
     if (c->results) HIP_TRY(hipHostFree(c->results));   // (idle: every user waits for its stream)
     c->results = nullptr;
     c->results_bytes = 0;
-    const size_t bytes = std::max<size_t>(need, 1 << 16);
     HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&c->results), bytes, hipHostMallocDefault));
     c->results_bytes = bytes;
   }

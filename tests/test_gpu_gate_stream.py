@@ -321,3 +321,22 @@ def test_one_wave_keeps_the_layers_in_order(ctx, n, rows):
     for t in tabs:
         assert _same(t.export(), ref)
         t.close()
+
+
+def test_scratch_grows_in_few_steps():
+    """Streams a little longer each time do not each reallocate the scratch."""
+    import torch
+    from paper_2408_00384_amd import Context, DeviceTableau, cliff_apply_encoded
+    ctx = Context(0)
+    words, offs, _ = _stream(2, [1] * 5000, 8)
+    dev = _upload(np.tile(words, 11))
+    t = DeviceTableau(ctx, 2, 1)
+    free = set()
+    for k in range(1, 11):   # 5,000 steps (2.5 MB) more each time
+        o = np.concatenate([offs[:-1] + i * offs[-1] for i in range(k)] + [[k * offs[-1]]]).astype(np.uint32)
+        cliff_apply_encoded(t.handle, dev.data_ptr(), o)
+        torch.cuda.synchronize()
+        free.add(torch.cuda.mem_get_info()[0])
+    assert len(free) <= 6, free
+    t.close()
+    ctx.close()
