@@ -73,6 +73,40 @@ def test_encode_layers_validation_on_host():
     assert len(ops) == 2
 
 
+@pytest.mark.parametrize("n,npairs", [(8, 4), (9, 4), (9, 2)])
+def test_encode_layers_writes_only_its_words(n, npairs):
+    """A circuit that is refused at its last layer leaves the outputs as they
+    were, an encoded one the words past its own, a buffer too small its end."""
+    import ctypes
+    from paper_2408_00384_amd import _binding as B
+    rng = np.random.default_rng([n, npairs])
+    depth = 5
+    h, s = (rng.integers(0, 2, (depth, n)).astype(np.uint8) for _ in range(2))
+    perm = np.stack([rng.permutation(n) for _ in range(depth)]).astype(np.uint32)
+    ctrl, tgt = np.ascontiguousarray(perm[:, :npairs]), np.ascontiguousarray(perm[:, npairs:2 * npairs])
+    want, want_offs = B.cliff_encode_layers(n, h, s, ctrl, tgt)
+
+    def encode(tgt, cap, null_ops=False):
+        ops, offs, nops = np.full(n * depth + 8, 0xABCD, np.uint64), np.full(depth + 1, 77, np.uint32), B._sz(99)
+        rc = B._lib.cliff_encode_layers(n, B._ptr(h, B._u8p), B._ptr(s, B._u8p), B._ptr(ctrl, B._u32p),
+                                        B._ptr(tgt, B._u32p), npairs, depth, None if null_ops else B._ptr(ops, B._u64p),
+                                        cap, B._ptr(offs, B._u32p), ctypes.byref(nops))
+        return rc, ops, offs, nops.value
+
+    k = len(want)
+    rc, ops, offs, nops = encode(tgt, len(want) + n + 8)
+    assert rc == 0 and nops == k and np.array_equal(offs, want_offs)
+    assert np.array_equal(ops[:k], want) and (ops[k:] == 0xABCD).all()
+    rc, ops, offs, nops = encode(tgt, k - 3)
+    assert rc == B.CLIFF_ENOMEM and nops == k and np.array_equal(offs, want_offs)
+    assert np.array_equal(ops[:k - 3], want[:k - 3]) and (ops[k - 3:] == 0xABCD).all()
+    bad = tgt.copy()
+    bad[depth - 1, npairs - 1] = ctrl[depth - 1, 0]
+    for null_ops in (False, True):
+        rc, ops, offs, nops = encode(bad, k, null_ops)
+        assert rc == B.CLIFF_EINVAL and nops == 99 and (ops == 0xABCD).all() and (offs == 77).all()
+
+
 def test_ctx_create_reports_error_without_gpu():
     import paper_2408_00384_amd as P
     import torch
