@@ -246,3 +246,42 @@ def test_large_chunks_fall_back_when_memory_is_short():
         t.close()
     finally:
         cx.close()
+
+
+@pytest.mark.parametrize("n", [7_000, 8_192, 10_240])
+def test_largest_register_resident_shapes_vs_oracle(ctx, n):
+    """The register-resident kernels asked for by name at four row words a lane
+    (219 and 256 words) and at the largest tableau they hold (320 words: every
+    lane word and column slot of every workgroup full), and the automatic mode
+    beside them: 32 measurements, two of them repeats, then sampled rows."""
+    import paper_2408_00384_amd as P
+    c = layered_circuit(n, 6, 1, gen_seed=[68, n], circuit_id=19)
+    rng = np.random.default_rng(n)
+    q = np.concatenate([np.arange(16), np.sort(rng.choice(np.arange(16, n - 1), 13, replace=False)),
+                        [n - 1, 0, n - 1]]).astype(np.uint32)
+    o = oracle.Tableau(n).apply_circuit_gates(c)
+    want = [o.measure(int(a), seed=c.seed, circuit=c.circuit_id, shot=0, m=i) for i, a in enumerate(q)]
+    x, z, r = o.get()
+    rows = np.concatenate([q, q + n, rng.choice(2 * n, 64, replace=False)]).astype(np.uint32)
+    # kinds of launches a mode makes and does not (at 8,192 and 10,240 the blocked
+    # pass's shape does not fit, and it is the one per measurement)
+    runs = {P.MEASURE_PERSISTENT: ("sweep", "blocked"),
+            P.MEASURE_BLOCKED: ("blocked", None) if n == 7_000 else ("sweep", "blocked"),
+            P.MEASURE_AUTO: ("blocked", "sweep")}
+    for mode, (does, does_not) in runs.items():
+        _mode(ctx, mode)
+        t = P.DeviceTableau(ctx, n, 1).apply_circuit_gates(c)
+        P.cliff_ctx_profile(ctx.handle, True)
+        try:
+            out, rnd = t.measure(q, seed=c.seed, circuit=c.circuit_id)
+            launches = {k: P.cliff_ctx_profile_read(ctx.handle, k)[1] for k in ("sweep", "blocked")}
+        finally:
+            P.cliff_ctx_profile(ctx.handle, False)
+            _mode(ctx, P.MEASURE_AUTO)
+        assert 0 < launches[does] < len(q) and (does_not is None or launches[does_not] == 0), (mode, launches)
+        assert np.array_equal(out[0], [w[0] for w in want]) and np.array_equal(rnd, [w[1] for w in want])
+        gx, gz, gr = t.export_rows(rows)
+        assert np.array_equal(gx, x[rows]) and np.array_equal(gz, z[rows]) and np.array_equal(gr[0], r[rows])
+        assert t.anomalies() == 0
+        t.close()
+    assert 0 < sum(w[1] for w in want) < len(q)
