@@ -23,11 +23,14 @@
 // teams per compute unit.
 //
 // Bound: VALU instructions (95 % of the busy cycles at 4,096 circuits of n = 8
-// to 256, depth n to 4 n), two thirds of them the gates'.  That batch took 3.31
-// ms with sign flips of Pauli codes in every op, a CNOT of 6 instructions a
-// 32-bit word and a measurement item of 60; 2.96 with 5 and 36.  (Four row
-// words per thread instead of two: 7 % fewer instructions, twice the bank
-// conflicts, no faster.)
+// to 256, depth n to 4 n), two thirds of them the gates'.  That batch took 3.36
+// ms with a CNOT of 6 instructions a 32-bit word and a measurement item of 60;
+// 2.91 with 5 and 36, no sign flips of Pauli codes where a wave has none (two
+// row words a thread only: with one the test costs as much as it saves, 1,024
+// circuits of n = 64 190 us without and 199 with it) and the pivot not forced
+// into scalar registers, of which 44 were spilled instead of 37 (n = 32, 128
+// layers, 4,096 circuits 0.59 ms with it, 0.56 without).  (Four row words per
+// thread: 7 % fewer instructions, twice the bank conflicts, no faster.)
 //
 // LDS banks (64 of 4 bytes): with the power-of-two column stride, column j
 // starts at bank 2 Wl j mod 64, so a gate op's accesses fall in one of 32 / Wl
@@ -213,25 +216,28 @@ __global__ void __launch_bounds__(TEAM) k_batch(const BatchDescDev *__restrict__
           // branch (nearly every op has one).  When the wave's two-qubit ops
           // are all CNOTs (a wave-uniform test), the CNOT runs under a lane
           // mask instead of the per-kind branches.
-          // Likewise the flips by x or z alone, which codes of H and S have not.
+          // Likewise, for two words, the flips by x or z alone, which codes of H
+          // and S have not.
           bool other = false, pauli = false;
 #pragma unroll
           for (int u = 0; u < N; ++u) {
             other |= pr[u] != PAIR_NONE && pr[u] != PAIR_CNOT;
-            pauli |= ((ca[u] | cb[u]) & kSqPauli) != 0;
+            pauli |= ((ca[u] | cb[u]) & kSqPauli) != 0;   // cb = 0 without a second qubit
           }
           const bool only_cnot = __ballot(other) == 0;
-          if (__ballot(pauli)) {
+          if constexpr (K == 2) {
+            if (__ballot(pauli)) {
 #pragma unroll
-            for (int u = 0; u < N; ++u) {
-              sq_pauli(ca[u], xa[u], za[u], racc);
-              sq_pauli(cb[u], xb[u], zb[u], racc);   // cb = 0 without a second qubit
+              for (int u = 0; u < N; ++u)
+                racc = bop3<LUT_XOR3>(sq_pauli(ca[u], xa[u], za[u]), sq_pauli(cb[u], xb[u], zb[u]), racc);
             }
           }
 #pragma unroll
           for (int u = 0; u < N; ++u) {
-            sq_rest(ca[u], xa[u], za[u], racc);
-            sq_rest(cb[u], xb[u], zb[u], racc);
+            if constexpr (K == 2)
+              racc = bop3<LUT_XOR3>(sq_rest(ca[u], xa[u], za[u]), sq_rest(cb[u], xb[u], zb[u]), racc);
+            else
+              racc = bop3<LUT_XOR3>(sq_flips(ca[u], xa[u], za[u]), sq_flips(cb[u], xb[u], zb[u]), racc);
             if (only_cnot) {
               const T mc = mask_if<T>(pr[u] == PAIR_CNOT);
               racc = bop3<LUT_AND_XOR>(xa[u] & bop3<LUT_AND_XNOR>(zb[u], xb[u], za[u]), mc, racc);
@@ -360,7 +366,6 @@ __global__ void __launch_bounds__(TEAM) k_batch(const BatchDescDev *__restrict__
       uint32_t p_next = kNone;
       uint64_t m_next = 0;
       if (p != kNone) {
-        p = __builtin_amdgcn_readfirstlane(p);   // (the wave's)
         const uint32_t pn = p - n, wpn = pn >> 6, wp = p >> 6;
         const uint64_t bpn = 1ull << (pn & 63), bpb = 1ull << (p & 63);
         // this lane's bits of rows p - n and p (zero where its word holds
@@ -410,7 +415,8 @@ __global__ void __launch_bounds__(TEAM) k_batch(const BatchDescDev *__restrict__
             xh += 4 * TEAM;
             zh += 4 * TEAM;
           }
-          if (slot == a % slots && wl == wp) sZ[a * Wl + wl] |= bpb;   // (this lane has swept column a)
+          if (slot == (a & (slots - 1)) && wl == wp)   // (this lane has swept column a)
+            atomicOr(reinterpret_cast<unsigned long long *>(&sZ[a * Wl + wl]), (unsigned long long)bpb);
         }
         // counters: the cpw column slots of a word sit in lanes sub * Wl + wl
         // of one wave (same wl): mod-4 sums by a butterfly over them, then
@@ -425,7 +431,7 @@ __global__ void __launch_bounds__(TEAM) k_batch(const BatchDescDev *__restrict__
           c1s[wave * Wl + lane] = c1;
         }
         // the owner lanes stage column a + 1 as measurement a left it
-        if (a + 1 < n && wl < W && (a + 1) % slots == own)
+        if (a + 1 < n && wl < W && ((a + 1) & (slots - 1)) == own)
           sN[(ab ^ 1u) * lay.mw + wl] = sX[(a + 1) * Wl + wl];
         lds_barrier();
         if (a + 1 < n) select(a + 1, p_next, m_next);
@@ -498,7 +504,7 @@ __global__ void __launch_bounds__(TEAM) k_batch(const BatchDescDev *__restrict__
         if (par & 1u) atomicXor(&s_par[ab], 1u);
         if (ycnt) atomicAdd(&s_y[ab], ycnt);
         // measurement a changed nothing: column a + 1 staged as it stands
-        if (a + 1 < n && wl < W && (a + 1) % slots == own)
+        if (a + 1 < n && wl < W && ((a + 1) & (slots - 1)) == own)
           sN[(ab ^ 1u) * lay.mw + wl] = sX[(a + 1) * Wl + wl];
         lds_barrier();
         if (a + 1 < n) select(a + 1, p_next, m_next);

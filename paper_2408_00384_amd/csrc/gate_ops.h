@@ -111,29 +111,33 @@ constexpr uint32_t LUT_AND_XOR_BC = 0x60;  // a & (b ^ c)
 constexpr uint32_t LUT_SELECT = 0xCA;      // a ? b : c
 
 // Apply a single-qubit code (bits SH .. SH + 6 of c) to x / z words of rows (32,
-// 64 or 128 rows at once).  Its sign flips by x or z alone (those of a Pauli in
-// the code; kSqPauli) and the rest come apart, since most codes have none of
-// the former.
+// 64 or 128 rows at once); the sign flips are returned, so that those of
+// several codes meet in the accumulator at once (LUT_XOR3) and it is no chain
+// through all of them.  sq_flips: the whole code.  The flips by x or z alone
+// (those of a Pauli in the code; kSqPauli) and the rest also come apart, since
+// most codes have none of the former: sq_pauli, then sq_rest.
 constexpr uint32_t kSqPauli = 0x30;
 template <uint32_t SH = 0, typename T>
-__device__ __forceinline__ void sq_pauli(uint32_t c, T x, T z, T &racc) {
-  racc = bop3<LUT_AND_XOR>(x, mask_if<T>((c >> (SH + 4)) & 1u),
-                           bop3<LUT_AND_XOR>(z, mask_if<T>((c >> (SH + 5)) & 1u), racc));
+__device__ __forceinline__ T sq_pauli(uint32_t c, T x, T z) {
+  return bop3<LUT_AND_XOR>(x, mask_if<T>((c >> (SH + 4)) & 1u), z & mask_if<T>((c >> (SH + 5)) & 1u));
 }
-template <uint32_t SH = 0, typename T>
-__device__ __forceinline__ void sq_rest(uint32_t c, T &x, T &z, T &racc) {
+template <uint32_t SH, bool PAULI, typename T>
+__device__ __forceinline__ T sq_part(uint32_t c, T &x, T &z) {
   auto bit = [c](uint32_t k) { return mask_if<T>((c >> (SH + k)) & 1u); };   // all-ones if set
-  racc = bop3<LUT_AND_XOR>(x & z, bit(6), racc);
+  T f = bop3<LUT_AND3>(x, z, bit(6));
+  if constexpr (PAULI) f = bop3<LUT_AND_XOR>(z, bit(5), bop3<LUT_AND_XOR>(x, bit(4), f));
   const T nx = bop3<LUT_ANDN_XOR>(x, bit(0), z & bit(1));   // (x & m00) ^ (z & m01)
   const T nz = bop3<LUT_ANDN_XOR>(z, bit(3), x & bit(2));   // (x & m10) ^ (z & m11)
   x = nx;
   z = nz;
+  return f;
 }
+template <uint32_t SH = 0, typename T>
+__device__ __forceinline__ T sq_rest(uint32_t c, T &x, T &z) { return sq_part<SH, false>(c, x, z); }
 template <typename T>
-__device__ __forceinline__ void sq_apply(uint32_t c, T &x, T &z, T &racc) {
-  sq_pauli(c, x, z, racc);
-  sq_rest(c, x, z, racc);
-}
+__device__ __forceinline__ T sq_flips(uint32_t c, T &x, T &z) { return sq_part<0, true>(c, x, z); }
+template <typename T>
+__device__ __forceinline__ void sq_apply(uint32_t c, T &x, T &z, T &racc) { racc ^= sq_flips(c, x, z); }
 
 template <typename T>
 __device__ __forceinline__ void pair_apply(uint32_t kind, T &xa, T &za, T &xb, T &zb, T &racc) {

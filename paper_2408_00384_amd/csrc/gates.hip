@@ -392,12 +392,8 @@ __device__ __forceinline__ void apply_decoded(uint2 d, T &racc) {
   get_col(pb, xb, zb);
   auto mask = [](uint32_t w, uint32_t bit) { return mask_if<T>((w >> bit) & 1u); };
   if (flags & (1u << kStepCodes)) {   // (layers of two-qubit gates alone have none)
-    if (flags & (1u << kStepPauli)) {
-      sq_pauli<18>(d.x, xa, za, racc);
-      sq_pauli<18>(d.y, xb, zb, racc);
-    }
-    sq_rest<18>(d.x, xa, za, racc);
-    sq_rest<18>(d.y, xb, zb, racc);
+    if (flags & (1u << kStepPauli)) racc = bop3<LUT_XOR3>(sq_pauli<18>(d.x, xa, za), sq_pauli<18>(d.y, xb, zb), racc);
+    racc = bop3<LUT_XOR3>(sq_rest<18>(d.x, xa, za), sq_rest<18>(d.y, xb, zb), racc);
   }
   // two-qubit gates under lane masks; without one xb and zb are zero (spare)
   const T mc = mask(d.y, kDecCnot), mz = mask(d.y, kDecCz);

@@ -220,3 +220,32 @@ def test_tuned_choices_are_bit_identical(ctx):
     for name in ("fixed", "one"):
         assert all(np.array_equal(a, b) for a, b in zip(outs["tuned"], outs[name])), name
     _check(circs[::6], outs["tuned"][::6])
+
+
+@pytest.mark.parametrize("n", [1, 31, 64, 65, 128, 129, 256])
+def test_whole_gate_set(ctx, n):
+    """Circuits of all nine gates, mixed, Pauli-free and CNOT-only layers among
+    them, at the row words where the kernel changes its form."""
+    from types import SimpleNamespace
+    from paper_2408_00384_amd import cliff_encode_gates
+    from paper_2408_00384_amd.batch import BatchPlan
+    rng = np.random.default_rng([101, n])
+    circs, lists = [], []
+    for i, allowed in enumerate([range(9), (0, 1, 2), (2,), (0, 1, 2, 7, 8), range(9)]):
+        g = 6 * n
+        ops = rng.choice(np.array([o for o in allowed if n > 1 or o not in (2, 7, 8)] or [0], np.uint8), g)
+        a = rng.integers(0, n, g).astype(np.uint32)
+        b = ((a + 1 + rng.integers(0, max(1, n - 1), g)) % n).astype(np.uint32)
+        enc = cliff_encode_gates(n, ops, a, b)
+        circs.append(SimpleNamespace(n=n, depth=len(enc[1]) - 1, shots=3, qubits=np.arange(n, dtype=np.uint32), seed=5,
+                                     circuit_id=i))
+        lists.append(((ops, a, b), enc))
+    with torch.cuda.stream(ctx.stream):
+        plan = BatchPlan(ctx, circs, encoded=[e for _, e in lists]).run()
+        outs = plan.outcomes()
+    assert plan.status() == dict(rejected=0, anomalies=0)
+    for c, (gates, _), out in zip(circs, lists, outs):
+        ref = oracle.Tableau(n).apply_gates(*gates)
+        for s in range(3):
+            o, _ = ref.clone().measure_list(c.qubits, seed=5, circuit=c.circuit_id, shot=s)
+            assert np.array_equal(out[s], o), "circuit %d shot %d" % (c.circuit_id, s)
