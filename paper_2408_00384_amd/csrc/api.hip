@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <new>
 #include <string>
 #include <vector>
 #include <mutex>
@@ -833,10 +834,16 @@ struct StreamPlan {
 static StreamPlan plan_stream(const cliff_tab *t, const uint32_t *offs, uint32_t depth) {
   StreamPlan p;
   p.fused = fused_gates_fit(t->d.n) && t->ctx->gate_mode != CLIFF_GATES_PER_LAYER;
-  p.decode = p.fused && !capturing(t->ctx) && decoded_gates_ready() && plan_steps(offs, depth, &p.dec);
-  if (p.decode) {
-    p.waves = std::max(kDecodeMinWaves, std::min(p.dec.most, kDecodeMaxWaves));
-    plan_rounds(&p.dec, p.waves);
+  if (!p.fused || capturing(t->ctx) || !decoded_gates_ready()) return p;
+  try {
+    p.decode = plan_steps(offs, depth, &p.dec);
+    if (p.decode) {
+      p.waves = std::max(kDecodeMinWaves, std::min(p.dec.most, kDecodeMaxWaves));
+      plan_rounds(&p.dec, p.waves);
+    }
+  } catch (const std::bad_alloc &) {   // a plan takes 8 bytes a layer and more; without it the op words are run
+    p.decode = false;
+    p.dec = DecodePlan();
   }
   return p;
 }
