@@ -412,13 +412,16 @@ static int check_layer_args(uint32_t n, const uint8_t *h, const uint8_t *s, cons
 // now 9).  state: n bytes of scratch, a qubit's code | 0x80 once a CNOT has
 // it.  ops: room for layer_room() words, *cnt of them written.
 static size_t layer_room(uint32_t n, uint32_t npairs) { return size_t(n) - npairs + 1; }
-static inline int take_pair(uint32_t n, uint32_t l, uint32_t k, uint32_t c, uint32_t g, uint8_t *state) {
+static inline int take_pair(uint32_t n, uint32_t l, uint32_t k, uint32_t c, uint32_t g, uint8_t *state, uint8_t *cc,
+                            uint8_t *cg) {
   if (c >= n || g >= n)
     return fail(CLIFF_EINVAL, "layer %u pair %u: qubit out of range (n=%u)", l, k, n);
   if (c == g) return fail(CLIFF_EINVAL, "layer %u pair %u: CNOT control == target", l, k);
-  if ((state[c] | state[g]) & 0x80) return fail(CLIFF_EINVAL, "layer %u: qubit used by two CNOTs", l);
-  state[c] |= 0x80;
-  state[g] |= 0x80;
+  *cc = state[c];
+  *cg = state[g];
+  if ((*cc | *cg) & 0x80) return fail(CLIFF_EINVAL, "layer %u: qubit used by two CNOTs", l);
+  state[c] = *cc | 0x80;
+  state[g] = *cg | 0x80;
   return CLIFF_OK;
 }
 static int encode_layer(uint32_t n, uint32_t l, const uint8_t *h, const uint8_t *s, const uint32_t *ctrl,
@@ -437,9 +440,10 @@ static int encode_layer(uint32_t n, uint32_t l, const uint8_t *h, const uint8_t 
   }
   for (uint32_t k = 0; k < npairs; ++k) {
     const uint32_t c = ctrl[k], g = tgt[k];
-    const int rc = take_pair(n, l, k, c, g, state);
+    uint8_t cc, cg;
+    const int rc = take_pair(n, l, k, c, g, state, &cc, &cg);
     if (rc) return rc;
-    ops[k] = make_op(c, g, state[c] & 0x7Fu, state[g] & 0x7Fu, PAIR_CNOT);
+    ops[k] = make_op(c, g, cc, cg, PAIR_CNOT);
   }
   size_t at = npairs;
   if (2 * size_t(npairs) < n) {
@@ -449,6 +453,26 @@ static int encode_layer(uint32_t n, uint32_t l, const uint8_t *h, const uint8_t 
     }
   }
   *cnt = at;
+  return CLIFF_OK;
+}
+// The same checks, and the number of words alone.
+static int count_layer(uint32_t n, uint32_t l, const uint8_t *h, const uint8_t *s, const uint32_t *ctrl,
+                       const uint32_t *tgt, uint32_t npairs, uint8_t *state, size_t *cnt) {
+  memset(state, 0, n);
+  for (uint32_t k = 0; k < npairs; ++k) {
+    const size_t at = size_t(l) * npairs + k;
+    uint8_t cc, cg;
+    const int rc = take_pair(n, l, k, ctrl[at], tgt[at], state, &cc, &cg);
+    if (rc) return rc;
+  }
+  *cnt = npairs;
+  if (2 * size_t(npairs) < n) {
+    h += size_t(l) * n;
+    s += size_t(l) * n;
+    uint32_t singles = 0;   // (H, S and both are codes other than the identity)
+    for (uint32_t q = 0; q < n; ++q) singles += uint32_t((h[q] | s[q]) != 0) & uint32_t(state[q] == 0);
+    *cnt += singles;
+  }
   return CLIFF_OK;
 }
 
@@ -461,33 +485,32 @@ extern "C" int cliff_encode_layers(uint32_t n, const uint8_t *h, const uint8_t *
   int rc = check_layer_args(n, h, s, ctrl, tgt, npairs, depth);
   if (rc) return rc;
   std::vector<uint8_t> state(n);
-  if (ops) {   // nothing is written for a circuit that is refused
-    for (uint32_t l = 0; l < depth; ++l) {
-      std::fill(state.begin(), state.end(), uint8_t(0));
-      for (uint32_t k = 0; k < npairs; ++k) {
-        const size_t at = size_t(l) * npairs + k;
-        rc = take_pair(n, l, k, ctrl[at], tgt[at], state.data());
-        if (rc) return rc;
-      }
-    }
-  }
-  // a layer of a caller's that may not fit, or has a word more than it needs
-  std::vector<uint64_t> row(depth ? layer_room(n, npairs) : 0);
   std::vector<uint32_t> bounds(size_t(depth) + 1);
-  const bool exact = 2 * size_t(npairs) == n;
+  // all layers checked and counted first: nothing is written for a circuit
+  // that is refused
   size_t total = 0;
   for (uint32_t l = 0; l < depth; ++l) {
     bounds[l] = uint32_t(total);
-    const size_t room = (ops && total < cap) ? cap - total : 0;
-    uint64_t *to = exact && room >= npairs ? ops + total : row.data();
     size_t cnt = 0;
-    rc = encode_layer(n, l, h, s, ctrl, tgt, npairs, state.data(), to, &cnt);
+    rc = count_layer(n, l, h, s, ctrl, tgt, npairs, state.data(), &cnt);
     if (rc) return rc;
-    if (to == row.data() && room) memcpy(ops + total, to, std::min(cnt, room) * 8);
     total += cnt;
     if (total > 0xFFFFFFF0ull) return fail(CLIFF_EINVAL, "cliff_encode_layers: stream too long");
   }
   bounds[depth] = uint32_t(total);
+  if (ops) {
+    // a layer that may not fit, or has a word more than it needs, by itself first
+    std::vector<uint64_t> row(depth ? layer_room(n, npairs) : 0);
+    const bool exact = 2 * size_t(npairs) == n;
+    for (uint32_t l = 0; l < depth && bounds[l] < cap; ++l) {
+      const size_t room = cap - bounds[l];
+      uint64_t *to = exact && room >= npairs ? ops + bounds[l] : row.data();
+      size_t cnt = 0;
+      rc = encode_layer(n, l, h, s, ctrl, tgt, npairs, state.data(), to, &cnt);
+      if (rc) return rc;
+      if (to == row.data()) memcpy(ops + bounds[l], to, std::min(cnt, room) * 8);
+    }
+  }
   if (offs) memcpy(offs, bounds.data(), bounds.size() * 4);
   *nops = total;
   if (ops && total > cap) return fail(CLIFF_ENOMEM, "cliff_encode_layers: need %zu words", total);
