@@ -15,11 +15,13 @@
  *    most recent failure on the calling thread.
  *  - Device memory belongs to the caller.  A tableau is a view bound onto one
  *    caller-owned device buffer of cliff_tab_bytes(n, shots) bytes; the library
- *    never frees it.  The context owns only its own staging buffers and the
- *    measurement scratch (allocated at the first measurement, grown to the
- *    largest tableau shape the context has measured: 3 MB at n = 10,000 in
- *    the automatic mode; the register-resident modes take about 270 MB at
- *    n = 4,096, 2.2 GB at n = 10,000; freed by cliff_ctx_destroy).
+ *    never frees it.  The context owns only, each from its first use on and
+ *    until cliff_ctx_destroy: staging buffers for uploads, a pinned area for
+ *    results (at most 16 MB), the measurement scratch (grown to the largest
+ *    tableau shape the context has measured: 3 MB at n = 10,000 in the
+ *    automatic mode; the register-resident modes take about 270 MB at
+ *    n = 4,096, 2.2 GB at n = 10,000) and the decoded gate streams (8 bytes per
+ *    op, layers rounded up to 64 ops, at most 576 MB; grown at least twofold).
  *  - Host pointers are read (inputs) or written (outputs) before the call
  *    returns.  Calls that return host data synchronize the context stream;
  *    the others only enqueue work on it.

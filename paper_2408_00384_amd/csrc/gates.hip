@@ -233,13 +233,13 @@ __device__ __forceinline__ void fused_body(uint64_t *X, uint64_t *Z, uint64_t *P
 //
 // Bound: instruction issue and the LDS accesses at random columns, which
 // hardly overlap in a layer of one round: n = 1,500 (750 ops a layer), per
-// layer and CU, 480 of 850 clocks issue VALU instructions (39 a step) and 456
+// layer and CU, 470 of 840 clocks issue VALU instructions (38 a step) and 456
 // serve LDS (4 x 9.5 a step, 3 each without bank conflicts).  From op words a
 // step took about 200 instructions with its branches (decode, range checks,
-// masks).  From op words -> decoded: n = 1,500, 3,000 layers 1,858 -> 1,061 us
+// masks).  From op words -> decoded: n = 1,500, 3,000 layers 1,858 -> 1,041 us
 // (+ 13 to decode); n = 500 x 100 tableaux, 2,000 layers 1,382 -> 936 (+ 150);
-// n = 64, 64 layers 34 -> 17; n = 1,024, 100 layers 60 -> 38; n = 10,000, 20 layers
-// 302 -> 214 (50 of it by the XCD order of the row groups).
+// n = 64, 64 layers 34 -> 16; n = 1,024, 100 layers 60 -> 37; n = 10,000, 20 layers
+// 302 -> 212 (50 of it by the XCD order of the row groups).
 constexpr uint32_t kSpareCols = 16;
 constexpr uint32_t kDecBits = (1u << 18) - 1;
 constexpr uint32_t kDecCnot = 25, kDecCz = 26, kDecSwap = 27;        // bits of word 1
@@ -572,8 +572,6 @@ __global__ void __launch_bounds__(256) k_gather_words(TabDev t, const uint32_t *
   }
 }
 
-// Outcomes of the last measurement pass (staging: out[i * S + s], kind[i])
-// into a caller's record: rec[s * ld + col0 + i], random flags rnd[col0 + i].
 // Outcomes of shots s0 .. s0 + rows and cnt measurements, transposed from the
 // staging's [measurement][shot] into rows of `pitch` bytes (a multiple of 64)
 // in host memory, and the random flags into `rnd`.  A block turns a tile of 64
@@ -618,6 +616,8 @@ __global__ void __launch_bounds__(256) k_emit_packed(TabDev t, uint32_t cnt, uin
   if (blockIdx.x == 0 && threadIdx.x < cnt) rnd[threadIdx.x] = t.kind[threadIdx.x];
 }
 
+// Outcomes of the last measurement pass (staging: out[i * S + s], kind[i])
+// into a caller's record: rec[s * ld + col0 + i], random flags rnd[col0 + i].
 __global__ void __launch_bounds__(256) k_record(TabDev t, uint32_t cnt, uint8_t *__restrict__ rec, size_t ld,
                                                 size_t col0, uint8_t *__restrict__ rnd) {
   const size_t total = size_t(cnt) * t.S;

@@ -346,9 +346,12 @@ hipError_t launch_gate_layer(const TabDev &t, const uint64_t *ops, uint32_t nops
 // LDS budget of the fused all-layers gate kernel (8 bytes per qubit).
 constexpr size_t kFusedGateLds = 160 * 1024 - 1024;
 bool fused_gates_fit(uint32_t n);
-// Fewest layers worth decoding a stream for: the decode launch costs 5 to 12
-// us, a layer gains 0.2 us and more (n = 64: 0.53 -> 0.26 us, n = 1,024: 0.60
-// -> 0.38, n = 1,500: 0.62 -> 0.35, n = 10,000, 16 waves: 15.1 -> 10.7).
+// Fewest layers worth decoding a stream of one tableau for.  The decode launch
+// costs 5 to 12 us, a layer gains 0.2 us and more (n = 64: 0.53 -> 0.26 us, n =
+// 1,024: 0.60 -> 0.37, n = 1,500: 0.62 -> 0.35, n = 10,000, 16 waves: 15.1 ->
+// 10.6).  16 layers, whole calls, op words / decoded: n = 64 26.6 / 26.1 us,
+// n = 300 30.4 / 30.3, n = 1,024 34.7 / 34.3, of few ops 31.0 / 29.4, n = 4,000 71 /
+// 62, n = 10,000 of few ops 202 / 154.
 constexpr uint32_t kDecodeMinDepth = 16;
 constexpr uint32_t kRoundEnds = 256;       // see launch_gates_decoded
 constexpr uint32_t kDecodeMaxWaves = 16;   // of a workgroup that runs a decoded stream

@@ -47,16 +47,18 @@
 // and k_lr_det_terms, k_lr_det, the deterministic outcomes, at the end of the pass.
 //
 // Bound: the sweep reads and writes the tableau once per 64 measurements and
-// takes 32 table reads per word of x and z (21 us a launch at n = 10,000: LDS
-// reads and memory about even; 71 us at n = 25,000, half written back: memory);
-// below n = 6,000 the planner's chain of 64 dependent steps (0.11 us each;
+// takes 32 table reads per two words of x and z.  n = 10,000: 21 us a launch,
+// vector instructions 72 % of the busy cycles, LDS 36 %, the tableau in the
+// last-level cache at 0.57 of a plain copy's rate; n = 25,000: 123 us, memory, at
+// 0.96 of a plain copy's rate (the launches before the first and after the last
+// block, which touch no tableau, 22 and 17 us); below n = 6,000 the planner's chain of 64 dependent steps (0.11 us each;
 // 11 us a sweep launch at n = 1,024) and the prep launch's chain of loads (7
 // to 8 us).  Against one rowsum sweep per measurement (register-resident up to
 // n = 10,240, one kernel per measurement above), circuit and measure-all:
 // n = 64, 16 shots 0.114 against 0.389 ms; n = 1,024, 128 shots 0.44 against
 // 2.68 ms; n = 3,001 after 2 layers, a third of the outcomes deterministic,
-// 1.21 against 7.28 ms; n = 5,003 1.84 against 8.23 ms; n = 10,000 4.74 against
-// 16.4 ms (blocks of 32 in registers); 128 of n = 25,000 2.29 against 12.3 ms.
+// 1.21 against 7.28 ms; n = 5,003 1.84 against 8.23 ms; n = 10,000 4.9 against
+// 16.4 ms (blocks of 32 in registers); 128 of n = 25,000 2.30 against 12.3 ms.
 // Blocks of 64: twice the work per launch of 32 at the same number of tableau
 // passes, and a row's bits are one 64-bit word.
 #include <algorithm>

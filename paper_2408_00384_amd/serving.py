@@ -11,9 +11,12 @@ others run is enqueued right away and overlaps on the device:
     for it in device memory (its op stream, layer offsets, descriptor and
     outcome bytes, request_bytes below).  A request waits until its bytes
     fit; one larger than the whole budget is rejected.  Each HBM lane's
-    context also keeps the register-resident measurement's chunk scratch,
-    sized once by the largest tableau shape the lane has measured (about
-    270 MB at n = 4,096); it is not charged per request;
+    context also keeps, not charged per request, the measurement's scratch
+    (under 1 MB at n = 4,096), the decoded form of its longest gate stream (8
+    bytes per op, layers rounded up to 64 ops: 134 MB at n = 4,096 and depth
+    2n; up to twice that as streams grow, never over 576 MB), its longest op
+    stream, and pinned host memory for uploads (4 MB) and results (at most 16
+    MB);
   * HBM lanes: requests that do not fit the batched kernel (n > 256 or more
     than 64 shots) run on one of several streams, each with its own context:
     tableau bound inside the arena, |0...0>, all gate layers, then all
