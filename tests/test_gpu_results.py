@@ -50,14 +50,33 @@ def test_outcomes_match_the_device_record(ctx, n, shots, k):
 @pytest.mark.parametrize("n,shots,k", [(1, 1, 1), (31, 63, 3), (32, 64, 31), (127, 65, 32), (129, 130, 33),
                                        (500, 5, 200)])
 def test_cond_paulis_vs_oracle(ctx, n, shots, k):
-    _cond_paulis(ctx, n, shots, k)
+    import torch
+    from paper_2408_00384_amd import DeviceTableau, cliff_apply_cond_paulis
+    c = layered_circuit(n, 6, 1, gen_seed=[96, n], circuit_id=32)
+    rng = np.random.default_rng([n, k])
+    q, p, col = rng.integers(0, n, k).astype(np.uint32), rng.integers(1, 4, k).astype(np.uint8), \
+        rng.integers(0, 9, k).astype(np.uint32)
+    bits = rng.integers(0, 2, (shots, 9)).astype(np.uint8)
+    rec = torch.from_numpy(bits).to("cuda:0")
+    torch.cuda.synchronize()
+    t = DeviceTableau(ctx, n, shots).apply_circuit_gates(c)
+    cliff_apply_cond_paulis(t.handle, q, p, col, rec.data_ptr(), 9)
+    gx, gz, gr = t.export()
+    for s in {0, shots // 2, shots - 1}:
+        r = oracle.Tableau(n).apply_circuit_gates(c)
+        for i in range(k):
+            if bits[s, col[i]]:
+                r.pauli(int(q[i]), int(p[i]))
+        x, z, rr = r.get()
+        assert np.array_equal(gx, x) and np.array_equal(gz, z) and np.array_equal(gr[s], rr)
+    t.close()
 
 
 # the ops of a wave in fours and one by one, and either side of 16, from where
 # on a block's waves share them
 @pytest.mark.parametrize("n,shots,k", [(33, 1, 4), (64, 64, 5), (65, 600, 7), (130, 129, 15), (130, 129, 16)])
 def test_few_cond_paulis_vs_oracle(ctx, n, shots, k):
-    _cond_paulis(ctx, n, shots, k)
+    test_cond_paulis_vs_oracle(ctx, n, shots, k)
 
 
 def test_one_cond_pauli_costs_less_than_sixteen(ctx):
@@ -80,29 +99,6 @@ def test_one_cond_pauli_costs_less_than_sixteen(ctx):
             times.append(time.perf_counter() - t0)
         best[k] = min(times)
     assert best[1] < best[16] / 2, best
-    t.close()
-
-
-def _cond_paulis(ctx, n, shots, k):
-    import torch
-    from paper_2408_00384_amd import DeviceTableau, cliff_apply_cond_paulis
-    c = layered_circuit(n, 6, 1, gen_seed=[96, n], circuit_id=32)
-    rng = np.random.default_rng([n, k])
-    q, p, col = rng.integers(0, n, k).astype(np.uint32), rng.integers(1, 4, k).astype(np.uint8), \
-        rng.integers(0, 9, k).astype(np.uint32)
-    bits = rng.integers(0, 2, (shots, 9)).astype(np.uint8)
-    rec = torch.from_numpy(bits).to("cuda:0")
-    torch.cuda.synchronize()
-    t = DeviceTableau(ctx, n, shots).apply_circuit_gates(c)
-    cliff_apply_cond_paulis(t.handle, q, p, col, rec.data_ptr(), 9)
-    gx, gz, gr = t.export()
-    for s in {0, shots // 2, shots - 1}:
-        r = oracle.Tableau(n).apply_circuit_gates(c)
-        for i in range(k):
-            if bits[s, col[i]]:
-                r.pauli(int(q[i]), int(p[i]))
-        x, z, rr = r.get()
-        assert np.array_equal(gx, x) and np.array_equal(gz, z) and np.array_equal(gr[s], rr)
     t.close()
 
 
